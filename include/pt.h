@@ -394,7 +394,8 @@ pt_status pt_nrc_training_records(pt_scene* scene, const pt_camera* camera, int3
 
 /* Tail hand-off of the sampling passes.  A pass runs the wavefront kernels
  * (one launch per stage per bounce) while many paths are alive; from bounce
- * min_bounce on, once at most max_fraction of the pass's paths are still
+ * min_bounce on, once at most max_fraction of the pass's paths (counted from
+ * at most 2^21 of them: a pass holds several samples of every pixel) are still
  * alive, one persistent kernel runs all remaining vertices of every path
  * (closest hit, shading, shadow ray, next ray) without a kernel boundary
  * per bounce.  The decision reads one counter back per pass.  Results are

@@ -86,7 +86,6 @@ bool finite_all(const float* p, size_t n) {
 
 // Device buffers of one set of path slots (struct-of-arrays).
 struct PathBufs {
-  int64_t capacity = 0, nrc_q_cap = 0;
   DevBuf ray_o, ray_d, hit, hit_inst, cls, beta, L, flags, q_ray[2], q_cls[kNumClasses], sh_o, sh_d, sh_c, sh_inst,
       counts, sig, dbg_nee, dbg_tail, spill, nrc_q, q_nrc, spread;
 };
@@ -317,29 +316,42 @@ pt_status ensure_lights(pt_scene* s) {
   return PT_OK;
 }
 
-pt_status ensure_paths(pt_scene* s, int64_t n, int set = 0) {
+// Path buffers of a set for n slots: what every pass needs, and what this
+// scene's materials, instances, cache options or signatures (debug) need
+// (161 bytes a slot on the icosphere field).
+hipError_t alloc_paths(pt_scene* s, int64_t n, int set, bool debug) {
   PathBufs& B = s->pb[set];
-  if (n <= B.capacity) return PT_OK;
-  size_t f4 = (size_t)n * sizeof(float4), u4 = (size_t)n * sizeof(uint32_t);
-  PT_HIP(B.ray_o.alloc(f4));
-  PT_HIP(B.ray_d.alloc(f4));
-  PT_HIP(B.hit.alloc(f4));
-  PT_HIP(B.hit_inst.alloc(u4));
-  PT_HIP(B.cls.alloc((size_t)n));
-  PT_HIP(B.sh_inst.alloc(u4));
-  PT_HIP(B.beta.alloc(f4));
-  PT_HIP(B.L.alloc(f4));
-  PT_HIP(B.flags.alloc(u4));
-  for (int i = 0; i < 2; ++i) PT_HIP(B.q_ray[i].alloc(u4));
-  for (int i = 0; i < kNumClasses; ++i) PT_HIP(B.q_cls[i].alloc(u4));
-  PT_HIP(B.sh_o.alloc(f4));
-  PT_HIP(B.sh_d.alloc(f4));
-  PT_HIP(B.sh_c.alloc(f4));
-  PT_HIP(B.sig.alloc((size_t)n * sizeof(uint64_t)));
-  PT_HIP(B.dbg_nee.alloc(u4));
-  PT_HIP(B.dbg_tail.alloc(u4));
-  PT_HIP(B.spread.alloc((size_t)n * sizeof(float2)));
-  B.capacity = n;
+  const size_t f4 = (size_t)n * sizeof(float4), u4 = (size_t)n * sizeof(uint32_t);
+  hipError_t e = hipSuccess;
+  for (DevBuf* b : {&B.ray_o, &B.ray_d, &B.hit, &B.beta, &B.L, &B.sh_o, &B.sh_d, &B.sh_c})
+    if (e == hipSuccess) e = b->alloc(f4);
+  for (DevBuf* b : {&B.flags, &B.q_ray[0], &B.q_ray[1]})
+    if (e == hipSuccess) e = b->alloc(u4);
+  if (e == hipSuccess) e = B.cls.alloc((size_t)n);
+  for (int i = 0; i < kNumClasses; ++i)
+    if (e == hipSuccess && ((s->class_mask | (1u << kClsMiss)) & (1u << i))) e = B.q_cls[i].alloc(u4);
+  if (s->two_level)
+    for (DevBuf* b : {&B.hit_inst, &B.sh_inst})
+      if (e == hipSuccess) e = b->alloc(u4);
+  if (debug) {
+    for (DevBuf* b : {&B.dbg_nee, &B.dbg_tail})
+      if (e == hipSuccess) e = b->alloc(u4);
+    if (e == hipSuccess) e = B.sig.alloc((size_t)n * sizeof(uint64_t));
+  }
+  if (s->nrc_on && s->nrc_cfg.spread_c > 0.0f && e == hipSuccess) e = B.spread.alloc((size_t)n * sizeof(float2));
+  return e;
+}
+
+void release_paths(PathBufs& B) {
+  for (DevBuf* b : {&B.ray_o, &B.ray_d, &B.hit, &B.hit_inst, &B.cls, &B.beta, &B.L, &B.flags, &B.q_ray[0],
+                    &B.q_ray[1], &B.sh_o, &B.sh_d, &B.sh_c, &B.sh_inst, &B.sig, &B.dbg_nee, &B.dbg_tail, &B.spread,
+                    &B.nrc_q, &B.q_nrc})
+    b->release();
+  for (DevBuf& b : B.q_cls) b.release();
+}
+
+pt_status ensure_paths(pt_scene* s, int64_t n, int set = 0, bool debug = false) {
+  PT_HIP(alloc_paths(s, n, set, debug));
   return PT_OK;
 }
 
@@ -365,12 +377,23 @@ pt_status ensure_counters(pt_scene* s, int set = 0) {
   return PT_OK;
 }
 
-pt_status ensure_spill(pt_scene* s, int grid_trace, int set = 0) {
+hipError_t alloc_spill(pt_scene* s, int grid_trace, int set) {
   int cap = stack_capacity(s->bvh_depth);
   size_t per = cap > kLdsStack ? (size_t)(cap - kLdsStack) : 1;
   size_t bytes = per * (size_t)grid_trace * kBlock * sizeof(uint2);
-  PT_HIP(s->pb[set].spill.alloc(bytes));
+  return s->pb[set].spill.alloc(bytes);
+}
+
+pt_status ensure_spill(pt_scene* s, int grid_trace, int set = 0) {
+  PT_HIP(alloc_spill(s, grid_trace, set));
   return PT_OK;
+}
+
+// Cache-query records and queue of a set, for n sampling paths.
+hipError_t alloc_queries(pt_scene* s, int64_t n, int set) {
+  PathBufs& B = s->pb[set];
+  hipError_t e = B.nrc_q.alloc((size_t)n * kNrcQueryFloats * sizeof(float));
+  return e == hipSuccess ? B.q_nrc.alloc((size_t)n * sizeof(uint32_t)) : e;
 }
 
 SceneDev scene_dev(pt_scene* s, int grid_trace, int set = 0) {
@@ -416,7 +439,9 @@ SceneDev scene_dev(pt_scene* s, int grid_trace, int set = 0) {
   return S;
 }
 
-PathsDev paths_dev(pt_scene* s, int64_t n, int x0, int y0, int w, int set = 0) {
+// Device view of a path set holding `spp` samples of each pixel of the tile (x0, y0, w, h).
+PathsDev paths_dev(pt_scene* s, int x0, int y0, int w, int h, int spp, int set = 0) {
+  const int64_t n = (int64_t)w * h * spp;
   PathBufs& B = s->pb[set];
   PathsDev P;
   std::memset(&P, 0, sizeof(P));
@@ -446,6 +471,8 @@ PathsDev paths_dev(pt_scene* s, int64_t n, int x0, int y0, int w, int set = 0) {
   P.x0 = x0;
   P.y0 = y0;
   P.w = w;
+  P.h = h;
+  P.spp = (uint32_t)spp;
   P.train_end = -1;
   P.nrc_factor = s->nrc_on && s->nrc_cfg.factorize ? 1 : 0;
   return P;
@@ -615,22 +642,54 @@ pt_status shade_streams(pt_scene* s, PassArgs& A) {
   return PT_OK;
 }
 
+// Slots of a sampling pass with several samples per pixel.  A pass of few
+// paths is bound by its launches and by each launch's longest ray (the box at
+// 128x128, 16 spp: 16 passes of 16K slots 4.66 ms, one pass of 262K 0.46 ms).
+// Icosphere field 1080p, 64 spp: 2^21 slots 157.7 ms, 2^22 140.1, 2^23 118.7,
+// 2^24 108.5, 2^25 102.9 (2^25 slots: 5.4 GB a path set); 512x512, 100 spp:
+// 26.7 / 25.2 / 21.6 / 19.9 / 18.9 ms.
+constexpr int64_t kPassSlots = 1 << 25;
+
+// Samples per pixel of a pass: as many as fit kPassSlots, spread evenly over
+// the passes of a call of n samples.
+int pass_samples(int64_t pixels, int n, int64_t slots = kPassSlots) {
+  const int64_t most = std::max<int64_t>(1, slots / pixels);
+  const int64_t passes = (n + most - 1) / most;
+  return (int)((n + passes - 1) / passes);
+}
+
 pt_status run_passes(pt_scene* s, const CamDev& C, int x0, int y0, int w, int h, int first, int n, int max_depth,
                      uint64_t seed, double* sum, float* per_sample, uint64_t* sigs, int spp_total,
                      bool train = false) {
-  int64_t N = (int64_t)w * h;
-  int64_t slots = N + (train ? s->nrc_cfg.train_paths : 0);
+  const int64_t N = (int64_t)w * h;
   const bool use_cache = s->nrc_on && s->nrc_ready;
   const bool tail = s->tail_fraction > 0.0 && s->tail_min_bounce <= max_depth;
-  const bool overlap = !train && !use_cache && tail && n > 1;
-  const int nsets = overlap ? 2 : 1;
+  int spp_max = train ? 1 : pass_samples(N, n);  // samples per pixel of a pass
+  int64_t slots = 0;
+  int n_passes = 0, nsets = 1;
+  bool overlap = false;
+  while (true) {
+    n_passes = (n + spp_max - 1) / spp_max;
+    slots = N * spp_max + (train ? s->nrc_cfg.train_paths : 0);
+    overlap = !train && !use_cache && tail && n_passes > 1;
+    nsets = overlap ? 2 : 1;
+    hipError_t e = hipSuccess;
+    for (int set = 0; set < nsets && e == hipSuccess; ++set) {
+      e = alloc_paths(s, slots, set, per_sample != nullptr);
+      if (e == hipSuccess) e = alloc_spill(s, traversal_grid(slots), set);
+      if (e == hipSuccess && use_cache) e = alloc_queries(s, N * spp_max, set);
+    }
+    if (e == hipSuccess) break;
+    // the device has less memory left than these passes need: smaller passes
+    if (e != hipErrorOutOfMemory || spp_max == 1) PT_HIP(e);
+    (void)hipGetLastError();
+    for (PathBufs& B : s->pb) release_paths(B);
+    spp_max = pass_samples(N, n, N * ((spp_max + 1) / 2));
+  }
   int grid = grid_for(slots), grid_trace = traversal_grid(slots);
   pt_status r = PT_OK;
-  for (int set = 0; set < nsets; ++set) {
-    if ((r = ensure_paths(s, slots, set))) return r;
+  for (int set = 0; set < nsets; ++set)
     if ((r = ensure_counters(s, set))) return r;
-    if ((r = ensure_spill(s, grid_trace, set))) return r;
-  }
   if (!s->tail_counts) PT_HIP(hipHostMalloc((void**)&s->tail_counts, 2 * sizeof(uint32_t), hipHostMallocDefault));
   if (overlap) {
     if (!s->stream2) PT_HIP(hipStreamCreateWithFlags(&s->stream2, hipStreamNonBlocking));
@@ -646,14 +705,16 @@ pt_status run_passes(pt_scene* s, const CamDev& C, int x0, int y0, int w, int h,
   int wavefront[2] = {max_depth + 1, max_depth + 1}, traces[2] = {0, 0};
   bool tail_on_2[2] = {false, false};
   int pending = -1;  // path set whose timing events are not read yet (overlap)
-  for (int k = 0; k < n; ++k) {
+  for (int k = 0; k < n_passes; ++k) {
     const int set = overlap ? (k & 1) : 0;
+    // the samples spread evenly over the passes
+    const int k0 = (int)((int64_t)n * k / n_passes), spp = (int)((int64_t)n * (k + 1) / n_passes) - k0;
     SceneDev S = scene_dev(s, grid_trace, set);
-    PathsDev P = paths_dev(s, N, x0, y0, w, set);
+    PathsDev P = paths_dev(s, x0, y0, w, h, spp, set);
     if (train && (r = setup_training(s, C, P, N, (uint32_t)first, max_depth, seed))) return r;
     PassArgs A;
     std::memset(&A, 0, sizeof(A));
-    A.sample = (uint32_t)(first + k);
+    A.sample = (uint32_t)(first + k0);
     A.k0 = (uint32_t)seed;
     A.k1 = (uint32_t)(seed >> 32);
     A.max_depth = max_depth;
@@ -667,11 +728,6 @@ pt_status run_passes(pt_scene* s, const CamDev& C, int x0, int y0, int w, int h,
     A.nrc_bounce = -1;
     if (use_cache) {
       PathBufs& B = s->pb[set];
-      if (N > B.nrc_q_cap) {
-        PT_HIP(B.nrc_q.alloc((size_t)N * kNrcQueryFloats * sizeof(float)));
-        PT_HIP(B.q_nrc.alloc((size_t)N * sizeof(uint32_t)));
-        B.nrc_q_cap = N;
-      }
       A.nrc_bounce = s->nrc_cfg.query_bounce;
       A.nrc_fwd = s->nrc_inf.as<uint4>();
       P.nrc_q = B.nrc_q.as<float>();
@@ -709,7 +765,7 @@ pt_status run_passes(pt_scene* s, const CamDev& C, int x0, int y0, int w, int h,
         PT_HIP(hipStreamWaitEvent(s->stream2, s->ev_bulk[set], 0));
       }
     }
-    PT_HIP(launch_accumulate(P, sum, C.W, per_sample, sigs, spp_total, k, acc));
+    PT_HIP(launch_accumulate(P, sum, C.W, per_sample, sigs, spp_total, k0, acc));
     if (ev) PT_HIP(hipEventRecord(ev[1], acc));
     if (overlap) PT_HIP(hipEventRecord(s->ev_done[set], s->stream2));
     if (ev) {
@@ -732,9 +788,8 @@ pt_status run_passes(pt_scene* s, const CamDev& C, int x0, int y0, int w, int h,
   s->samples += (int64_t)n * N;
   if (train) {
     auto t0 = std::chrono::steady_clock::now();
-    PathsDev P = paths_dev(s, N, x0, y0, w, 0);
+    PathsDev P = paths_dev(s, x0, y0, w, h, 1, 0);
     P.n = (int32_t)slots;
-    P.n_render = (int32_t)N;
     P.rec = s->nrc_rec[0].as<float>();
     P.rec_depth = max_depth;
     if ((r = finish_training(s, P, nullptr, s->stream, true))) return r;
@@ -766,13 +821,8 @@ pt_status run_cache_frames(pt_scene* s, const CamDev& C, int first, int n, int m
     if ((r = ensure_paths(s, slots, set))) return r;
     if ((r = ensure_counters(s, set))) return r;
     if ((r = ensure_spill(s, grid_trace, set))) return r;
-    PathBufs& B = s->pb[set];
-    if (N > B.nrc_q_cap) {
-      PT_HIP(B.nrc_q.alloc((size_t)N * kNrcQueryFloats * sizeof(float)));
-      PT_HIP(B.q_nrc.alloc((size_t)N * sizeof(uint32_t)));
-      B.nrc_q_cap = N;
-    }
-    Ps[set] = paths_dev(s, N, 0, 0, C.W, set);
+    PT_HIP(alloc_queries(s, N, set));
+    Ps[set] = paths_dev(s, 0, 0, C.W, C.H, 1, set);
     if ((r = setup_training(s, C, Ps[set], N, (uint32_t)first, max_depth, seed, set))) return r;
   }
   if ((r = nrc_ensure_ws(s, s->nrc_cfg.batch_size))) return r;
@@ -976,7 +1026,7 @@ pt_status nrc_trace_training(pt_scene* s, const CamDev& C, uint32_t frame, int m
   int grid = grid_for(n), grid_trace = traversal_grid(n);
   if ((r = ensure_spill(s, grid_trace))) return r;
   SceneDev S = scene_dev(s, grid_trace);
-  PathsDev P = paths_dev(s, 0, 0, 0, 1);
+  PathsDev P = paths_dev(s, 0, 0, 1, 0, 1);
   if ((r = setup_training(s, C, P, 0, frame, max_depth, seed))) return r;
   PassArgs A;
   std::memset(&A, 0, sizeof(A));

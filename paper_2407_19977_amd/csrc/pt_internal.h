@@ -75,7 +75,7 @@ struct PathsDev {
   uint8_t* cls;        // material class of the hit (binning)
   float4* beta;        // throughput rgb, pdf of the last BSDF sample
   float4* L;           // radiance rgb, eta scale (product of eta^2 over refractions)
-  uint32_t* flags;     // bit 0: last bounce was a delta lobe
+  uint32_t* flags;     // bit 0: last bounce was a delta lobe; bits 1..: pixel index (row-major)
   uint32_t* q_ray[2];  // extension queues (double-buffered)
   uint32_t* q_cls[kNumClasses];
   float4* sh_o;        // shadow ray o.xyz, tmax
@@ -89,7 +89,10 @@ struct PathsDev {
   uint32_t* dbg_tail;  // pending lobe / roulette / end events (debug)
   int32_t n;           // number of path slots: n_render sampling paths, then training paths
   int32_t n_render;
-  int32_t x0, y0, w;   // sampling path slot -> pixel (x0 + slot % w, y0 + slot / w)
+  // sampling path slots: `spp` samples of every pixel of the tile (x0, y0, w, h), slot =
+  // place * spp + sample of the pass, places in blocks of pixels (place_pixel)
+  int32_t x0, y0, w, h;
+  uint32_t spp;
   // training path k = slot - n_render: pixel index (k * pix_stride + pix_off) mod pix_total,
   // sample index train_sample
   uint32_t pix_stride, pix_off, pix_total, train_sample;
@@ -149,8 +152,8 @@ struct PassArgs {
   int nrc_bounce;          // vertex at which paths end in the radiance cache, -1: no cache
   const uint4* nrc_fwd;    // packed forward weight fragments (when nrc_bounce >= 0)
   hipEvent_t* nrc_events;  // 2 events around the cache-query kernel when timing, else nullptr
-  // tail hand-off: from bounce tail_min_bounce on, when at most tail_fraction of the slots are
-  // still alive, one persistent kernel finishes the paths (tail_host_count: pinned host word)
+  // tail hand-off: from bounce tail_min_bounce on, when at most tail_fraction of the slots (of
+  // the first 2^21 of a larger pass) are still alive, one persistent kernel finishes the paths (tail_host_count: pinned host word)
   uint32_t* tail_host_count;
   int tail_min_bounce;
   double tail_fraction;
@@ -175,7 +178,7 @@ struct PassArgs {
 hipError_t launch_pass(const SceneDev& S, const PathsDev& P, const CamDev& C, const PassArgs& A,
                        hipStream_t st);
 hipError_t launch_accumulate(const PathsDev& P, double* sum, int W, float* per_sample, uint64_t* sig_out,
-                             int spp_total, int sample_index, hipStream_t st);
+                             int spp_total, int first_index, hipStream_t st);
 hipError_t launch_resolve(const double* sum, float* out, int64_t n_values, double inv_spp, hipStream_t st);
 hipError_t launch_zero_f64(double* p, int64_t n, hipStream_t st);
 // display image of the running mean (pt_display.hip): rgba8 and encoded are nullable

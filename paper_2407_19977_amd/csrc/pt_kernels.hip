@@ -1,7 +1,7 @@
 // Wavefront path-tracing kernels for gfx950 (wave64).
 //
-// One sampling pass traces one path per slot (one sample of every pixel of
-// the tile) through the loop
+// One sampling pass traces one path per slot (one or more samples of every
+// pixel of the tile) through the loop
 //   generate -> [reset -> traverse -> bin -> shade<class>...] x (max_depth+1) -> traverse -> accumulate
 // where traverse finds the closest hits of a bounce's rays together with the
 // shadow rays of the previous bounce's shading.  From bounce 2 on, once few
@@ -262,16 +262,33 @@ __device__ inline float pow_heuristic(float a, float b) {
 
 __device__ inline bool finite3(V3 c) { return isfinite(c.x) && isfinite(c.y) && isfinite(c.z); }
 
-// Pixel index (row-major) and sample index of a path slot: a tile of the
-// image for sampling paths, the strided pixel set of the radiance cache's
-// training paths after them.
-__device__ inline uint32_t slot_pixel(const PathsDev& P, uint32_t slot, uint32_t img_w) {
-  if (slot >= (uint32_t)P.n_render)
-    return (uint32_t)(((uint64_t)(slot - (uint32_t)P.n_render) * P.pix_stride + P.pix_off) % P.pix_total);
-  return (uint32_t)(P.y0 + slot / P.w) * img_w + (uint32_t)(P.x0 + slot % P.w);
+// Pixel (x, y) of place p of a w x h tile: rows in bands of kPixBlock, each
+// band in blocks of kPixBlock columns (the last band and block of a band may
+// be narrower), row-major inside a block.  A bijection of [0, w h) for any w
+// and h.  Neighbouring slots are then neighbouring pixels in both directions,
+// and the samples of one pixel are adjacent, so a wave's rays start in a small
+// square of the image.  Icosphere field 512x512, 100 spp: rows instead of
+// blocks 20.1 ms, blocks of 4 19.8, of 8 19.9, of 16 19.9 with the samples
+// apart (16 pixels, then their next sample); 19.3 with the samples adjacent.
+#ifndef PT_PIX_BLOCK
+#define PT_PIX_BLOCK 8
+#endif
+constexpr uint32_t kPixBlock = PT_PIX_BLOCK;
+__device__ inline void place_pixel(uint32_t p, uint32_t w, uint32_t h, uint32_t& x, uint32_t& y) {
+  const uint32_t band = p / (kPixBlock * w), r = p - band * (kPixBlock * w);
+  const uint32_t bh = min(kPixBlock, h - band * kPixBlock);
+  const uint32_t blk = r / (kPixBlock * bh), q = r - blk * (kPixBlock * bh);
+  const uint32_t bw = min(kPixBlock, w - blk * kPixBlock);
+  const uint32_t ly = q / bw;
+  x = blk * kPixBlock + (q - ly * bw);
+  y = band * kPixBlock + ly;
 }
+
+// Sample index of a path slot (`sample`: the pass's first): sampling paths
+// (slot = place * spp + sample of the pass), then the radiance cache's
+// training paths.
 __device__ inline uint32_t slot_sample(const PathsDev& P, uint32_t slot, uint32_t sample) {
-  return slot >= (uint32_t)P.n_render ? P.train_sample : sample;
+  return slot >= (uint32_t)P.n_render ? P.train_sample : sample + slot % P.spp;
 }
 
 // ---------------------------------------------------------------- generate
@@ -280,9 +297,21 @@ __global__ __launch_bounds__(kBlock) void k_generate(PathsDev P, CamDev C, uint3
                                                      uint32_t k1) {
   int n = P.n;
   for (int slot = blockIdx.x * kBlock + threadIdx.x; slot < n; slot += gridDim.x * kBlock) {
-    uint32_t pix = slot_pixel(P, (uint32_t)slot, (uint32_t)C.W);
-    int px = (int)(pix % (uint32_t)C.W), py = (int)(pix / (uint32_t)C.W);
-    U4 r = philox(pix, slot_sample(P, (uint32_t)slot, sample), 0u, 0u, k0, k1);
+    uint32_t pix, px, py, smp;
+    if (slot >= P.n_render) {  // training path: the strided pixel set
+      pix = (uint32_t)(((uint64_t)(slot - P.n_render) * P.pix_stride + P.pix_off) % P.pix_total);
+      px = pix % (uint32_t)C.W;
+      py = pix / (uint32_t)C.W;
+      smp = P.train_sample;
+    } else {
+      const uint32_t place = (uint32_t)slot / P.spp;
+      smp = sample + ((uint32_t)slot - place * P.spp);
+      place_pixel(place, (uint32_t)P.w, (uint32_t)P.h, px, py);
+      px += (uint32_t)P.x0;
+      py += (uint32_t)P.y0;
+      pix = py * (uint32_t)C.W + px;
+    }
+    U4 r = philox(pix, smp, 0u, 0u, k0, k1);
     float fx = (float)px + u01(r.x), fy = (float)py + u01(r.y);
     float x = (2.0f * fx / (float)C.W - 1.0f) * C.tan_half * C.aspect;
     float y = (1.0f - 2.0f * fy / (float)C.H) * C.tan_half;
@@ -291,7 +320,7 @@ __global__ __launch_bounds__(kBlock) void k_generate(PathsDev P, CamDev C, uint3
     P.ray_d[slot] = make_float4(d.x, d.y, d.z, u2f(0xFFFFFFFFu));
     P.beta[slot] = make_float4(1.0f, 1.0f, 1.0f, 0.0f);
     P.L[slot] = make_float4(0.0f, 0.0f, 0.0f, 1.0f);
-    P.flags[slot] = 1u;
+    P.flags[slot] = (pix << 1) | 1u;
     P.q_ray[0][slot] = (uint32_t)slot;
     if (DEBUG) P.sig[slot] = kFnvOffset;
     if (P.rec && slot >= P.n_render)
@@ -596,7 +625,7 @@ struct ShadeOut {
 // sampling, Russian roulette and the next ray.
 template <int CLS, bool DEBUG, bool TWO>
 __device__ inline void shade_one(const SceneDev& S, const PathsDev& P, uint32_t slot, int b, int max_depth,
-                                 uint32_t sample, uint32_t k0, uint32_t k1, uint32_t img_w, int nrc_bounce,
+                                 uint32_t sample, uint32_t k0, uint32_t k1, int nrc_bounce,
                                  ShadeOut& o, unsigned long long& nonfinite) {
   o.cont = o.shadow = o.query = false;
   float4 rd = P.ray_d[slot];
@@ -736,7 +765,7 @@ __device__ inline void shade_one(const SceneDev& S, const PathsDev& P, uint32_t 
       V3 wo = v3(dot(wo_w, t), dot(wo_w, bt), dot(wo_w, n));
       Bsdf B = bsdf_setup<CLS>(m, entering, wo.z);
       if (wo.z <= 0.0f) B.absorbed = true;
-      Rng rng{slot_pixel(P, slot, img_w), slot_sample(P, slot, sample), k0, k1};
+      Rng rng{flags >> 1, slot_sample(P, slot, sample), k0, k1};
       U4 r0 = rng.block((uint32_t)b, 0u), r1 = rng.block((uint32_t)b, 1u);
       // next-event estimation
       if (!B.absorbed && bsdf_has_nondelta<CLS>(m, B)) {
@@ -790,7 +819,7 @@ __device__ inline void shade_one(const SceneDev& S, const PathsDev& P, uint32_t 
           P.ray_o[slot] = make_float4(p.x, p.y, p.z, u2f(prim));
           P.ray_d[slot] = make_float4(dn.x, dn.y, dn.z, u2f(inst));
           P.beta[slot] = make_float4(beta.x, beta.y, beta.z, pdf_prev);
-          P.flags[slot] = prev_delta ? 1u : 0u;
+          P.flags[slot] = (flags & ~1u) | (prev_delta ? 1u : 0u);
           o.cont = true;
         }
       }
@@ -816,7 +845,7 @@ __device__ inline void shade_one(const SceneDev& S, const PathsDev& P, uint32_t 
 
 template <int CLS, bool DEBUG, bool TWO>
 __global__ __launch_bounds__(kShadeBlock) void k_shade(SceneDev S, PathsDev P, int b, int max_depth, int next,
-                                                  uint32_t sample, uint32_t k0, uint32_t k1, uint32_t img_w,
+                                                  uint32_t sample, uint32_t k0, uint32_t k1,
                                                   int nrc_bounce) {
   // per queue (next rays, shadow rays, cache queries): wave counts, then the workgroup's base
   __shared__ uint32_t s_app[3][kShadeBlock / 64 + 1];
@@ -830,7 +859,7 @@ __global__ __launch_bounds__(kShadeBlock) void k_shade(SceneDev S, PathsDev P, i
     o.cont = o.shadow = o.query = false;
     if (active) {
       slot = P.q_cls[CLS][i];
-      shade_one<CLS, DEBUG, TWO>(S, P, slot, b, max_depth, sample, k0, k1, img_w, nrc_bounce, o, nonfinite);
+      shade_one<CLS, DEBUG, TWO>(S, P, slot, b, max_depth, sample, k0, k1, nrc_bounce, o, nonfinite);
     }
     // One atomic per queue per workgroup iteration: the queue counters are
     // single words that every workgroup of the launch appends to.
@@ -1004,23 +1033,23 @@ __global__ __launch_bounds__(kBlock, kTraceWaves) void k_traverse(SceneDev S, Pa
 // walks and signatures are the same code as the wavefront kernels'.
 template <bool DEBUG, bool TWO>
 __device__ inline void shade_any(int cls, const SceneDev& S, const PathsDev& P, uint32_t slot, int b, int max_depth,
-                                 uint32_t sample, uint32_t k0, uint32_t k1, uint32_t img_w, int nrc_bounce,
+                                 uint32_t sample, uint32_t k0, uint32_t k1, int nrc_bounce,
                                  ShadeOut& o, unsigned long long& nf) {
   const int q = nrc_bounce;
   switch (cls) {
-    case kClsMiss: shade_one<kClsMiss, DEBUG, TWO>(S, P, slot, b, max_depth, sample, k0, k1, img_w, q, o, nf); break;
-    case kClsAbsorb: shade_one<kClsAbsorb, DEBUG, TWO>(S, P, slot, b, max_depth, sample, k0, k1, img_w, q, o, nf); break;
-    case kClsDiffuse: shade_one<kClsDiffuse, DEBUG, TWO>(S, P, slot, b, max_depth, sample, k0, k1, img_w, q, o, nf); break;
-    case kClsMetal: shade_one<kClsMetal, DEBUG, TWO>(S, P, slot, b, max_depth, sample, k0, k1, img_w, q, o, nf); break;
-    case kClsPlastic: shade_one<kClsPlastic, DEBUG, TWO>(S, P, slot, b, max_depth, sample, k0, k1, img_w, q, o, nf); break;
-    case kClsGlass: shade_one<kClsGlass, DEBUG, TWO>(S, P, slot, b, max_depth, sample, k0, k1, img_w, q, o, nf); break;
-    default: shade_one<kClsGeneral, DEBUG, TWO>(S, P, slot, b, max_depth, sample, k0, k1, img_w, q, o, nf); break;
+    case kClsMiss: shade_one<kClsMiss, DEBUG, TWO>(S, P, slot, b, max_depth, sample, k0, k1, q, o, nf); break;
+    case kClsAbsorb: shade_one<kClsAbsorb, DEBUG, TWO>(S, P, slot, b, max_depth, sample, k0, k1, q, o, nf); break;
+    case kClsDiffuse: shade_one<kClsDiffuse, DEBUG, TWO>(S, P, slot, b, max_depth, sample, k0, k1, q, o, nf); break;
+    case kClsMetal: shade_one<kClsMetal, DEBUG, TWO>(S, P, slot, b, max_depth, sample, k0, k1, q, o, nf); break;
+    case kClsPlastic: shade_one<kClsPlastic, DEBUG, TWO>(S, P, slot, b, max_depth, sample, k0, k1, q, o, nf); break;
+    case kClsGlass: shade_one<kClsGlass, DEBUG, TWO>(S, P, slot, b, max_depth, sample, k0, k1, q, o, nf); break;
+    default: shade_one<kClsGeneral, DEBUG, TWO>(S, P, slot, b, max_depth, sample, k0, k1, q, o, nf); break;
   }
 }
 
 template <bool DEBUG, bool COUNT, bool TWO>
 __global__ __launch_bounds__(kBlock) void k_tail(SceneDev S, PathsDev P, int cur, int b_first, int max_depth,
-                                                 uint32_t sample, uint32_t k0, uint32_t k1, uint32_t img_w,
+                                                 uint32_t sample, uint32_t k0, uint32_t k1,
                                                  int nrc_bounce) {
   __shared__ unsigned long long s_stack[kLdsStack * kBlock];
   const uint32_t count = P.counts[cur];
@@ -1152,7 +1181,7 @@ __global__ __launch_bounds__(kBlock) void k_tail(SceneDev S, PathsDev P, int cur
     const uint32_t n_walk = (uint32_t)__popcll((unsigned long long)__ballot(phase == 1 || phase == 2));
     if (n_ready && kTailShadeWait * n_ready >= n_walk && phase == 3) {
       ShadeOut o;
-      shade_any<DEBUG, TWO>(cls, S, P, slot, b, max_depth, sample, k0, k1, img_w, nrc_bounce, o, nonfinite);
+      shade_any<DEBUG, TWO>(cls, S, P, slot, b, max_depth, sample, k0, k1, nrc_bounce, o, nonfinite);
       // paths that ended in the radiance cache join its query queue (one atomic per wave)
       const uint64_t m_q = __ballot(o.query);
       if (m_q) {
@@ -1201,24 +1230,38 @@ __global__ __launch_bounds__(kBlock) void k_tail(SceneDev S, PathsDev P, int cur
 }
 
 // -------------------------------------------------------------- accumulate
-// FP64 per-pixel running sums: one writer per pixel per pass, no atomics.
+// FP64 per-pixel running sums: one writer per pixel per pass, no atomics; the
+// pass's samples are added one by one in sample order, so the sums do not
+// depend on how many samples a pass takes.
 __global__ __launch_bounds__(kBlock) void k_accumulate(PathsDev P, double* sum, int W, float* per_sample,
-                                                       uint64_t* sig_out, int spp_total, int sample_index) {
-  for (int slot = blockIdx.x * kBlock + threadIdx.x; slot < P.n_render; slot += gridDim.x * kBlock) {
-    float4 L = P.L[slot];
+                                                       uint64_t* sig_out, int spp_total, int first_index) {
+  const uint32_t places = (uint32_t)P.w * (uint32_t)P.h;
+  for (uint32_t p = blockIdx.x * kBlock + threadIdx.x; p < places; p += gridDim.x * kBlock) {
+    uint32_t x, y;
+    place_pixel(p, (uint32_t)P.w, (uint32_t)P.h, x, y);
+    const float4* L = P.L + (size_t)p * P.spp;
     if (sum) {
-      int px = P.x0 + slot % P.w, py = P.y0 + slot / P.w;
-      double* s = sum + 3 * ((size_t)py * W + px);
-      s[0] += (double)L.x;
-      s[1] += (double)L.y;
-      s[2] += (double)L.z;
+      double* s = sum + 3 * ((size_t)(P.y0 + y) * W + (P.x0 + x));
+      double sx = s[0], sy = s[1], sz = s[2];
+      for (uint32_t k = 0; k < P.spp; ++k) {
+        const float4 v = L[k];
+        sx += (double)v.x;
+        sy += (double)v.y;
+        sz += (double)v.z;
+      }
+      s[0] = sx;
+      s[1] = sy;
+      s[2] = sz;
     }
     if (per_sample) {
-      size_t o = (size_t)slot * spp_total + sample_index;
-      per_sample[3 * o] = L.x;
-      per_sample[3 * o + 1] = L.y;
-      per_sample[3 * o + 2] = L.z;
-      sig_out[o] = P.sig[slot];
+      for (uint32_t k = 0; k < P.spp; ++k) {
+        const float4 v = L[k];
+        const size_t o = ((size_t)y * P.w + x) * spp_total + first_index + k;
+        per_sample[3 * o] = v.x;
+        per_sample[3 * o + 1] = v.y;
+        per_sample[3 * o + 2] = v.z;
+        sig_out[o] = P.sig[(size_t)p * P.spp + k];
+      }
     }
   }
 }
@@ -1332,7 +1375,7 @@ int traversal_grid(int64_t rays) {
 }
 
 template <bool DEBUG, bool TWO>
-static hipError_t shade_all(const SceneDev& S, const PathsDev& P, const PassArgs& A, int b, int next, uint32_t W,
+static hipError_t shade_all(const SceneDev& S, const PathsDev& P, const PassArgs& A, int b, int next,
                             hipStream_t st) {
   // The class kernels touch disjoint path slots and append through atomics,
   // so with side streams they run concurrently (each is bound by the
@@ -1357,7 +1400,7 @@ static hipError_t shade_all(const SceneDev& S, const PathsDev& P, const PassArgs
 #define PT_SHADE(C)                                                                                      \
   case C:                                                                                                \
     hipLaunchKernelGGL((k_shade<C, DEBUG, TWO>), g, blk, 0, q, S, P, b, A.max_depth, next, A.sample, A.k0, \
-                       A.k1, W, A.nrc_bounce);                                                           \
+                       A.k1, A.nrc_bounce);                                                           \
     break;
       PT_SHADE(kClsMiss)
       PT_SHADE(kClsAbsorb)
@@ -1378,6 +1421,14 @@ static hipError_t shade_all(const SceneDev& S, const PathsDev& P, const PassArgs
   }
   return hipGetLastError();
 }
+
+// The hand-off fraction counts from at most this many slots, so the tail
+// kernel never takes more than max_fraction of them however large the pass:
+// its lanes are 18 % active, the wavefront kernels fill the chip with a few
+// hundred thousand paths.  Icosphere field 1080p 64 spp in passes of 2^25
+// slots: 0.7M 103.8 ms, 1.4M 103.5, 2M 102.9, 3M 106.5, no bound (2^24
+// slots) 121.9; instanced scene 32 spp: 151.7 / 153.7 / 150.8 / 153.7 ms.
+static constexpr int32_t kTailPassSlots = 1 << 21;
 
 template <bool DEBUG, bool COUNT, bool TWO>
 static hipError_t bounce_loop(const SceneDev& S, const PathsDev& P, const CamDev& C, const PassArgs& A,
@@ -1404,19 +1455,20 @@ static hipError_t bounce_loop(const SceneDev& S, const PathsDev& P, const CamDev
     if (A.nrc_events) hipEventRecord(A.nrc_events[1], q);
     return e2;
   };
+  const double tail_limit = A.tail_fraction * (double)std::min(P.n, kTailPassSlots);
   for (int b = 0; b <= A.max_depth; ++b) {
     int cur = b & 1, next = cur ^ 1;
     if (A.tail_host_count && b >= A.tail_min_bounce) {
       // hand the remaining vertices to one persistent kernel once few paths are left
       if (A.tail_bound && A.nrc_bounce >= 0 && b > A.nrc_bounce &&
-          (double)A.tail_bound <= A.tail_fraction * (double)P.n) {
+          (double)A.tail_bound <= tail_limit) {
         *A.tail_host_count = A.tail_bound;  // a bound known on the host: no need to read the count
       } else {
         hipError_t e0 = hipMemcpyAsync(A.tail_host_count, &P.counts[cur], sizeof(uint32_t), hipMemcpyDeviceToHost, st);
         if (e0 == hipSuccess) e0 = hipStreamSynchronize(st);
         if (e0 != hipSuccess) return e0;
       }
-      if ((double)*A.tail_host_count <= A.tail_fraction * (double)P.n) {
+      if ((double)*A.tail_host_count <= tail_limit) {
         if (A.wavefront_bounces) *A.wavefront_bounces = b;
         hipStream_t ts = st;
         if (A.tail_stream) {  // continue on the second stream; the caller's stream is free for the next pass
@@ -1439,7 +1491,7 @@ static hipError_t bounce_loop(const SceneDev& S, const PathsDev& P, const CamDev
         if (A.tail_events) hipEventRecord(A.tail_events[0], ts);
         hipLaunchKernelGGL((k_tail<DEBUG, COUNT, TWO>),
                            dim3(tail_grid(A.grid_trace, *A.tail_host_count, A.tail_stream != nullptr)), blk, 0, ts,
-                           S, P, cur, b, A.max_depth, A.sample, A.k0, A.k1, (uint32_t)C.W, A.nrc_bounce);
+                           S, P, cur, b, A.max_depth, A.sample, A.k0, A.k1, A.nrc_bounce);
         if (A.tail_events) hipEventRecord(A.tail_events[1], ts);
         if (A.nrc_bounce >= 0 && b <= A.nrc_bounce) {
           // the tail kernel took over at or before the query vertex: the paths it ends in the
@@ -1454,7 +1506,7 @@ static hipError_t bounce_loop(const SceneDev& S, const PathsDev& P, const CamDev
     traverse(cur, st);  // this bounce's closest hits and the previous bounce's shadow rays
     shadow_pending = false;
     hipLaunchKernelGGL(k_bin, dim3(A.grid_bin), blk, 0, st, P, cur);  // also empties the shadow queue
-    hipError_t e = shade_all<DEBUG, TWO>(S, P, A, b, next, (uint32_t)C.W, st);
+    hipError_t e = shade_all<DEBUG, TWO>(S, P, A, b, next, st);
     if (e != hipSuccess) return e;
     shadow_pending = b < A.max_depth;
     if (b == A.nrc_bounce) {  // every path still alive ended in the cache at this vertex
@@ -1504,9 +1556,9 @@ static int blocks_for(int64_t n) {
 }
 
 hipError_t launch_accumulate(const PathsDev& P, double* sum, int W, float* per_sample, uint64_t* sig_out,
-                             int spp_total, int sample_index, hipStream_t st) {
-  hipLaunchKernelGGL(k_accumulate, dim3(blocks_for(P.n_render)), dim3(kBlock), 0, st, P, sum, W, per_sample, sig_out,
-                     spp_total, sample_index);
+                             int spp_total, int first_index, hipStream_t st) {
+  hipLaunchKernelGGL(k_accumulate, dim3(blocks_for((int64_t)P.w * P.h)), dim3(kBlock), 0, st, P, sum, W, per_sample,
+                     sig_out, spp_total, first_index);
   return hipGetLastError();
 }
 

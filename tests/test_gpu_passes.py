@@ -1,0 +1,62 @@
+"""Several samples per pixel in one sampling pass (GPU).
+
+A call of n samples runs them in as few passes as fit, its pixels in blocks
+of 8x8 and a pixel's samples in neighbouring slots.  The FP64 sums must not
+depend on that grouping (each path's radiance is the same floats, added in
+sample order), so every comparison here is bit for bit.
+"""
+import os
+import sys
+
+import numpy as np
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+sys.path.insert(0, ROOT)
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+
+# block edges and remainders in each direction, one pixel, one row, one column
+SIZES = [(1, 1), (7, 3), (8, 8), (9, 17), (65, 1), (1, 23), (40, 31)]
+
+
+@pytest.fixture(scope="module")
+def scene():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2407_19977_amd import pt, scenes
+    sc = scenes.cornell()
+    s = pt.scene_from(sc, device=0)
+    yield sc, s
+    s.close()
+
+
+@pytest.mark.parametrize("w,h", SIZES)
+@pytest.mark.parametrize("spp", [2, 5])
+def test_sums_do_not_depend_on_the_grouping(scene, w, h, spp):
+    print(f"[passes] {w}x{h}, {spp} spp", flush=True)
+    sc, s = scene
+    cam = sc.with_camera(width=w, height=h).camera
+    mean = torch.empty((h, w, 3), dtype=torch.float32, device="cuda:0")
+    sums = [torch.empty((h, w, 3), dtype=torch.float64, device="cuda:0") for _ in range(2)]
+    s.reset_accumulation()
+    for k in range(spp):
+        s.accumulate(cam, 3 + k, 1, 4, 11)
+    s.resolve(mean, sums[0])
+    s.reset_accumulation()
+    s.accumulate(cam, 3, spp, 4, 11)
+    s.resolve(mean, sums[1])
+    assert torch.equal(sums[0], sums[1])
+    # per sample: the rows, columns and sample indices of the debug output are the image's
+    per = torch.empty((h, w, spp, 3), dtype=torch.float32, device="cuda:0")
+    sig = torch.empty((h, w, spp), dtype=torch.int64, device="cuda:0")
+    s.render_debug(cam, 0, 0, w, h, 3, spp, 4, 11, per, sig)
+    acc = np.zeros((h, w, 3))
+    for k in range(spp):
+        acc += per[:, :, k].cpu().numpy().astype(np.float64)
+    assert np.array_equal(acc, sums[1].cpu().numpy())
+    if w > 2 and h > 2:  # a crop gives the same paths
+        pc = torch.empty((h - 2, w - 2, spp, 3), dtype=torch.float32, device="cuda:0")
+        sg = torch.empty((h - 2, w - 2, spp), dtype=torch.int64, device="cuda:0")
+        s.render_debug(cam, 1, 2, w - 2, h - 2, 3, spp, 4, 11, pc, sg)
+        assert torch.equal(pc, per[2:, 1:w - 1]) and torch.equal(sg, sig[2:, 1:w - 1])
