@@ -439,8 +439,8 @@ pt_status pt_bvh_host_build_instanced(const pt_mesh* meshes, int32_t n_meshes, c
 pt_status pt_bvh_host_info(const pt_bvh_host* bvh, pt_bvh_info* info);
 /* Copy nodes (n_nodes * 128 bytes) and triangles (n_tris * 48 bytes) to host memory. */
 pt_status pt_bvh_host_copy(const pt_bvh_host* bvh, void* nodes, void* tris);
-/* Closest hit on the host through the BVH4 (same traversal code as the GPU,
- * compiled for the CPU).  rays/hits as for pt_trace_closest, host memory. */
+/* Closest hit on the host through the BVH4 (the GPU's triangle test and walk
+ * order; its box test in plain form).  rays/hits as for pt_trace_closest, host memory. */
 pt_status pt_bvh_host_trace(const pt_bvh_host* bvh, const float* rays, int64_t n, uint32_t* hits);
 /* The same walk with a stack of `stack_capacity` entries per ray (<= 0: the
  * capacity pt_bvh_info reports; at most 512), for checking the stack bound

@@ -95,10 +95,11 @@ struct pt_scene {
   hipStream_t stream = nullptr;
   // geometry
   bool has_bvh = false;
-  DevBuf nodes, tris;
+  DevBuf nodes, tris, top;
   uint32_t n_tris = 0;
   int bvh_depth = 0;
-  int64_t n_nodes = 0;       // mesh-level BVH4 nodes in `nodes`
+  int64_t n_nodes = 0;       // mesh-level BVH4 nodes in `nodes` (two-level scenes: the top level's follow)
+  uint32_t bvh_root = 0;     // node a walk starts at
   int bvh_max_leaf = 0;
   double bvh_sah = 0.0;      // host builds only
   double bvh_build_ms = 0.0; // triangle soup in host memory -> BVH ready where the builder leaves it
@@ -109,7 +110,7 @@ struct pt_scene {
   std::vector<int32_t> host_tri_mat;  // [n], prim order (single level)
   // two-level hierarchy
   bool two_level = false;
-  DevBuf insts, tlas, tlas_items, light_map, mesh_tri_first, mesh_tri_count;
+  DevBuf insts, tlas_items, light_map, mesh_tri_first, mesh_tri_count;
   std::vector<InstRec> host_insts;
   std::vector<std::vector<float>> host_mesh_verts;   // per mesh [n][9], object space, prim order
   std::vector<std::vector<int32_t>> host_mesh_mat;   // per mesh [n]
@@ -402,7 +403,9 @@ SceneDev scene_dev(pt_scene* s, int grid_trace, int set = 0) {
   S.nodes = s->nodes.as<BVHNode>();
   S.tris = s->tris.as<TriRec>();
   S.n_tris = s->n_tris;
-  S.root = 0;
+  S.root = s->bvh_root;
+  S.small_nodes = s->nodes.bytes <= ((size_t)1 << 32) ? 1 : 0;
+  S.top = s->top.as<BVHNode>();
   S.mats = s->mats.as<MatRec>();
   S.tri_light = s->tri_light.as<int32_t>();
   S.lights = s->lights.as<LightTri>();
@@ -427,7 +430,6 @@ SceneDev scene_dev(pt_scene* s, int grid_trace, int set = 0) {
   S.spill_stride = (uint32_t)grid_trace * kBlock;
   S.insts = s->insts.as<InstRec>();
   S.n_insts = (uint32_t)s->host_insts.size();
-  S.tlas = s->tlas.as<BVHNode>();
   S.tlas_items = s->tlas_items.as<uint32_t>();
   S.light_map = s->light_map.as<int32_t>();
   S.mesh_tri_first = s->mesh_tri_first.as<uint32_t>();
@@ -676,7 +678,7 @@ pt_status run_passes(pt_scene* s, const CamDev& C, int x0, int y0, int w, int h,
     hipError_t e = hipSuccess;
     for (int set = 0; set < nsets && e == hipSuccess; ++set) {
       e = alloc_paths(s, slots, set, per_sample != nullptr);
-      if (e == hipSuccess) e = alloc_spill(s, traversal_grid(slots), set);
+      if (e == hipSuccess) e = alloc_spill(s, traversal_grid(slots, s->two_level), set);
       if (e == hipSuccess && use_cache) e = alloc_queries(s, N * spp_max, set);
     }
     if (e == hipSuccess) break;
@@ -686,7 +688,7 @@ pt_status run_passes(pt_scene* s, const CamDev& C, int x0, int y0, int w, int h,
     for (PathBufs& B : s->pb) release_paths(B);
     spp_max = pass_samples(N, n, N * ((spp_max + 1) / 2));
   }
-  int grid = grid_for(slots), grid_trace = traversal_grid(slots);
+  int grid = grid_for(slots), grid_trace = traversal_grid(slots, s->two_level);
   pt_status r = PT_OK;
   for (int set = 0; set < nsets; ++set)
     if ((r = ensure_counters(s, set))) return r;
@@ -814,7 +816,7 @@ pt_status run_passes(pt_scene* s, const CamDev& C, int x0, int y0, int w, int h,
 pt_status run_cache_frames(pt_scene* s, const CamDev& C, int first, int n, int max_depth, uint64_t seed) {
   const int64_t N = (int64_t)C.W * C.H;
   const int64_t slots = N + s->nrc_cfg.train_paths;
-  int grid = grid_for(slots), grid_trace = traversal_grid(slots);
+  int grid = grid_for(slots), grid_trace = traversal_grid(slots, s->two_level);
   pt_status r = PT_OK;
   PathsDev Ps[2];
   for (int set = 0; set < 2; ++set) {  // every allocation before the first launch
@@ -1023,7 +1025,7 @@ pt_status nrc_trace_training(pt_scene* s, const CamDev& C, uint32_t frame, int m
   pt_status r = ensure_paths(s, n);
   if (r) return r;
   if ((r = ensure_counters(s))) return r;
-  int grid = grid_for(n), grid_trace = traversal_grid(n);
+  int grid = grid_for(n), grid_trace = traversal_grid(n, s->two_level);
   if ((r = ensure_spill(s, grid_trace))) return r;
   SceneDev S = scene_dev(s, grid_trace);
   PathsDev P = paths_dev(s, 0, 0, 1, 0, 1);
@@ -1441,9 +1443,15 @@ pt_status build_two_level(pt_scene* s, const pt_mesh* meshes, int32_t n_meshes, 
                         std::string& err) { return gpu_mesh_bvh(s, v, prim, mat, n, b, err); };
   r = build_two_level_host(meshes, n_meshes, instances, n_instances, T, on_device ? &gpu : nullptr);
   if (r) return r;
+  // the top level's nodes follow the meshes', so that a walk reads one array
+  const uint32_t root = (uint32_t)T.nodes.size();
+  for (BVHNode n : T.top.nodes) {
+    for (uint32_t& c : n.child)
+      if (!ref_is_leaf(c)) c += root;
+    T.nodes.push_back(n);
+  }
   PT_HIP(upload(s->nodes, T.nodes.data(), T.nodes.size() * sizeof(BVHNode), s->stream));
   PT_HIP(upload(s->tris, T.tris.data(), T.tris.size() * sizeof(TriRec), s->stream));
-  PT_HIP(upload(s->tlas, T.top.nodes.data(), T.top.nodes.size() * sizeof(BVHNode), s->stream));
   PT_HIP(upload(s->tlas_items, T.items.data(), T.items.size() * sizeof(uint32_t), s->stream));
   PT_HIP(upload(s->insts, T.insts.data(), T.insts.size() * sizeof(InstRec), s->stream));
   PT_HIP(upload(s->mesh_tri_first, T.tfirst.data(), T.tfirst.size() * sizeof(uint32_t), s->stream));
@@ -1453,7 +1461,10 @@ pt_status build_two_level(pt_scene* s, const pt_mesh* meshes, int32_t n_meshes, 
   set_box(s, T.box_lo, T.box_hi);
   s->n_tris = (uint32_t)T.tris.size();
   s->bvh_depth = T.depth;
+  PT_HIP(s->top.alloc(kTopNodes * sizeof(BVHNode)));
+  PT_HIP(launch_top_nodes(s->nodes.as<BVHNode>(), root, s->top.as<BVHNode>(), s->stream));
   s->n_nodes = T.mesh_nodes;
+  s->bvh_root = root;
   s->bvh_max_leaf = T.max_leaf;
   s->bvh_sah = T.sah;
   s->bvh_build_ms = T.build_ms;
@@ -1579,9 +1590,12 @@ pt_status build_bvh_any(pt_scene* s, const pt_mesh* meshes, int32_t n_meshes, co
          dz = (double)(float)hi[2] - (float)lo[2];
   s->tmin = (float)(1e-5 * std::sqrt(dx * dx + dy * dy + dz * dz));
   set_box(s, lo, hi);
+  PT_HIP(s->top.alloc(kTopNodes * sizeof(BVHNode)));
+  PT_HIP(launch_top_nodes(s->nodes.as<BVHNode>(), 0u, s->top.as<BVHNode>(), s->stream));
   s->n_tris = (uint32_t)total;
   s->bvh_depth = depth;
   s->n_nodes = n_nodes;
+  s->bvh_root = 0;
   s->bvh_max_leaf = max_leaf;
   s->bvh_sah = sah;
   s->bvh_build_ms = build_ms;
@@ -2147,7 +2161,7 @@ pt_status pt_trace_closest(pt_scene* s, const float* rays, int64_t n, uint32_t* 
   if (!s->has_bvh) return fail(PT_ERR_STATE, "pt_build_bvh has not been called");
   if (n == 0) return PT_OK;
   if ((r = set_device(s))) return r;
-  int grid = brute ? trace_grid_blocks() : traversal_grid(n);
+  int grid = brute ? trace_grid_blocks() : traversal_grid(n, s->two_level);
   if ((r = ensure_spill(s, grid))) return r;
   if ((r = ensure_counters(s))) return r;
   SceneDev S = scene_dev(s, grid);
@@ -2174,7 +2188,7 @@ pt_status pt_trace_closest_noalloc(pt_scene* s, const float* rays, int64_t n, ui
     return fail(PT_ERR_UNSUPPORTED, "BVH depth %d needs %zu bytes of stack spill per workgroup, more than the %zu-byte "
                 "scratch of the allocation-free call", s->bvh_depth, lane_bytes * kBlock,
                 kNoAllocScratchBytes - kNoAllocStatsBytes);
-  const int grid = brute ? trace_grid_blocks() : (int)std::min<int64_t>(traversal_grid(n), fit);
+  const int grid = brute ? trace_grid_blocks() : (int)std::min<int64_t>(traversal_grid(n, s->two_level), fit);
   SceneDev S = scene_dev(s, grid);
   S.spill = reinterpret_cast<uint2*>(base + kNoAllocStatsBytes);
   S.spill_stride = (uint32_t)grid * kBlock;

@@ -19,15 +19,22 @@ constexpr int kBlock = 256;     // threads per workgroup (4 waves of 64)
 #define PT_LDS_STACK 10
 #endif
 constexpr int kLdsStack = PT_LDS_STACK;  // traversal stack entries per lane kept in LDS
+#ifndef PT_TOP_NODES
+#define PT_TOP_NODES 40
+#endif
+constexpr uint32_t kTopNodes = PT_TOP_NODES;   // nodes from the top of the tree that the traversal kernels keep in LDS
+constexpr uint32_t kTopBit = 0x40000000u;      // reference to one of them (inner nodes have indexes below 2^27)
 constexpr int kEnvRowGuide = 1024;      // guide-table sizes of the environment CDFs (powers of two)
 constexpr int kEnvColGuide = 256;
 
 // Scene data the kernels read (all device pointers).
 struct SceneDev {
-  const BVHNode* nodes;
+  const BVHNode* nodes;  // mesh nodes, then (two-level scenes) the top level's
   const TriRec* tris;
   uint32_t n_tris;
-  uint32_t root;
+  uint32_t root;         // where a walk starts
+  int32_t small_nodes;   // 1: the nodes take less than 2^32 bytes
+  const BVHNode* top;    // [kTopNodes] the tree's first nodes (launch_top_nodes); place 0 is the root
   const MatRec* mats;
   const int32_t* tri_light;  // light index by primitive id, -1 if not emissive
   const LightTri* lights;
@@ -47,7 +54,6 @@ struct SceneDev {
   // two-level hierarchy (instances); unused for a single world-space mesh
   const InstRec* insts;
   uint32_t n_insts;
-  const BVHNode* tlas;
   const uint32_t* tlas_items;     // instance ids in top-level leaf order
   const int32_t* light_map;       // per instance with emitters: primitive -> light index
   const uint32_t* mesh_tri_first; // first triangle record of each mesh (brute force)
@@ -184,6 +190,8 @@ hipError_t launch_zero_f64(double* p, int64_t n, hipStream_t st);
 // display image of the running mean (pt_display.hip): rgba8 and encoded are nullable
 hipError_t launch_display(const double* sum, int64_t n_pixels, double inv_samples, double exposure, uint32_t* rgba8,
                           float* encoded, hipStream_t st);
+// top [kTopNodes] (device): the first nodes from `root`, breadth first; entries beyond the tree stay as they are
+hipError_t launch_top_nodes(const BVHNode* nodes, uint32_t root, BVHNode* top, hipStream_t st);
 hipError_t launch_zero_u64(unsigned long long* p, int64_t n, hipStream_t st);
 hipError_t launch_trace_rays(const SceneDev& S, const float* rays, int64_t n, uint32_t* hits, bool brute,
                              bool two_level, int grid, unsigned long long* stats, hipStream_t st);
@@ -197,7 +205,7 @@ static_assert(kNumStats * sizeof(unsigned long long) <= kNoAllocStatsBytes, "cou
 // Device address of `dev`'s scratch; call with `dev` current.  The symbol is
 // looked up once per device and the address kept.
 hipError_t noalloc_scratch(int dev, unsigned char** out);
-int traversal_grid(int64_t rays);  // workgroups of the traversal kernel for a pass of `rays` paths
+int traversal_grid(int64_t rays, bool two_level);  // workgroups of the traversal kernel for a pass of `rays` paths
 int tail_grid(int grid_trace, uint32_t paths, bool beside);  // workgroups of the tail kernel
 
 // ---- GPU BVH construction (pt_bvh_gpu.hip) ----

@@ -94,8 +94,9 @@ __device__ inline uint64_t sig_tail(uint64_t h, uint32_t tail) {
 // ----------------------------------------------------------------- stacks
 // Traversal stack: the first kLdsStack entries of each lane in LDS as
 // (ref, key) pairs, entry e of lane l at [e][l] (one 8-byte access per push
-// or pop, conflict-free), deeper entries in a global spill area.  The LDS
-// pointer keeps its address space so pops are LDS reads, not flat loads.
+// or pop, conflict-free), deeper entries in a global spill area.  `top` is the
+// place of the next entry as if all of them were in LDS; the pointer keeps its
+// address space so pushes and pops are LDS accesses, not flat ones.
 // The capacity (3 x BVH depth + 4) bounds a depth-first walk that pushes at
 // most three siblings per level.
 typedef __attribute__((address_space(3))) unsigned long long lds_u64;
@@ -103,37 +104,50 @@ __device__ inline unsigned long long stack_entry(uint32_t r, float k) {
   return (unsigned long long)r | ((unsigned long long)f2u(k) << 32);
 }
 struct DevStack {
-  lds_u64* lds;
-  uint2* spill;
-  uint32_t sstride;
-  int sp, cap;
+  lds_u64 *base, *top;
   bool overflow;
-  __device__ inline void push(uint32_t r, float k) {
-    if (sp < kLdsStack) {
-      lds[sp * kBlock] = stack_entry(r, k);
-    } else if (sp < cap) {
-      spill[(size_t)(sp - kLdsStack) * sstride] = make_uint2(r, f2u(k));
-    } else {
+  __device__ inline lds_u64* lds_end() const { return base + kLdsStack * kBlock; }
+  __device__ inline bool room(int n) const { return top <= lds_end() - n * kBlock; }  // n more entries fit in LDS
+  __device__ inline void push_lds(unsigned long long e) {
+    *top = e;
+    top += kBlock;
+  }
+  __device__ inline unsigned long long* spill_entry(const SceneDev& S, uint32_t i) const {
+    return reinterpret_cast<unsigned long long*>(S.spill) + (size_t)i * S.spill_stride +
+           (blockIdx.x * kBlock + threadIdx.x);
+  }
+  __device__ inline void push(const SceneDev& S, unsigned long long e) {
+    if (room(1)) {
+      push_lds(e);
+      return;
+    }
+    const uint32_t i = (uint32_t)(top - lds_end()) / kBlock;  // entries in the spill area
+    if (i >= (uint32_t)(S.stack_cap - kLdsStack)) {
       overflow = true;
       return;
     }
-    sp++;
+    *spill_entry(S, i) = e;
+    top += kBlock;
   }
-  __device__ inline uint32_t pop(float& k) {
-    --sp;
-    // the LDS read is unconditional (clamped index) so it stays an LDS access;
+  __device__ inline unsigned long long pop(const SceneDev& S) {
+    top -= kBlock;
+    // the LDS read is unconditional (clamped place) so it stays an LDS access;
     // the rare spill read replaces it
-    unsigned long long w = lds[(sp < kLdsStack ? sp : kLdsStack - 1) * kBlock];
-    if (sp >= kLdsStack)  // a relaxed atomic load is never merged with the LDS read into a flat load
-      w = __hip_atomic_load(reinterpret_cast<unsigned long long*>(spill + (size_t)(sp - kLdsStack) * sstride),
-                            __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
-    k = u2f((uint32_t)(w >> 32));
-    return (uint32_t)w;
+    lds_u64* last = lds_end() - kBlock;
+    unsigned long long w = *(top < last ? top : last);
+    if (top > last)  // a relaxed atomic load is never merged with the LDS read into a flat load
+      w = __hip_atomic_load(spill_entry(S, (uint32_t)(top - lds_end()) / kBlock), __ATOMIC_RELAXED,
+                            __HIP_MEMORY_SCOPE_WAVEFRONT);
+    return w;
   }
-  __device__ inline int size() const { return sp; }
+  __device__ inline void clear() { top = base; }
+  __device__ inline bool empty() const { return top == base; }
 };
-__device__ inline lds_u64* lds_stack_base(unsigned long long* shared_stack) {
-  return (lds_u64*)(shared_stack + threadIdx.x);
+__device__ inline DevStack make_stack(unsigned long long* shared_stack) {
+  DevStack st;
+  st.base = st.top = (lds_u64*)(shared_stack + threadIdx.x);
+  st.overflow = false;
+  return st;
 }
 
 // ------------------------------------------------------------------ lights
@@ -391,108 +405,307 @@ constexpr uint32_t kTailShadeWait = PT_TAIL_SHADE_WAIT;
 // tail kernel beside the next pass: paths per workgroup (two per lane)
 constexpr uint64_t kTailPathsPerGroup = PT_TAIL_PATHS_PER_GROUP;
 #ifndef PT_TRACE_WAVES
-#define PT_TRACE_WAVES 7
+#define PT_TRACE_WAVES 6
 #endif
-// minimum waves per SIMD the traversal kernel is compiled for
+// minimum waves per SIMD the traversal kernel is compiled for: 6 is the most that
+// needs no scratch (field render at 4 / 5 / 6 / 7: 107.5 / 101.4 / 97.5 / 98.2 ms)
 constexpr int kTraceWaves = PT_TRACE_WAVES;
+#ifndef PT_TRACE_WAVES_2
+#define PT_TRACE_WAVES_2 5
+#endif
+constexpr int kTraceWaves2 = PT_TRACE_WAVES_2;  // two-level scenes: the world-space ray takes registers too (6: 124.6 ms, 5: 119.4)
 
+// Ray of a lane's walk in the space of the current level: what the triangle
+// test reads (the same values as ray_prepare's, bit for bit) and the box test's
+// constants.
 struct LaneRay {
-  RayPre r;   // ray in the space of the current level
-  RayPre rw;  // world-space ray (two-level scenes)
-  float tmin, tmax;
+  float ox, oy, oz;
+  float Sx, Sy, Sz;
+  uint32_t k;  // kx, ky, kz, two bits each
+  // Box test of a plane p of axis a: t = fma(p, i_a, c) with c = -(o_a i_a) moved
+  // by slack to the safe side, n_a for the plane the ray meets first and f_a for
+  // the other.
+  float ix, iy, iz, nx, ny, nz, fx, fy, fz;
+  float wox, woy, woz, wdx, wdy, wdz;  // world-space ray (two-level scenes)
   uint32_t skip_inst, skip_prim;
-  uint32_t cur;    // next reference to process, kEmpty: pop
-  float cur_key;   // its entry distance
-  uint32_t inst;   // instance of the current mesh walk, kNoInst at the top level
-  int base;        // stack size when that mesh walk started
-  bool any;        // shadow ray: stop at the first accepted triangle (kWalkPerLane walks)
-  Hit best;
+  uint32_t cur;      // next reference to process, kEmpty: pop
+  float cur_key;     // its entry distance (two-level scenes)
+  uint32_t inst;     // instance of the current mesh walk, kNoInst at the top level
+  lds_u64* base;     // stack top when that mesh walk started
+  bool any;          // shadow ray: stop at the first accepted triangle (kWalkPerLane walks)
+  // best hit so far (tri kEmpty: none, t is the ray's tmax)
+  float t, b1, b2;
+  uint32_t tri, best_inst;
+  __device__ inline bool found() const { return tri != kEmpty; }
 };
 
+// ---- top of the tree in LDS
+// A third of all node visits go to the first kTopNodes nodes in breadth-first
+// order.  The traversal kernels keep copies of them in LDS (one per workgroup),
+// where a read does not go through the CU's load path (2^20 incoherent rays 330
+// -> 318 us); their references to each other carry kTopBit and the place in the
+// table, others are as in the tree.  40 nodes fit six workgroups a CU (64 with
+// five: the icosphere field renders in 101.4 ms against 97.5).
+typedef __attribute__((address_space(3))) unsigned char lds_byte;
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(3))) f32x4 lds_f32x4;
+typedef __attribute__((address_space(3))) u32x4 lds_u32x4;
+constexpr uint32_t kTopStride = 144;  // bytes per node in LDS: 16 more than the node, to spread the banks
+constexpr uint32_t kTopLds = kTopNodes * kTopStride;
+__device__ inline lds_byte* top_load(const SceneDev& S, unsigned char* shared) {
+  for (uint32_t i = threadIdx.x; i < kTopNodes * 8u; i += kBlock)
+    *(lds_u32x4*)((lds_byte*)shared + (i >> 3) * kTopStride + (i & 7u) * 16u) =
+        reinterpret_cast<const u32x4*>(S.top)[i];
+  return (lds_byte*)shared;
+}
+
+__device__ inline float widen_limit(float t) { return fmaf(fabsf(t), 1.9073486328125e-06f, t); }  // t + 2^-19 |t|
+
+// Box-test constants of one axis.  The box only prunes, so it needs safe, not
+// exact, distances: with inv within 1 ulp of 1/d, fma(p, inv, -(o inv)) is off by
+// at most 4 u |t| + u |o inv| (u = 2^-24); the constants move by 4 u |o inv| to
+// the safe side, the far distance and the pruning limit widen by 64 u and 32 u
+// relative, so every box is at least as wide as one widened by 16 u computed from
+// (p - o) / d.  A component below 2^-100 counts as 2^-100 with a slack of 2^40,
+// 2^-60 in space: finite products instead of 0 x inf, and the axis still prunes.
+__device__ inline void box_axis(float o, float d, float& inv, float& n, float& f) {
+  const float tiny = 7.888609052210118e-31f;  // 2^-100
+  const bool small = fabsf(d) < tiny;
+  inv = __builtin_amdgcn_rcpf(small ? copysignf(tiny, d) : d);
+  const float c = o * inv, e = fmaf(fabsf(c), 2.384185791015625e-07f, small ? 1099511627776.0f : 0.0f);
+  n = -c - e;
+  f = -c + e;
+}
+// Byte offset in a node of the planes that a ray with inverse direction inv meets first on axis a (the others' is this ^ 16).
+__device__ inline uint32_t near_offset(uint32_t a, float inv) { return (32u * a) | ((f2u(inv) >> 27) & 16u); }
+
+__device__ inline void lane_box(LaneRay& L, float ox, float oy, float oz, float dx, float dy, float dz) {
+#pragma clang fp contract(off)
+  box_axis(ox, dx, L.ix, L.nx, L.fx);
+  box_axis(oy, dy, L.iy, L.ny, L.fy);
+  box_axis(oz, dz, L.iz, L.nz, L.fz);
+}
+
+// The ray (o, d) of the level whose triangles are tested next.
+__device__ inline void lane_ray(LaneRay& L, float ox, float oy, float oz, float dx, float dy, float dz) {
+  const RayPre r = ray_prepare(ox, oy, oz, dx, dy, dz);
+  L.ox = ox;
+  L.oy = oy;
+  L.oz = oz;
+  L.Sx = r.Sx;
+  L.Sy = r.Sy;
+  L.Sz = r.Sz;
+  L.k = (uint32_t)(r.kx | (r.ky << 2) | (r.kz << 4));
+  lane_box(L, ox, oy, oz, dx, dy, dz);
+}
+
 template <bool TWO>
-__device__ inline void lane_start(LaneRay& L, float ox, float oy, float oz, float dx, float dy, float dz, float tmin,
+__device__ inline void lane_start(LaneRay& L, float ox, float oy, float oz, float dx, float dy, float dz,
                                   float tmax, uint32_t skip_inst, uint32_t skip_prim, uint32_t root) {
-  L.r = ray_prepare(ox, oy, oz, dx, dy, dz);
-  if (TWO) L.rw = L.r;
-  L.tmin = tmin;
-  L.tmax = tmax;
+  if (TWO) {  // the top level tests no triangles
+    L.wox = ox;
+    L.woy = oy;
+    L.woz = oz;
+    L.wdx = dx;
+    L.wdy = dy;
+    L.wdz = dz;
+    lane_box(L, ox, oy, oz, dx, dy, dz);
+  } else {
+    lane_ray(L, ox, oy, oz, dx, dy, dz);
+  }
   L.skip_inst = skip_inst;
   L.skip_prim = skip_prim;
   L.cur = root;
   L.cur_key = -INFINITY;
   L.inst = kNoInst;
-  L.base = 0;
-  hit_clear(L.best);
+  L.t = tmax;
+  L.b1 = L.b2 = 0.0f;
+  L.tri = L.best_inst = kEmpty;
 }
 
 // Walk kinds of lane_step: closest hit, any hit (shadow rays), or the kind
 // the lane's own `any` flag names.
 enum { kWalkClosest = 0, kWalkAny = 1, kWalkPerLane = 2 };
 
+// Order two stack entries by key, then ref: as doubles, (key, ref) pairs with
+// the key in the high word order as the keys do (keys are not NaN and at most
+// +inf, whose pattern is a finite double's), and one 64-bit minimum and maximum
+// take the place of a compare and four selects.  (asm: the builtins would first
+// quieten every operand.)
+__device__ inline void entry_sort(double& a, double& b) {
+  double lo, hi;
+  asm("v_min_f64 %0, %1, %2" : "=v"(lo) : "v"(a), "v"(b));
+  asm("v_max_f64 %0, %1, %2" : "=v"(hi) : "v"(a), "v"(b));
+  a = lo;
+  b = hi;
+}
+__device__ inline float entry_key(double e) { return u2f((uint32_t)(__double_as_longlong(e) >> 32)); }
+__device__ inline uint32_t entry_ref(double e) { return (uint32_t)__double_as_longlong(e); }
+__device__ inline double entry_make(uint32_t ref, float key) {
+  return __longlong_as_double((long long)stack_entry(ref, key));
+}
+
+struct TriRay {
+  float ox, oy, oz, Sx, Sy, Sz;
+  int kx, ky, kz;
+};
+
+// Test the triangles of a leaf (any: stop at the first accepted one); true if one was accepted.
+template <bool COUNT, bool TWO>
+__device__ inline bool lane_leaf(const SceneDev& S, LaneRay& L, float tmin, bool any, uint32_t& ntri) {
+  const uint32_t first = leaf_first(L.cur), cnt = leaf_count(L.cur);
+  const TriRay r{L.ox, L.oy, L.oz, L.Sx, L.Sy, L.Sz, (int)(L.k & 3u), (int)((L.k >> 2) & 3u), (int)(L.k >> 4)};
+  bool found = false;
+  for (uint32_t j = 0; j < cnt; ++j) {
+    const TriRec tr = S.tris[first + j];
+    if (COUNT) ntri++;
+    const uint32_t prim = f2u(tr.a.w);
+    // intersect before the origin-triangle check so the record's three loads
+    // issue together instead of waiting on the primitive id first
+    float t, b1, b2;
+    if (!tri_intersect(r, tr.a, tr.b, tr.c, t, b1, b2)) continue;
+    if (prim == L.skip_prim && (!TWO || L.inst == L.skip_inst)) continue;
+    if (!(t > tmin && t <= L.t)) continue;
+    if (t == L.t) {  // ties: the smallest (instance, primitive)
+      if (!L.found()) continue;  // t is tmax
+      if (TWO && L.inst != L.best_inst) {
+        if (L.inst > L.best_inst) continue;
+      } else if (prim >= f2u(S.tris[L.tri].a.w)) {
+        continue;
+      }
+    }
+    L.t = t;
+    L.b1 = b1;
+    L.b2 = b2;
+    L.tri = first + j;
+    if (TWO) L.best_inst = L.inst;
+    found = true;
+    if (any) return true;
+  }
+  return found;
+}
+
+// What bounds the walk (icosphere field, 33M paths a pass): a divergent 16-byte
+// load costs the CU's load path one cycle per lane, so a node's seven parts cost
+// seven cycles per lane, beside the node step's VALU work.  Sub and multiply per
+// plane, minima for the near plane and compare-select sorting (0.92 / 0.81 VALU
+// issue at bounces 0 / 1) became one fma per plane with the plane chosen by
+// address and a 64-bit minimum sort: 3.85 -> 3.48 and 8.4 -> 7.6 ms at 0.67 / 0.61
+// issue, 33 % fewer VALU instructions.  What is left is the latency of the ~14 of
+// a wave's ~30 nodes that miss the L1.
+// Slower: quads or the whole wave fetching nodes cooperatively into LDS (field
+// render 121-130 ms against 99), rays sorted by direction (traversal +20 %).
+//
 // One step of a lane's walk: visit one node, or test one leaf, then pop the
 // next entry that can still hold a closer hit.  In two-level scenes a
 // top-level leaf pushes its instances as entries (leaf bit, count 0,
 // instance id) that start a mesh walk on top of the stack.  Returns true when
 // the walk is over (any-hit walks: also at the first accepted triangle).
-template <int KIND, bool COUNT, bool TWO>
-__device__ inline bool lane_step(const SceneDev& S, LaneRay& L, DevStack& st, uint32_t& nvis, uint32_t& ntri,
-                                 uint32_t& ninst) {
+// TOP: the walk started at the table's root (`top`: its copy in LDS).
+template <int KIND, bool COUNT, bool TWO, bool TOP>
+__device__ inline bool lane_step(const SceneDev& S, LaneRay& L, float tmin, DevStack& st, lds_byte* top,
+                                 uint32_t& nvis, uint32_t& ntri, uint32_t& ninst) {
   const bool any = KIND == kWalkAny || (KIND == kWalkPerLane && L.any);
   const uint32_t cur = L.cur;
   if (cur != kEmpty) {
     if (!ref_is_leaf(cur)) {
-      const BVHNode* nodes = (TWO && L.inst == kNoInst) ? S.tlas : S.nodes;
-      const BVHNode n = nodes[cur];
       if (COUNT) nvis++;
-      float tn[4];
-      float tcur = fminf(L.best.t, L.tmax);
-      uint32_t m = node_slabs(n, L.r, L.tmin, tcur, tn);
-      float k0 = (m & 1u) ? tn[0] : INFINITY, k1 = (m & 2u) ? tn[1] : INFINITY;
-      float k2 = (m & 4u) ? tn[2] : INFINITY, k3 = (m & 8u) ? tn[3] : INFINITY;
-      uint32_t r0 = (m & 1u) ? n.child[0] : kEmpty, r1 = (m & 2u) ? n.child[1] : kEmpty;
-      uint32_t r2 = (m & 4u) ? n.child[2] : kEmpty, r3 = (m & 8u) ? n.child[3] : kEmpty;
-      cswap(k0, r0, k1, r1);
-      cswap(k2, r2, k3, r3);
-      cswap(k0, r0, k2, r2);
-      cswap(k1, r1, k3, r3);
-      cswap(k1, r1, k2, r2);
-      if (r3 != kEmpty) st.push(r3, k3);
-      if (r2 != kEmpty) st.push(r2, k2);
-      if (r1 != kEmpty) st.push(r1, k1);
-      L.cur = r0;
-      L.cur_key = k0;
-      if (r0 != kEmpty) return false;
+      const float tlim = widen_limit(L.t);
+      const uint32_t sx = near_offset(0, L.ix), sy = near_offset(1, L.iy), sz = near_offset(2, L.iz);
+      const char* nodes = reinterpret_cast<const char*>(S.nodes);
+      f32x4 an, af, bn, bf, cn, cf;
+      u32x4 ch;
+      if (TOP && (cur & kTopBit)) {
+        lds_byte* q = top + (cur & ~kTopBit) * kTopStride;
+        an = *(lds_f32x4*)(q + sx);
+        af = *(lds_f32x4*)(q + (sx ^ 16u));
+        bn = *(lds_f32x4*)(q + sy);
+        bf = *(lds_f32x4*)(q + (sy ^ 16u));
+        cn = *(lds_f32x4*)(q + sz);
+        cf = *(lds_f32x4*)(q + (sz ^ 16u));
+        ch = *(lds_u32x4*)(q + 96);
+      } else if (S.small_nodes) {  // node bytes below 2^32: 32-bit offsets from the base
+        const uint32_t o = cur << 7, x = o + sx, y = o + sy, z = o + sz;
+        an = *reinterpret_cast<const f32x4*>(nodes + x);
+        af = *reinterpret_cast<const f32x4*>(nodes + (x ^ 16u));
+        bn = *reinterpret_cast<const f32x4*>(nodes + y);
+        bf = *reinterpret_cast<const f32x4*>(nodes + (y ^ 16u));
+        cn = *reinterpret_cast<const f32x4*>(nodes + z);
+        cf = *reinterpret_cast<const f32x4*>(nodes + (z ^ 16u));
+        ch = *reinterpret_cast<const u32x4*>(nodes + (o + 96u));
+        asm volatile("; 32-bit node offsets" ::: "memory");  // keeps the two forms apart
+      } else {
+        const char* q = nodes + ((uint64_t)cur << 7);
+        an = *reinterpret_cast<const f32x4*>(q + sx);
+        af = *reinterpret_cast<const f32x4*>(q + (sx ^ 16u));
+        bn = *reinterpret_cast<const f32x4*>(q + sy);
+        bf = *reinterpret_cast<const f32x4*>(q + (sy ^ 16u));
+        cn = *reinterpret_cast<const f32x4*>(q + sz);
+        cf = *reinterpret_cast<const f32x4*>(q + (sz ^ 16u));
+        ch = *reinterpret_cast<const u32x4*>(q + 96);
+        asm volatile("; 64-bit node addresses" ::: "memory");
+      }
+      // entry of child c: its box's entry distance, +inf for a missed box
+      auto child = [&](float ax, float ay, float az, float bx, float by, float bz, uint32_t ref) -> double {
+        const float tn = fmaxf(fmaxf(fmaxf(fmaf(ax, L.ix, L.nx), fmaf(ay, L.iy, L.ny)), fmaf(az, L.iz, L.nz)), tmin);
+        const float tf = fminf(fminf(fmaf(bx, L.ix, L.fx), fmaf(by, L.iy, L.fy)), fmaf(bz, L.iz, L.fz));
+        const float te = fminf(fmaf(fabsf(tf), 3.814697265625e-06f, tf), tlim);  // tf + 2^-18 |tf|
+        return entry_make(ref, tn <= te ? tn : INFINITY);
+      };
+      double e0 = child(an.x, bn.x, cn.x, af.x, bf.x, cf.x, ch.x), e1 = child(an.y, bn.y, cn.y, af.y, bf.y, cf.y, ch.y);
+      double e2 = child(an.z, bn.z, cn.z, af.z, bf.z, cf.z, ch.z), e3 = child(an.w, bn.w, cn.w, af.w, bf.w, cf.w, ch.w);
+      entry_sort(e0, e1);
+      entry_sort(e2, e3);
+      entry_sort(e0, e2);
+      entry_sort(e1, e3);
+      entry_sort(e1, e2);
+      const bool h1 = entry_key(e1) < INFINITY, h2 = entry_key(e2) < INFINITY, h3 = entry_key(e3) < INFINITY;
+      const auto bits = [](double e) { return (unsigned long long)__double_as_longlong(e); };
+      if (st.room(3)) {
+        if (h3) st.push_lds(bits(e3));
+        if (h2) st.push_lds(bits(e2));
+        if (h1) st.push_lds(bits(e1));
+      } else {
+        if (h3) st.push(S, bits(e3));
+        if (h2) st.push(S, bits(e2));
+        if (h1) st.push(S, bits(e1));
+      }
+      if (entry_key(e0) < INFINITY) {
+        L.cur = entry_ref(e0);
+        if (TWO) L.cur_key = entry_key(e0);
+        return false;
+      }
     } else if (TWO && L.inst == kNoInst) {
       const uint32_t first = leaf_first(cur), cnt = leaf_count(cur);
       if (cnt == 0) {  // an instance entry: walk its mesh in object space
         const InstRec& I = S.insts[first];
         if (COUNT) ninst++;
-        L.r = ray_to_object(I.w2o, L.rw.ox, L.rw.oy, L.rw.oz, L.rw.dx, L.rw.dy, L.rw.dz);
+        float o[3], d[3];
+        ray_to_object(I.w2o, L.wox, L.woy, L.woz, L.wdx, L.wdy, L.wdz, o, d);
+        lane_ray(L, o[0], o[1], o[2], d[0], d[1], d[2]);
         L.inst = first;
-        L.base = st.size();
+        L.base = st.top;
         L.cur = I.blas_root;
         return false;
       }
-      for (int j = (int)cnt - 1; j >= 0; --j) st.push(kLeafBit | S.tlas_items[first + j], L.cur_key);
+      for (int j = (int)cnt - 1; j >= 0; --j) st.push(S, stack_entry(kLeafBit | S.tlas_items[first + j], L.cur_key));
     } else {
-      if (leaf_test<KIND == kWalkAny, COUNT>(S.tris, cur, L.r, L.tmin, L.tmax, TWO ? L.inst : 0u, L.skip_inst,
-                                             L.skip_prim, L.best, ntri, any) &&
-          any)
-        return true;
+      if (lane_leaf<COUNT, TWO>(S, L, tmin, any, ntri) && any) return true;
     }
     L.cur = kEmpty;
   }
   while (true) {
-    if (TWO && L.inst != kNoInst && st.size() == L.base) {  // mesh walk over: back to the top level
+    if (TWO && L.inst != kNoInst && st.top == L.base) {  // mesh walk over: back to the top level
       L.inst = kNoInst;
-      L.r = L.rw;
+      lane_box(L, L.wox, L.woy, L.woz, L.wdx, L.wdy, L.wdz);
     }
-    if (st.size() == 0) return true;
-    float k;
-    uint32_t q = st.pop(k);
-    if (k <= fminf(L.best.t, L.tmax)) {
-      L.cur = q;
-      L.cur_key = k;
+    if (st.empty()) return true;
+    const unsigned long long e = st.pop(S);
+    const float k = u2f((uint32_t)(e >> 32));
+    if (k <= widen_limit(L.t)) {
+      L.cur = (uint32_t)e;
+      if (TWO) L.cur_key = k;
       return false;
     }
   }
@@ -502,13 +715,12 @@ __device__ inline bool lane_step(const SceneDev& S, LaneRay& L, DevStack& st, ui
 // start(i, L) (load item i into the lane) and finish(i, L, found).
 template <int KIND, bool COUNT, bool TWO, class Src>
 __device__ inline void persistent_trace(const SceneDev& S, Src& src, uint32_t count, unsigned long long* s_stack,
-                                        uint32_t* s_next, uint32_t& nvis, uint32_t& ntri, bool& overflow) {
+                                        lds_byte* top, uint32_t* s_next, uint32_t& nvis, uint32_t& ntri, bool& overflow) {
   const uint32_t per = (count + gridDim.x - 1) / gridDim.x;
   const uint32_t b0 = min(count, blockIdx.x * per), b1 = min(count, b0 + per);
   if (threadIdx.x == 0) *s_next = b0;
   __syncthreads();
-  const uint32_t gtid = blockIdx.x * kBlock + threadIdx.x;
-  DevStack st{lds_stack_base(s_stack), S.spill + gtid, S.spill_stride, 0, S.stack_cap, false};
+  DevStack st = make_stack(s_stack);
   LaneRay L;
   bool busy = false, drained = false;
   uint32_t item = 0;
@@ -523,7 +735,7 @@ __device__ inline void persistent_trace(const SceneDev& S, Src& src, uint32_t co
       const uint32_t i = base + lane_prefix(idle);
       if (!busy && i < b1) {
         item = i;
-        st.sp = 0;
+        st.clear();
         src.start(i, L);
         busy = true;
       }
@@ -540,8 +752,8 @@ __device__ inline void persistent_trace(const SceneDev& S, Src& src, uint32_t co
       go = busy && (!at_leaf || kLeafWait * n_leaf >= kLeafWaitDen * n_node);
     }
     uint32_t ninst = 0;
-    if (go && lane_step<KIND, COUNT, TWO>(S, L, st, nvis, ntri, ninst)) {
-      src.finish(item, L, L.best.tri != 0xFFFFFFFFu);
+    if (go && lane_step<KIND, COUNT, TWO, true>(S, L, src.tmin, st, top, nvis, ntri, ninst)) {
+      src.finish(item, L, L.found());
       busy = false;
     }
   }
@@ -556,17 +768,17 @@ struct ExtendSrc {
   __device__ inline void start(uint32_t i, LaneRay& L) {
     uint32_t slot = P.q_ray[cur][i];
     float4 o = P.ray_o[slot], d = P.ray_d[slot];
-    lane_start<TWO>(L, o.x, o.y, o.z, d.x, d.y, d.z, S.tmin, INFINITY, f2u(d.w), f2u(o.w), TWO ? 0u : S.root);
+    lane_start<TWO>(L, o.x, o.y, o.z, d.x, d.y, d.z, INFINITY, f2u(d.w), f2u(o.w), kTopBit);
   }
   __device__ inline void finish(uint32_t i, const LaneRay& L, bool found) {
     uint32_t slot = P.q_ray[cur][i];
     int cls = kClsMiss;
     if (found) {
-      P.hit[slot] = make_float4(L.best.t, L.best.b1, L.best.b2, u2f(L.best.tri));
-      uint32_t mid = L.best.mat;
+      P.hit[slot] = make_float4(L.t, L.b1, L.b2, u2f(L.tri));
+      uint32_t mid = f2u(S.tris[L.tri].b.w);
       if (TWO) {
-        P.hit_inst[slot] = L.best.inst;
-        int32_t ov = S.insts[L.best.inst].mat_override;
+        P.hit_inst[slot] = L.best_inst;
+        int32_t ov = S.insts[L.best_inst].mat_override;
         if (ov >= 0) mid = (uint32_t)ov;
       }
       cls = S.mats[mid].cls;
@@ -908,8 +1120,8 @@ struct ConnectSrc {
   __device__ inline void start(uint32_t i, LaneRay& L) {
     float4 o = P.sh_o[i], d = P.sh_d[i];
     uint32_t skip_prim = f2u(P.sh_c[i].w);
-    if (TWO) lane_start<true>(L, o.x, o.y, o.z, d.x, d.y, d.z, S.tmin, o.w, P.sh_inst[i], skip_prim, 0u);
-    else lane_start<false>(L, o.x, o.y, o.z, d.x, d.y, d.z, S.tmin, o.w, 0u, skip_prim, S.root);
+    if (TWO) lane_start<true>(L, o.x, o.y, o.z, d.x, d.y, d.z, o.w, P.sh_inst[i], skip_prim, kTopBit);
+    else lane_start<false>(L, o.x, o.y, o.z, d.x, d.y, d.z, o.w, 0u, skip_prim, kTopBit);
   }
   __device__ inline void finish(uint32_t i, const LaneRay& L, bool occ) {
     uint32_t slot = f2u(P.sh_d[i].w);
@@ -943,9 +1155,11 @@ struct ConnectSrc {
 // first; its shadow rays fill the lanes that the last closest-hit walks leave
 // idle, instead of every workgroup of the GPU draining at a kernel boundary.
 template <bool DEBUG, bool COUNT, bool TWO>
-__global__ __launch_bounds__(kBlock, kTraceWaves) void k_traverse(SceneDev S, PathsDev P, int cur) {
+__global__ __launch_bounds__(kBlock, TWO ? kTraceWaves2 : kTraceWaves) void k_traverse(SceneDev S, PathsDev P, int cur) {
   __shared__ unsigned long long s_stack[kLdsStack * kBlock];
+  __shared__ __align__(16) unsigned char s_top[kTopLds];
   __shared__ uint32_t s_next;
+  lds_byte* top = top_load(S, s_top);
   const uint32_t ne = cur >= 0 ? P.counts[cur] : 0u, ns = P.counts[kCountShadow];
   if (blockIdx.x == 0 && threadIdx.x == 0) {
     if (ne) atomicAdd(&P.stats[kStatExt], (unsigned long long)ne);
@@ -955,8 +1169,7 @@ __global__ __launch_bounds__(kBlock, kTraceWaves) void k_traverse(SceneDev S, Pa
   const uint32_t n_e = share_size(ne, wg, G), n_all = n_e + share_size(ns, wg, G);
   if (threadIdx.x == 0) s_next = 0u;
   __syncthreads();
-  const uint32_t gtid = blockIdx.x * kBlock + threadIdx.x;
-  DevStack st{lds_stack_base(s_stack), S.spill + gtid, S.spill_stride, 0, S.stack_cap, false};
+  DevStack st = make_stack(s_stack);
   unsigned long long nonfinite = 0;
   ExtendSrc<TWO> es{S, P, cur < 0 ? 0 : cur};
   ConnectSrc<DEBUG, TWO> cs{S, P, nonfinite};
@@ -978,7 +1191,7 @@ __global__ __launch_bounds__(kBlock, kTraceWaves) void k_traverse(SceneDev S, Pa
       if (!busy && v < n_all) {
         shadow = v >= n_e;
         item = shadow ? share_item(v - n_e, ns, wg, G) : share_item(v, ne, wg, G);
-        st.sp = 0;
+        st.clear();
         if (shadow) cs.start(item, L);
         else es.start(item, L);
         L.any = shadow;
@@ -997,8 +1210,8 @@ __global__ __launch_bounds__(kBlock, kTraceWaves) void k_traverse(SceneDev S, Pa
       const uint32_t n_node = (uint32_t)__popcll((unsigned long long)__ballot(busy && !at_leaf));
       go = busy && (!at_leaf || kLeafWait * n_leaf >= kLeafWaitDen * n_node);
     }
-    if (go && lane_step<kWalkPerLane, COUNT, TWO>(S, L, st, rv, rt, ri)) {
-      const bool found = L.best.tri != 0xFFFFFFFFu;
+    if (go && lane_step<kWalkPerLane, COUNT, TWO, true>(S, L, S.tmin, st, top, rv, rt, ri)) {
+      const bool found = L.found();
       if (shadow) cs.finish(item, L, found);
       else es.finish(item, L, found);
       if (COUNT) {
@@ -1066,8 +1279,7 @@ __global__ __launch_bounds__(kBlock) void k_tail(SceneDev S, PathsDev P, int cur
   __syncthreads();
   uint32_t* next_path = &s_next;
 #endif
-  const uint32_t gtid = blockIdx.x * kBlock + threadIdx.x;
-  DevStack st{lds_stack_base(s_stack), S.spill + gtid, S.spill_stride, 0, S.stack_cap, false};
+  DevStack st = make_stack(s_stack);
   LaneRay L;
   // 0 idle, 1 closest-hit walk, 2 shadow-ray walk, 3 hit found and waiting to be shaded
   int phase = 0;
@@ -1082,8 +1294,8 @@ __global__ __launch_bounds__(kBlock) void k_tail(SceneDev S, PathsDev P, int cur
   uint32_t ninst = 0;
   auto start_closest = [&](void) {
     float4 o = P.ray_o[slot], d = P.ray_d[slot];
-    st.sp = 0;
-    lane_start<TWO>(L, o.x, o.y, o.z, d.x, d.y, d.z, S.tmin, INFINITY, f2u(d.w), f2u(o.w), TWO ? 0u : S.root);
+    st.clear();
+    lane_start<TWO>(L, o.x, o.y, o.z, d.x, d.y, d.z, INFINITY, f2u(d.w), f2u(o.w), S.root);
     L.any = false;
     rv = rt = ri = 0;
     phase = 1;
@@ -1115,7 +1327,7 @@ __global__ __launch_bounds__(kBlock) void k_tail(SceneDev S, PathsDev P, int cur
       const uint32_t n_node = (uint32_t)__popcll((unsigned long long)__ballot(walking && !at_leaf));
       go = walking && (!at_leaf || kLeafWait * n_leaf >= kLeafWaitDen * n_node);
     }
-    const bool done = go && lane_step<kWalkPerLane, COUNT, TWO>(S, L, st, rv, rt, ri);
+    const bool done = go && lane_step<kWalkPerLane, COUNT, TWO, false>(S, L, S.tmin, st, nullptr, rv, rt, ri);
     if (done && COUNT) {
       ninst += ri;
       if (phase == 1) {
@@ -1130,12 +1342,12 @@ __global__ __launch_bounds__(kBlock) void k_tail(SceneDev S, PathsDev P, int cur
       if (done) {
         overflow |= st.overflow;
         cls = kClsMiss;
-        if (L.best.tri != 0xFFFFFFFFu) {
-          P.hit[slot] = make_float4(L.best.t, L.best.b1, L.best.b2, u2f(L.best.tri));
-          uint32_t mid = L.best.mat;
+        if (L.found()) {
+          P.hit[slot] = make_float4(L.t, L.b1, L.b2, u2f(L.tri));
+          uint32_t mid = f2u(S.tris[L.tri].b.w);
           if (TWO) {
-            P.hit_inst[slot] = L.best.inst;
-            int32_t ov = S.insts[L.best.inst].mat_override;
+            P.hit_inst[slot] = L.best_inst;
+            int32_t ov = S.insts[L.best_inst].mat_override;
             if (ov >= 0) mid = (uint32_t)ov;
           }
           cls = S.mats[mid].cls;
@@ -1147,7 +1359,7 @@ __global__ __launch_bounds__(kBlock) void k_tail(SceneDev S, PathsDev P, int cur
     } else if (phase == 2) {
       if (done) {
         overflow |= st.overflow;
-        const bool occ = L.best.tri != 0xFFFFFFFFu;
+        const bool occ = L.found();
         if (!occ) {
           V3 cc = v3(sh_c.x, sh_c.y, sh_c.z);
           if (finite3(cc)) {
@@ -1192,9 +1404,9 @@ __global__ __launch_bounds__(kBlock) void k_tail(SceneDev S, PathsDev P, int cur
         if (o.query) P.q_nrc[qbase + lane_prefix(m_q)] = slot;
       }
       if (o.shadow) {
-        st.sp = 0;
-        lane_start<TWO>(L, o.sh_o.x, o.sh_o.y, o.sh_o.z, o.sh_d.x, o.sh_d.y, o.sh_d.z, S.tmin, o.sh_o.w,
-                        TWO ? o.sh_inst : 0u, f2u(o.sh_c.w), TWO ? 0u : S.root);
+        st.clear();
+        lane_start<TWO>(L, o.sh_o.x, o.sh_o.y, o.sh_o.z, o.sh_d.x, o.sh_d.y, o.sh_d.z, o.sh_o.w,
+                        TWO ? o.sh_inst : 0u, f2u(o.sh_c.w), S.root);
         L.any = true;
         rv = rt = ri = 0;
         sh_c = o.sh_c;
@@ -1280,6 +1492,52 @@ __global__ __launch_bounds__(kBlock) void k_zero_u64(unsigned long long* p, int6
 }
 
 // ------------------------------------------------------- ray query kernels
+// The first kTopNodes nodes of the tree in breadth-first order from `root`, with
+// references to each other replaced by kTopBit | place.  One wave; lanes expand
+// the places found so far, kTopNodes at most, until no place is left to expand.
+__global__ __launch_bounds__(64) void k_top_nodes(const BVHNode* nodes, uint32_t root, BVHNode* top) {
+  __shared__ uint32_t s_node[kTopNodes];
+  const uint32_t lane = threadIdx.x;
+  if (lane == 0) s_node[0] = root;
+  __syncthreads();
+  uint32_t n = 1;
+  for (uint32_t done = 0; done < n;) {  // places [done, n) are expanded together, at most 64 of them
+    const uint32_t batch = min(64u, n - done);
+    BVHNode v;
+    uint32_t inner = 0;
+    if (lane < batch) {
+      v = nodes[s_node[done + lane]];
+      for (int c = 0; c < 4; ++c) inner += (int)v.child[c] >= 0 ? 1u : 0u;
+    }
+    uint32_t before = inner;  // inclusive prefix over the lanes
+    for (int d = 1; d < 64; d <<= 1) {
+      const uint32_t o = (uint32_t)__shfl_up((int)before, d);
+      if ((int)lane >= d) before += o;
+    }
+    const uint32_t total = (uint32_t)__shfl((int)before, 63);
+    uint32_t place = n + before - inner;
+    if (lane < batch) {
+      for (int c = 0; c < 4; ++c) {
+        if ((int)v.child[c] < 0) continue;  // a leaf or empty
+        if (place < kTopNodes) {
+          s_node[place] = v.child[c];
+          v.child[c] = kTopBit | place;
+        }
+        ++place;
+      }
+      top[done + lane] = v;
+    }
+    __syncthreads();
+    done += batch;
+    n = min(n + total, kTopNodes);
+  }
+}
+
+hipError_t launch_top_nodes(const BVHNode* nodes, uint32_t root, BVHNode* top, hipStream_t st) {
+  hipLaunchKernelGGL(k_top_nodes, dim3(1), dim3(64), 0, st, nodes, root, top);
+  return hipGetLastError();
+}
+
 // Closest hits of a ray array ([n][8]: o, tmin, d, tmax) -> [n][6] words.
 __device__ inline void write_hit(uint32_t* H, const Hit& h) {
   bool hit = h.tri != 0xFFFFFFFFu;
@@ -1296,22 +1554,37 @@ struct RaysSrc {
   const SceneDev& S;
   const float* rays;
   uint32_t* hits;
+  float tmin;  // of the lane's ray
   __device__ inline void start(uint32_t i, LaneRay& L) {
     const float* R = rays + 8 * (size_t)i;
-    lane_start<TWO>(L, R[0], R[1], R[2], R[4], R[5], R[6], R[3], R[7], 0xFFFFFFFFu, 0xFFFFFFFFu, TWO ? 0u : S.root);
+    tmin = R[3];
+    lane_start<TWO>(L, R[0], R[1], R[2], R[4], R[5], R[6], R[7], 0xFFFFFFFFu, 0xFFFFFFFFu, kTopBit);
   }
-  __device__ inline void finish(uint32_t i, const LaneRay& L, bool) { write_hit(hits + 6 * (size_t)i, L.best); }
+  __device__ inline void finish(uint32_t i, const LaneRay& L, bool found) {
+    Hit h;
+    hit_clear(h);
+    if (found) {
+      h.t = L.t;
+      h.b1 = L.b1;
+      h.b2 = L.b2;
+      h.inst = TWO ? L.best_inst : 0u;
+      h.tri = L.tri;
+      h.prim = f2u(S.tris[L.tri].a.w);
+    }
+    write_hit(hits + 6 * (size_t)i, h);
+  }
 };
 
 template <bool TWO>
 __global__ __launch_bounds__(kBlock) void k_trace_rays(SceneDev S, const float* rays, uint32_t n, uint32_t* hits,
                                                        unsigned long long* stats) {
   __shared__ unsigned long long s_stack[kLdsStack * kBlock];
+  __shared__ __align__(16) unsigned char s_top[kTopLds];
   __shared__ uint32_t s_next;
   uint32_t nvis = 0, ntri = 0;
   bool overflow = false;
-  RaysSrc<TWO> src{S, rays, hits};
-  persistent_trace<kWalkClosest, false, TWO>(S, src, n, s_stack, &s_next, nvis, ntri, overflow);
+  RaysSrc<TWO> src{S, rays, hits, 0.0f};
+  persistent_trace<kWalkClosest, false, TWO>(S, src, n, s_stack, top_load(S, s_top), &s_next, nvis, ntri, overflow);
   if (overflow) atomicAdd(&stats[kStatOverflow], 1ull);
 }
 
@@ -1358,20 +1631,21 @@ int tail_grid(int grid_trace, uint32_t paths, bool beside) {
 
 // The traversal kernels keep one resident set of workgroups (persistent
 // lanes); more would only queue behind them.
-int traversal_grid(int64_t rays) {
-  int64_t need = std::max<int64_t>(1, (rays + kBlock - 1) / kBlock);
-  static int resident = 0;
-  if (!resident) {
+int traversal_grid(int64_t rays, bool two_level) {
+  const int64_t need = std::max<int64_t>(1, (rays + kBlock - 1) / kBlock);
+  static int resident[2] = {0, 0};
+  if (!resident[two_level]) {
     int dev = 0, cus = 0, per = 0;
     if (hipGetDevice(&dev) != hipSuccess ||
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1)
       cus = 256;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, k_traverse<true, true, true>, kBlock, 0) != hipSuccess ||
-        per < 1)
-      per = 1;
-    resident = std::max(1, cus * per);
+    const hipError_t e = two_level
+                             ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, k_traverse<false, false, true>, kBlock, 0)
+                             : hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, k_traverse<false, false, false>, kBlock, 0);
+    if (e != hipSuccess || per < 1) per = 1;
+    resident[two_level] = std::max(1, cus * per);
   }
-  return (int)std::min<int64_t>(need, resident);
+  return (int)std::min<int64_t>(need, resident[two_level]);
 }
 
 template <bool DEBUG, bool TWO>

@@ -80,7 +80,8 @@ __host__ __device__ inline RayPre ray_prepare(float ox, float oy, float oz, floa
 
 // Watertight test; returns true with t = T/det (as T * (1/det)) and the
 // barycentric weights of v1 and v2.
-__host__ __device__ inline bool tri_intersect(const RayPre& r, const float4& A4, const float4& B4,
+template <class Ray>
+__host__ __device__ inline bool tri_intersect(const Ray& r, const float4& A4, const float4& B4,
                                               const float4& C4, float& t, float& b1, float& b2) {
 #pragma clang fp contract(off)
   float Ax0 = A4.x - r.ox, Ay0 = A4.y - r.oy, Az0 = A4.z - r.oz;
@@ -243,16 +244,21 @@ __host__ __device__ inline bool traverse_bvh(const BVHNode* __restrict__ nodes, 
 
 // World -> object transform of a ray, in the fixed FP32 order
 // o'_r = ((w_r0 ox + w_r1 oy) + w_r2 oz) + w_r3,  d'_r = (w_r0 dx + w_r1 dy) + w_r2 dz.
-__host__ __device__ inline RayPre ray_to_object(const float* w, float ox, float oy, float oz, float dx, float dy,
-                                                float dz) {
+__host__ __device__ inline void ray_to_object(const float* w, float ox, float oy, float oz, float dx, float dy,
+                                              float dz, float o[3], float d[3]) {
 #pragma clang fp contract(off)
-  float o[3], d[3];
 #pragma unroll
   for (int k = 0; k < 3; ++k) {
     const float* q = w + 4 * k;
     o[k] = ((q[0] * ox + q[1] * oy) + q[2] * oz) + q[3];
     d[k] = (q[0] * dx + q[1] * dy) + q[2] * dz;
   }
+}
+
+__host__ __device__ inline RayPre ray_to_object(const float* w, float ox, float oy, float oz, float dx, float dy,
+                                                float dz) {
+  float o[3], d[3];
+  ray_to_object(w, ox, oy, oz, dx, dy, dz, o, d);
   return ray_prepare(o[0], o[1], o[2], d[0], d[1], d[2]);
 }
 

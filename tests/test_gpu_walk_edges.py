@@ -1,0 +1,90 @@
+"""Closest-hit walk on rays at the edges of its box test (GPU).
+
+The walk prunes with distances fma(plane, 1/d, -o/d), moved to the safe side,
+and near and far planes chosen by the direction's signs.  Whatever the ray, the
+hits must be the ones of testing every triangle, bit for bit: directions with
+zero, negative-zero and tiny components, origins on box planes and far away,
+negative and large tmin, finite tmax.
+"""
+import os
+import sys
+
+import numpy as np
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+sys.path.insert(0, ROOT)
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+
+
+def _scene(which):
+    from paper_2407_19977_amd import scenes
+    if which == "box":
+        return scenes.cornell()
+    if which == "field":
+        return scenes.spheres(level=2, env_size=(64, 32))
+    sc = scenes.instanced(env_size=(64, 32))
+    sc.instances = sc.instances[:12] + sc.instances[-2:]
+    return sc
+
+
+def _rays(sc, n, kind, seed):
+    r = np.random.Generator(np.random.PCG64(seed))
+    if sc.instances:
+        verts = np.concatenate([i.object_to_world[:, :3] @ sc.meshes[i.mesh].vertices[::97].T
+                                + i.object_to_world[:, 3:] for i in sc.instances[:-2]], 1).T
+    else:
+        verts = sc.meshes[0].vertices
+    lo, hi = verts.min(0), verts.max(0)
+    rays = np.zeros((n, 8), np.float32)
+    target = verts[r.integers(0, len(verts), n)]
+    o = r.uniform(lo, hi, (n, 3)) + r.normal(size=(n, 3)) * 0.3
+    d = r.normal(size=(n, 3))
+    rays[:, 3], rays[:, 7] = 1e-4, np.inf
+    if kind == "axis":  # along one axis, through a vertex's coordinates: on the planes of the boxes around it
+        ax = r.integers(0, 3, n)
+        o = target.copy()
+        o[np.arange(n), ax] += r.choice([-5.0, 5.0], n)
+        d = np.where(r.uniform(size=(n, 3)) < 0.5, 0.0, -0.0)
+        d[np.arange(n), ax] = np.sign(target[np.arange(n), ax] - o[np.arange(n), ax])
+    elif kind == "plane":  # one zero component, aimed at a vertex
+        ax = r.integers(0, 3, n)
+        d = target - o
+        o[np.arange(n), ax] = target[np.arange(n), ax]
+        d[np.arange(n), ax] = r.choice([0.0, -0.0], n)
+    elif kind == "tiny":  # denormal and very small components
+        d = target - o
+        k = r.integers(0, 3, n)
+        d[np.arange(n), k] = r.choice([1e-45, -1e-40, 1e-38, -1e-31, 1e-30, 1e-20], n)
+    elif kind == "far":  # from far away
+        d = r.normal(size=(n, 3))
+        d /= np.linalg.norm(d, axis=1, keepdims=True)
+        o = target - d * r.choice([100.0, 1e4], (n, 1))
+    elif kind == "range":  # negative and large tmin, finite tmax
+        d = target - o
+        rays[:, 3] = r.choice([-2.0, -0.1, 0.0, 0.9], n)
+        rays[:, 7] = r.choice([0.5, 1.0, 1.5, np.inf], n)
+    rays[:, 0:3], rays[:, 4:7] = o, d
+    return rays
+
+
+@pytest.mark.parametrize("kind", ["axis", "plane", "tiny", "far", "range"])
+@pytest.mark.parametrize("which", ["box", "field", "instanced"])
+def test_hits_equal_brute_force(which, kind):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2407_19977_amd import pt
+    print(f"[walk] {which} {kind}", flush=True)
+    sc = _scene(which)
+    n = 3000 if which != "instanced" else 1200
+    rays = torch.from_numpy(_rays(sc, n, kind, 17)).to("cuda:0")
+    s = pt.scene_from(sc, device=0)
+    a = torch.empty((n, 6), dtype=torch.int32, device="cuda:0")
+    b = torch.empty_like(a)
+    s.trace_closest(rays, a)
+    s.trace_closest(rays, b, brute_force=True)
+    s.close()
+    assert int(b[:, 5].sum()) > n // 10, "too few rays hit to tell anything"
+    bad = torch.nonzero((a != b).any(1)).ravel()
+    assert len(bad) == 0, f"{len(bad)} of {n} rays differ, first {bad[:5].tolist()}: {rays[bad[:2]].tolist()}"
