@@ -136,7 +136,7 @@ struct pt_scene {
   hipStream_t shade_side[2] = {nullptr, nullptr};  // side streams of the shading kernels (default priority)
   hipEvent_t shade_fork = nullptr, shade_join[2] = {nullptr, nullptr};
   hipEvent_t ev_bulk[2] = {nullptr, nullptr}, ev_done[2] = {nullptr, nullptr};
-  uint32_t* tail_counts = nullptr;     // pinned host words, one per set
+  uint32_t* tail_counts = nullptr;     // pinned host copies of the queue counters, kShardWords per set
   // accumulation
   DevBuf sum;
   int acc_w = 0, acc_h = 0;
@@ -324,16 +324,19 @@ hipError_t alloc_paths(pt_scene* s, int64_t n, int set, bool debug) {
   PathBufs& B = s->pb[set];
   const size_t f4 = (size_t)n * sizeof(float4), u4 = (size_t)n * sizeof(uint32_t);
   hipError_t e = hipSuccess;
-  for (DevBuf* b : {&B.ray_o, &B.ray_d, &B.hit, &B.beta, &B.L, &B.sh_o, &B.sh_d, &B.sh_c})
+  const size_t qn = kShards * (size_t)queue_segment(n);  // a ray or shadow queue with all its segments
+  for (DevBuf* b : {&B.ray_o, &B.ray_d, &B.hit, &B.beta, &B.L})
     if (e == hipSuccess) e = b->alloc(f4);
-  for (DevBuf* b : {&B.flags, &B.q_ray[0], &B.q_ray[1]})
-    if (e == hipSuccess) e = b->alloc(u4);
+  for (DevBuf* b : {&B.sh_o, &B.sh_d, &B.sh_c})
+    if (e == hipSuccess) e = b->alloc(qn * sizeof(float4));
+  for (DevBuf* b : {&B.q_ray[0], &B.q_ray[1]})
+    if (e == hipSuccess) e = b->alloc(qn * sizeof(uint32_t));
+  if (e == hipSuccess) e = B.flags.alloc(u4);
   if (e == hipSuccess) e = B.cls.alloc((size_t)n);
   for (int i = 0; i < kNumClasses; ++i)
     if (e == hipSuccess && ((s->class_mask | (1u << kClsMiss)) & (1u << i))) e = B.q_cls[i].alloc(u4);
-  if (s->two_level)
-    for (DevBuf* b : {&B.hit_inst, &B.sh_inst})
-      if (e == hipSuccess) e = b->alloc(u4);
+  if (s->two_level && e == hipSuccess) e = B.hit_inst.alloc(u4);
+  if (s->two_level && e == hipSuccess) e = B.sh_inst.alloc(qn * sizeof(uint32_t));
   if (debug) {
     for (DevBuf* b : {&B.dbg_nee, &B.dbg_tail})
       if (e == hipSuccess) e = b->alloc(u4);
@@ -356,8 +359,8 @@ pt_status ensure_paths(pt_scene* s, int64_t n, int set = 0, bool debug = false) 
   return PT_OK;
 }
 
-int bin_grid(int64_t n) {  // 1024 rays per workgroup iteration
-  return (int)std::max<int64_t>(1, std::min<int64_t>((n + 1023) / 1024, 2048));
+int bin_grid(int64_t n) {  // 4096 rays per workgroup iteration; whole rounds over the queue segments
+  return (int)(std::max<int64_t>(1, std::min<int64_t>((n + 4095) / 4096 + kShards - 1, 2048) / kShards) * kShards);
 }
 
 int grid_for(int64_t n) {
@@ -692,7 +695,7 @@ pt_status run_passes(pt_scene* s, const CamDev& C, int x0, int y0, int w, int h,
   pt_status r = PT_OK;
   for (int set = 0; set < nsets; ++set)
     if ((r = ensure_counters(s, set))) return r;
-  if (!s->tail_counts) PT_HIP(hipHostMalloc((void**)&s->tail_counts, 2 * sizeof(uint32_t), hipHostMallocDefault));
+  if (!s->tail_counts) PT_HIP(hipHostMalloc((void**)&s->tail_counts, 2 * kShardWords * sizeof(uint32_t), hipHostMallocDefault));
   if (overlap) {
     if (!s->stream2) PT_HIP(hipStreamCreateWithFlags(&s->stream2, hipStreamNonBlocking));
     for (int k = 0; k < 2; ++k) {
@@ -736,7 +739,7 @@ pt_status run_passes(pt_scene* s, const CamDev& C, int x0, int y0, int w, int h,
       P.q_nrc = B.q_nrc.as<uint32_t>();
     }
     if (tail) {
-      A.tail_host_count = s->tail_counts + set;
+      A.tail_host_count = s->tail_counts + set * kShardWords;
       A.tail_min_bounce = s->tail_min_bounce;
       A.tail_fraction = s->tail_fraction;
     }
@@ -828,7 +831,7 @@ pt_status run_cache_frames(pt_scene* s, const CamDev& C, int first, int n, int m
     if ((r = setup_training(s, C, Ps[set], N, (uint32_t)first, max_depth, seed, set))) return r;
   }
   if ((r = nrc_ensure_ws(s, s->nrc_cfg.batch_size))) return r;
-  if (!s->tail_counts) PT_HIP(hipHostMalloc((void**)&s->tail_counts, 2 * sizeof(uint32_t), hipHostMallocDefault));
+  if (!s->tail_counts) PT_HIP(hipHostMalloc((void**)&s->tail_counts, 2 * kShardWords * sizeof(uint32_t), hipHostMallocDefault));
   if (!s->stream2) PT_HIP(hipStreamCreateWithFlags(&s->stream2, hipStreamNonBlocking));
   for (int k = 0; k < 2; ++k) {
     if (!s->ev_bulk[k]) PT_HIP(hipEventCreateWithFlags(&s->ev_bulk[k], hipEventDisableTiming));
@@ -877,7 +880,7 @@ pt_status run_cache_frames(pt_scene* s, const CamDev& C, int first, int n, int m
     A.query_wait = k > 0 ? s->ev_train : nullptr;  // the previous frame's Adam steps
     A.query_beside = true;
     if (tail) {
-      A.tail_host_count = s->tail_counts + set;
+      A.tail_host_count = s->tail_counts + set * kShardWords;
       A.tail_min_bounce = s->tail_min_bounce;
       A.tail_fraction = s->tail_fraction;
       A.tail_bound = (uint32_t)s->nrc_cfg.train_paths;

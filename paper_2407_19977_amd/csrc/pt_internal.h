@@ -82,13 +82,14 @@ struct PathsDev {
   float4* beta;        // throughput rgb, pdf of the last BSDF sample
   float4* L;           // radiance rgb, eta scale (product of eta^2 over refractions)
   uint32_t* flags;     // bit 0: last bounce was a delta lobe; bits 1..: pixel index (row-major)
-  uint32_t* q_ray[2];  // extension queues (double-buffered)
+  uint32_t* q_ray[2];  // extension queues (double-buffered): kShards segments of seg_cap slots
   uint32_t* q_cls[kNumClasses];
-  float4* sh_o;        // shadow ray o.xyz, tmax
+  float4* sh_o;        // shadow queue, in segments as the ray queues: o.xyz, tmax
   float4* sh_d;        // d.xyz, path slot (bits)
   float4* sh_c;        // contribution rgb, skip primitive (bits)
   uint32_t* sh_inst;   // skip instance
-  uint32_t* counts;    // [0..1] ray queues, [2..2+kNumClasses) classes, [2+kNumClasses] shadow
+  uint32_t* counts;    // queue lengths, see count_*
+  uint32_t seg_cap;    // items a queue segment has room for
   unsigned long long* stats;  // see kStat*
   uint64_t* sig;       // path signatures (debug)
   uint32_t* dbg_nee;   // pending next-event light id (debug)
@@ -137,10 +138,25 @@ enum {
   kStatTailInstances = 17,    // instances entered by the tail kernel's walks (two-level; counting on)
   kNumStats = 18
 };
-constexpr int kCountShadow = 2 + kNumClasses;
-constexpr int kCountQuery = kCountShadow + 1;
-constexpr int kCountTail = kCountQuery + 1;  // paths the tail kernel has taken so far
-constexpr int kNumCounts = 16;
+// Queue counters, each on a 128-byte line of its own (the counters of one
+// segment, which one workgroup adds to together, share a line).
+constexpr uint32_t kShards = 16;      // segments of the ray and shadow queues
+constexpr uint32_t kCountLine = 32;   // words
+constexpr int kQueueAll = 2;          // the ray queue that holds every slot, beside queues 0 and 1
+__host__ __device__ constexpr uint32_t count_ray(uint32_t seg, int queue) { return seg * kCountLine + (uint32_t)queue; }
+__host__ __device__ constexpr uint32_t count_shadow(uint32_t seg) { return seg * kCountLine + 2u; }
+__host__ __device__ constexpr uint32_t count_class(uint32_t cls) { return (kShards + cls) * kCountLine; }
+constexpr uint32_t kShardWords = kShards * kCountLine;
+constexpr uint32_t kCountQuery = count_class(kNumClasses);
+constexpr uint32_t kCountTail = kCountQuery + kCountLine;  // paths the tail kernel has taken so far
+constexpr uint32_t kNumCounts = kCountTail + kCountLine;
+#ifndef PT_SHADE_BLOCK
+#define PT_SHADE_BLOCK 256
+#endif
+constexpr int kShadeBlock = PT_SHADE_BLOCK;  // threads per workgroup of the shading kernels
+// Room of a segment for a pass of n paths: of a class's ceil(c / kShadeBlock) blocks a segment gets
+// at most 1 / kShards, rounded up, and every path of a block may append one item.
+constexpr int64_t queue_segment(int64_t n) { return n / kShards + (int64_t)kNumClasses * (kShadeBlock + kShadeBlock / kShards + 1) + 1; }
 
 // ---- kernel launchers (pt_kernels.hip) ----
 struct PassArgs {
@@ -160,7 +176,7 @@ struct PassArgs {
   hipEvent_t* nrc_events;  // 2 events around the cache-query kernel when timing, else nullptr
   // tail hand-off: from bounce tail_min_bounce on, when at most tail_fraction of the slots (of
   // the first 2^21 of a larger pass) are still alive, one persistent kernel finishes the paths (tail_host_count: pinned host word)
-  uint32_t* tail_host_count;
+  uint32_t* tail_host_count;  // kShardWords pinned words
   int tail_min_bounce;
   double tail_fraction;
   hipEvent_t* tail_events;  // 2 events around the tail kernel when timing, else nullptr

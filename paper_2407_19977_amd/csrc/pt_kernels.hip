@@ -305,6 +305,27 @@ __device__ inline uint32_t slot_sample(const PathsDev& P, uint32_t slot, uint32_
   return slot >= (uint32_t)P.n_render ? P.train_sample : sample + slot % P.spp;
 }
 
+// ------------------------------------------------------------------ queues
+// A ray or shadow queue is kShards segments, each with its own counter on a
+// 128-byte line of its own: atomics on one line take 11.4 ns each, one after
+// the other, so a single counter held the shading of 33M paths (one append per
+// 256 paths and queue) at 1.5 ms whatever else it did.  The shading kernels
+// append block k of a class to segment k mod kShards, which fills the segments
+// evenly, and workgroup g of a consumer takes from segment g mod kShards.
+// The ray queue of the first vertex is every slot in order, with no array.
+struct QueueShare {
+  uint32_t n;       // items of the segment (kQueueAll: of the pass)
+  uint32_t wg, G;   // this workgroup among those that share them
+  const uint32_t* q;
+  __device__ inline uint32_t slot(const PathsDev& P, uint32_t i) const { return q ? q[i] : i; }
+};
+__device__ inline QueueShare queue_share(const PathsDev& P, int cur) {
+  if (cur == kQueueAll) return QueueShare{(uint32_t)P.n, blockIdx.x, gridDim.x, nullptr};
+  const uint32_t seg = blockIdx.x % kShards;
+  return QueueShare{P.counts[count_ray(seg, cur)], blockIdx.x / kShards, gridDim.x / kShards,
+                    P.q_ray[cur] + (size_t)seg * P.seg_cap};
+}
+
 // ---------------------------------------------------------------- generate
 template <bool DEBUG>
 __global__ __launch_bounds__(kBlock) void k_generate(PathsDev P, CamDev C, uint32_t sample, uint32_t k0,
@@ -335,27 +356,25 @@ __global__ __launch_bounds__(kBlock) void k_generate(PathsDev P, CamDev C, uint3
     P.beta[slot] = make_float4(1.0f, 1.0f, 1.0f, 0.0f);
     P.L[slot] = make_float4(0.0f, 0.0f, 0.0f, 1.0f);
     P.flags[slot] = (pix << 1) | 1u;
-    P.q_ray[0][slot] = (uint32_t)slot;
     if (DEBUG) P.sig[slot] = kFnvOffset;
     if (P.rec && slot >= P.n_render)
       for (int r = 0; r < P.rec_depth; ++r)
         P.rec[((size_t)(slot - P.n_render) * P.rec_depth + r) * kNrcRecFloats + 18] = 0.0f;
   }
-  if (blockIdx.x == 0 && threadIdx.x == 0) {
-    P.counts[0] = (uint32_t)n;
-    P.counts[kCountShadow] = 0u;
-    P.counts[kCountQuery] = 0u;
+  if (blockIdx.x == 0) {
+    if (threadIdx.x < kShards) P.counts[count_shadow(threadIdx.x)] = 0u;
+    if (threadIdx.x == 0) P.counts[kCountQuery] = 0u;
   }
 }
 
-// Empty the next ray queue and the class queues (the shadow queue is still
-// being traced; k_bin empties it).
 __global__ void k_zero_u32(uint32_t* p) { *p = 0u; }
 
+// Empty the next ray queue and the class queues (the shadow queue is still
+// being traced; k_bin empties it).
 __global__ void k_reset_counts(uint32_t* counts, int next_queue) {
-  int i = threadIdx.x;
-  if (i >= 2 && i < kCountShadow) counts[i] = 0u;
-  if (i == next_queue) counts[i] = 0u;
+  const uint32_t i = threadIdx.x;
+  if (i < kShards) counts[count_ray(i, next_queue)] = 0u;
+  else if (i < kShards + kNumClasses) counts[count_class(i - kShards)] = 0u;
 }
 
 // ------------------------------------------------------------------ extend
@@ -385,15 +404,8 @@ constexpr uint32_t kLeafWait = PT_LEAF_WAIT, kLeafWaitDen = PT_LEAF_WAIT_DEN;
 #endif
 // with side streams each class kernel gets 1/PT_SHADE_GRID_DIV of the grid, so
 // that the concurrent class kernels can be resident together
-#ifndef PT_SHADE_BLOCK
-#define PT_SHADE_BLOCK 256
-#endif
-constexpr int kShadeBlock = PT_SHADE_BLOCK;  // threads per workgroup of the shading kernels
 #ifndef PT_TAIL_SHADE_WAIT
 #define PT_TAIL_SHADE_WAIT 1
-#endif
-#ifndef PT_TAIL_DYNAMIC
-#define PT_TAIL_DYNAMIC 1  // tail kernel: paths from a device-wide counter (0: a static share per workgroup)
 #endif
 // tail kernel: lanes waiting to shade go ahead once kTailShadeWait x their
 // number reaches the number of lanes still walking (a large value shades at
@@ -764,14 +776,11 @@ template <bool TWO>
 struct ExtendSrc {
   const SceneDev& S;
   const PathsDev& P;
-  int cur;
-  __device__ inline void start(uint32_t i, LaneRay& L) {
-    uint32_t slot = P.q_ray[cur][i];
+  __device__ inline void start(uint32_t slot, LaneRay& L) {
     float4 o = P.ray_o[slot], d = P.ray_d[slot];
     lane_start<TWO>(L, o.x, o.y, o.z, d.x, d.y, d.z, INFINITY, f2u(d.w), f2u(o.w), kTopBit);
   }
-  __device__ inline void finish(uint32_t i, const LaneRay& L, bool found) {
-    uint32_t slot = P.q_ray[cur][i];
+  __device__ inline void finish(uint32_t slot, const LaneRay& L, bool found) {
     int cls = kClsMiss;
     if (found) {
       P.hit[slot] = make_float4(L.t, L.b1, L.b2, u2f(L.tri));
@@ -790,35 +799,40 @@ struct ExtendSrc {
 };
 
 // Material binning of the rays just traced: a counting sort by class with
-// one atomic per class per workgroup (1024 rays).
+// one atomic per class per workgroup tile of kBinTile rays (atomics on one
+// counter take 11.4 ns each however many workgroups issue them: with tiles of
+// 1024 they were half of this kernel's 0.82 ms for 33M rays).
+constexpr uint32_t kBinItems = 16, kBinTile = kBinItems * kBlock;
 __global__ __launch_bounds__(kBlock) void k_bin(PathsDev P, int cur) {
   __shared__ uint32_t s_cnt[kNumClasses], s_base[kNumClasses];
-  const uint32_t count = P.counts[cur];
   // the traversal launch before this one has traced the shadow queue: empty it for the shading
-  if (blockIdx.x == 0 && threadIdx.x == 0) P.counts[kCountShadow] = 0u;
-  for (uint32_t blk = blockIdx.x * (4u * kBlock); blk < count; blk += gridDim.x * (4u * kBlock)) {
+  if (blockIdx.x == 0 && threadIdx.x < kShards) P.counts[count_shadow(threadIdx.x)] = 0u;
+  const QueueShare q = queue_share(P, cur);
+  for (uint32_t blk = q.wg * kBinTile; blk < q.n; blk += q.G * kBinTile) {
     if (threadIdx.x < kNumClasses) s_cnt[threadIdx.x] = 0u;
     __syncthreads();
-    uint32_t slot[4], pos[4];
-    int cls[4];
+    uint32_t slot[kBinItems], pos[kBinItems];
+    int cls[kBinItems];
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      uint32_t i = blk + k * kBlock + threadIdx.x;
+    for (uint32_t k = 0; k < kBinItems; ++k) {
+      const uint32_t i = blk + k * kBlock + threadIdx.x;
       cls[k] = -1;
-      if (i < count) {
-        slot[k] = P.q_ray[cur][i];
+      if (i < q.n) {
+        slot[k] = q.slot(P, i);
         cls[k] = P.cls[slot[k]];
-        pos[k] = atomicAdd(&s_cnt[cls[k]], 1u);  // LDS
       }
     }
+#pragma unroll
+    for (uint32_t k = 0; k < kBinItems; ++k)
+      if (cls[k] >= 0) pos[k] = atomicAdd(&s_cnt[cls[k]], 1u);  // LDS
     __syncthreads();
     if (threadIdx.x < kNumClasses) {
       uint32_t c = s_cnt[threadIdx.x];
-      s_base[threadIdx.x] = c ? atomicAdd(&P.counts[2 + threadIdx.x], c) : 0u;
+      s_base[threadIdx.x] = c ? atomicAdd(&P.counts[count_class(threadIdx.x)], c) : 0u;
     }
     __syncthreads();
 #pragma unroll
-    for (int k = 0; k < 4; ++k)
+    for (uint32_t k = 0; k < kBinItems; ++k)
       if (cls[k] >= 0) P.q_cls[cls[k]][s_base[cls[k]] + pos[k]] = slot[k];
     __syncthreads();
   }
@@ -1061,7 +1075,7 @@ __global__ __launch_bounds__(kShadeBlock) void k_shade(SceneDev S, PathsDev P, i
                                                   int nrc_bounce) {
   // per queue (next rays, shadow rays, cache queries): wave counts, then the workgroup's base
   __shared__ uint32_t s_app[3][kShadeBlock / 64 + 1];
-  const uint32_t count = P.counts[2 + CLS];
+  const uint32_t count = P.counts[count_class(CLS)];
   unsigned long long nonfinite = 0;
   for (uint32_t base = blockIdx.x * kShadeBlock; base < count; base += gridDim.x * kShadeBlock) {
     uint32_t i = base + threadIdx.x;
@@ -1073,8 +1087,9 @@ __global__ __launch_bounds__(kShadeBlock) void k_shade(SceneDev S, PathsDev P, i
       slot = P.q_cls[CLS][i];
       shade_one<CLS, DEBUG, TWO>(S, P, slot, b, max_depth, sample, k0, k1, nrc_bounce, o, nonfinite);
     }
-    // One atomic per queue per workgroup iteration: the queue counters are
-    // single words that every workgroup of the launch appends to.
+    // one atomic per queue per workgroup iteration
+    const uint32_t shard = base / kShadeBlock % kShards;
+    const size_t seg = (size_t)shard * P.seg_cap;
     const uint64_t m_cont = __ballot(o.cont), m_sh = __ballot(o.shadow), m_q = __ballot(o.query);
     const int w = (int)(threadIdx.x >> 6);
     if (lane_id() == 0) {
@@ -1086,8 +1101,9 @@ __global__ __launch_bounds__(kShadeBlock) void k_shade(SceneDev S, PathsDev P, i
     if (threadIdx.x < 3) {
       uint32_t tot = 0;
       for (int k = 0; k < kShadeBlock / 64; ++k) tot += s_app[threadIdx.x][k];
-      uint32_t* ctr = threadIdx.x == 0 ? &P.counts[next] : threadIdx.x == 1 ? &P.counts[kCountShadow]
-                                                                              : &P.counts[kCountQuery];
+      uint32_t* ctr = threadIdx.x == 0   ? &P.counts[count_ray(shard, next)]
+                      : threadIdx.x == 1 ? &P.counts[count_shadow(shard)]
+                                         : &P.counts[kCountQuery];
       s_app[threadIdx.x][kShadeBlock / 64] = tot ? atomicAdd(ctr, tot) : 0u;
     }
     __syncthreads();
@@ -1098,10 +1114,10 @@ __global__ __launch_bounds__(kShadeBlock) void k_shade(SceneDev S, PathsDev P, i
       off[q] = acc;
     }
     __syncthreads();  // s_app is rewritten by the next iteration
-    if (o.cont) P.q_ray[next][off[0] + lane_prefix(m_cont)] = slot;
+    if (o.cont) P.q_ray[next][seg + off[0] + lane_prefix(m_cont)] = slot;
     if (o.query) P.q_nrc[off[2] + lane_prefix(m_q)] = slot;
     if (o.shadow) {
-      const uint32_t spos = off[1] + lane_prefix(m_sh);
+      const size_t spos = seg + off[1] + lane_prefix(m_sh);
       P.sh_o[spos] = o.sh_o;
       P.sh_d[spos] = o.sh_d;
       P.sh_c[spos] = o.sh_c;
@@ -1160,18 +1176,21 @@ __global__ __launch_bounds__(kBlock, TWO ? kTraceWaves2 : kTraceWaves) void k_tr
   __shared__ __align__(16) unsigned char s_top[kTopLds];
   __shared__ uint32_t s_next;
   lds_byte* top = top_load(S, s_top);
-  const uint32_t ne = cur >= 0 ? P.counts[cur] : 0u, ns = P.counts[kCountShadow];
-  if (blockIdx.x == 0 && threadIdx.x == 0) {
-    if (ne) atomicAdd(&P.stats[kStatExt], (unsigned long long)ne);
-    if (ns) atomicAdd(&P.stats[kStatShadow], (unsigned long long)ns);
+  // closest-hit rays (queue `cur`; none if < 0) and shadow rays of this workgroup's segments
+  QueueShare qe = queue_share(P, max(cur, 0));
+  if (cur < 0) qe.n = 0u;
+  const uint32_t seg = blockIdx.x % kShards, wg_s = blockIdx.x / kShards, G_s = gridDim.x / kShards;
+  const uint32_t ns = P.counts[count_shadow(seg)], sh_first = seg * P.seg_cap;
+  if (threadIdx.x == 0) {  // each count once
+    if (qe.n && qe.wg == 0) atomicAdd(&P.stats[kStatExt], (unsigned long long)qe.n);
+    if (ns && wg_s == 0) atomicAdd(&P.stats[kStatShadow], (unsigned long long)ns);
   }
-  const uint32_t G = gridDim.x, wg = blockIdx.x;
-  const uint32_t n_e = share_size(ne, wg, G), n_all = n_e + share_size(ns, wg, G);
+  const uint32_t n_e = share_size(qe.n, qe.wg, qe.G), n_all = n_e + share_size(ns, wg_s, G_s);
   if (threadIdx.x == 0) s_next = 0u;
   __syncthreads();
   DevStack st = make_stack(s_stack);
   unsigned long long nonfinite = 0;
-  ExtendSrc<TWO> es{S, P, cur < 0 ? 0 : cur};
+  ExtendSrc<TWO> es{S, P};
   ConnectSrc<DEBUG, TWO> cs{S, P, nonfinite};
   LaneRay L;
   L.any = false;
@@ -1190,7 +1209,7 @@ __global__ __launch_bounds__(kBlock, TWO ? kTraceWaves2 : kTraceWaves) void k_tr
       const uint32_t v = base + lane_prefix(idle);
       if (!busy && v < n_all) {
         shadow = v >= n_e;
-        item = shadow ? share_item(v - n_e, ns, wg, G) : share_item(v, ne, wg, G);
+        item = shadow ? sh_first + share_item(v - n_e, ns, wg_s, G_s) : qe.slot(P, share_item(v, qe.n, qe.wg, qe.G));
         st.clear();
         if (shadow) cs.start(item, L);
         else es.start(item, L);
@@ -1265,20 +1284,21 @@ __global__ __launch_bounds__(kBlock) void k_tail(SceneDev S, PathsDev P, int cur
                                                  uint32_t sample, uint32_t k0, uint32_t k1,
                                                  int nrc_bounce) {
   __shared__ unsigned long long s_stack[kLdsStack * kBlock];
-  const uint32_t count = P.counts[cur];
-#if PT_TAIL_DYNAMIC
-  // every wave takes paths from one device-wide counter (zeroed before the
-  // launch), so the longest paths do not pile up in one workgroup's share
-  uint32_t* next_path = &P.counts[kCountTail];
-  const uint32_t q1 = count;
-#else
-  __shared__ uint32_t s_next;
-  const uint32_t per = (count + gridDim.x - 1) / gridDim.x;
-  const uint32_t q0 = min(count, blockIdx.x * per), q1 = min(count, q0 + per);
-  if (threadIdx.x == 0) s_next = q0;
+  __shared__ uint32_t s_count;
+  // Every wave takes paths from one device-wide counter (zeroed before the
+  // launch), so the longest paths do not pile up in one workgroup's share.
+  __shared__ uint32_t s_first[kShards];  // segments of the queue: the path number each starts at
+  if (threadIdx.x == 0) {
+    uint32_t n = 0;
+    for (uint32_t g = 0; g < kShards; ++g) {
+      s_first[g] = n;
+      n += cur == kQueueAll ? 0u : P.counts[count_ray(g, cur)];
+    }
+    s_count = cur == kQueueAll ? (uint32_t)P.n : n;
+  }
   __syncthreads();
-  uint32_t* next_path = &s_next;
-#endif
+  const uint32_t q1 = s_count;
+  uint32_t* next_path = &P.counts[kCountTail];
   DevStack st = make_stack(s_stack);
   LaneRay L;
   // 0 idle, 1 closest-hit walk, 2 shadow-ray walk, 3 hit found and waiting to be shaded
@@ -1311,7 +1331,13 @@ __global__ __launch_bounds__(kBlock) void k_tail(SceneDev S, PathsDev P, int cur
       if (base + n_idle >= q1) drained = true;
       const uint32_t i = base + lane_prefix(idle);
       if (phase == 0 && i < q1) {
-        slot = P.q_ray[cur][i];
+        if (cur == kQueueAll) {
+          slot = i;
+        } else {
+          uint32_t g = kShards - 1;
+          while (g > 0 && s_first[g] > i) --g;
+          slot = P.q_ray[cur][(size_t)g * P.seg_cap + (i - s_first[g])];
+        }
         b = b_first;
         start_closest();
       }
@@ -1645,7 +1671,10 @@ int traversal_grid(int64_t rays, bool two_level) {
     if (e != hipSuccess || per < 1) per = 1;
     resident[two_level] = std::max(1, cus * per);
   }
-  return (int)std::min<int64_t>(need, resident[two_level]);
+  // a multiple of the queues' segments, which the workgroups share out among them
+  const int64_t g = std::min<int64_t>(need, resident[two_level]);
+  return (int)std::max<int64_t>(kShards, need <= resident[two_level] ? (g + kShards - 1) / kShards * kShards
+                                                                      : g / kShards * kShards);
 }
 
 template <bool DEBUG, bool TWO>
@@ -1731,18 +1760,23 @@ static hipError_t bounce_loop(const SceneDev& S, const PathsDev& P, const CamDev
   };
   const double tail_limit = A.tail_fraction * (double)std::min(P.n, kTailPassSlots);
   for (int b = 0; b <= A.max_depth; ++b) {
-    int cur = b & 1, next = cur ^ 1;
+    const int next = (b & 1) ^ 1, cur = b == 0 ? kQueueAll : b & 1;
     if (A.tail_host_count && b >= A.tail_min_bounce) {
       // hand the remaining vertices to one persistent kernel once few paths are left
+      uint32_t alive = 0;
       if (A.tail_bound && A.nrc_bounce >= 0 && b > A.nrc_bounce &&
           (double)A.tail_bound <= tail_limit) {
-        *A.tail_host_count = A.tail_bound;  // a bound known on the host: no need to read the count
+        alive = A.tail_bound;  // a bound known on the host: no need to read the count
+      } else if (cur == kQueueAll) {
+        alive = (uint32_t)P.n;
       } else {
-        hipError_t e0 = hipMemcpyAsync(A.tail_host_count, &P.counts[cur], sizeof(uint32_t), hipMemcpyDeviceToHost, st);
+        hipError_t e0 = hipMemcpyAsync(A.tail_host_count, P.counts, kShardWords * sizeof(uint32_t),
+                                       hipMemcpyDeviceToHost, st);
         if (e0 == hipSuccess) e0 = hipStreamSynchronize(st);
         if (e0 != hipSuccess) return e0;
+        for (uint32_t g = 0; g < kShards; ++g) alive += A.tail_host_count[count_ray(g, cur)];
       }
-      if ((double)*A.tail_host_count <= tail_limit) {
+      if ((double)alive <= tail_limit) {
         if (A.wavefront_bounces) *A.wavefront_bounces = b;
         hipStream_t ts = st;
         if (A.tail_stream) {  // continue on the second stream; the caller's stream is free for the next pass
@@ -1761,10 +1795,10 @@ static hipError_t bounce_loop(const SceneDev& S, const PathsDev& P, const CamDev
           if (e2 != hipSuccess) return e2;
           query_pending = false;
         }
-        if (PT_TAIL_DYNAMIC) hipLaunchKernelGGL(k_zero_u32, dim3(1), dim3(1), 0, ts, P.counts + kCountTail);
+        hipLaunchKernelGGL(k_zero_u32, dim3(1), dim3(1), 0, ts, P.counts + kCountTail);
         if (A.tail_events) hipEventRecord(A.tail_events[0], ts);
         hipLaunchKernelGGL((k_tail<DEBUG, COUNT, TWO>),
-                           dim3(tail_grid(A.grid_trace, *A.tail_host_count, A.tail_stream != nullptr)), blk, 0, ts,
+                           dim3(tail_grid(A.grid_trace, alive, A.tail_stream != nullptr)), blk, 0, ts,
                            S, P, cur, b, A.max_depth, A.sample, A.k0, A.k1, A.nrc_bounce);
         if (A.tail_events) hipEventRecord(A.tail_events[1], ts);
         if (A.nrc_bounce >= 0 && b <= A.nrc_bounce) {
@@ -1805,8 +1839,10 @@ static hipError_t bounce_loop(const SceneDev& S, const PathsDev& P, const CamDev
   return hipGetLastError();
 }
 
-hipError_t launch_pass(const SceneDev& S, const PathsDev& P, const CamDev& C, const PassArgs& A, hipStream_t st) {
+hipError_t launch_pass(const SceneDev& S, const PathsDev& paths, const CamDev& C, const PassArgs& A, hipStream_t st) {
   dim3 blk(kBlock);
+  PathsDev P = paths;
+  P.seg_cap = (uint32_t)queue_segment(P.n);
   if (A.debug) hipLaunchKernelGGL((k_generate<true>), dim3(A.grid), blk, 0, st, P, C, A.sample, A.k0, A.k1);
   else hipLaunchKernelGGL((k_generate<false>), dim3(A.grid), blk, 0, st, P, C, A.sample, A.k0, A.k1);
   const int sel = (A.debug ? 4 : 0) | (A.count ? 2 : 0) | (A.two_level ? 1 : 0);
