@@ -86,7 +86,7 @@ bool finite_all(const float* p, size_t n) {
 
 // Device buffers of one set of path slots (struct-of-arrays).
 struct PathBufs {
-  DevBuf ray_o, ray_d, hit, hit_inst, cls, beta, L, flags, q_ray[2], q_cls[kNumClasses], sh_o, sh_d, sh_c, sh_inst,
+  DevBuf path, hit_inst, cls, L, eta, q_ray[2], q_cls[kNumClasses], sh_o, sh_d, sh_c, sh_inst,
       counts, sig, dbg_nee, dbg_tail, spill, nrc_q, q_nrc, spread;
 };
 
@@ -121,7 +121,7 @@ struct pt_scene {
   uint32_t class_mask = 0;
   // environment
   int env_w = 0, env_h = 0;
-  DevBuf env, env_row_pmf, env_row_cdf, env_col_pmf, env_col_cdf, env_row_guide, env_col_guide;
+  DevBuf env, env_row_pmf, env_row_cdf, env_col_cdf, env_row_guide, env_col_guide;
   // lights
   bool lights_dirty = true;
   DevBuf lights, light_cdf, tri_light;
@@ -317,21 +317,24 @@ pt_status ensure_lights(pt_scene* s) {
   return PT_OK;
 }
 
+// Refraction scales a path's roulette by eta^2, which is then kept per path.
+bool has_transmission(const pt_scene* s) { return (s->class_mask & ((1u << kClsGlass) | (1u << kClsGeneral))) != 0; }
+
 // Path buffers of a set for n slots: what every pass needs, and what this
 // scene's materials, instances, cache options or signatures (debug) need
-// (161 bytes a slot on the icosphere field).
+// (157 bytes a slot on the icosphere field).
 hipError_t alloc_paths(pt_scene* s, int64_t n, int set, bool debug) {
   PathBufs& B = s->pb[set];
   const size_t f4 = (size_t)n * sizeof(float4), u4 = (size_t)n * sizeof(uint32_t);
   hipError_t e = hipSuccess;
   const size_t qn = kShards * (size_t)queue_segment(n);  // a ray or shadow queue with all its segments
-  for (DevBuf* b : {&B.ray_o, &B.ray_d, &B.hit, &B.beta, &B.L})
-    if (e == hipSuccess) e = b->alloc(f4);
+  e = B.path.alloc((size_t)n * sizeof(PathRec));
+  if (e == hipSuccess) e = B.L.alloc(f4);
   for (DevBuf* b : {&B.sh_o, &B.sh_d, &B.sh_c})
     if (e == hipSuccess) e = b->alloc(qn * sizeof(float4));
   for (DevBuf* b : {&B.q_ray[0], &B.q_ray[1]})
     if (e == hipSuccess) e = b->alloc(qn * sizeof(uint32_t));
-  if (e == hipSuccess) e = B.flags.alloc(u4);
+  if (has_transmission(s) && e == hipSuccess) e = B.eta.alloc(u4);
   if (e == hipSuccess) e = B.cls.alloc((size_t)n);
   for (int i = 0; i < kNumClasses; ++i)
     if (e == hipSuccess && ((s->class_mask | (1u << kClsMiss)) & (1u << i))) e = B.q_cls[i].alloc(u4);
@@ -347,8 +350,7 @@ hipError_t alloc_paths(pt_scene* s, int64_t n, int set, bool debug) {
 }
 
 void release_paths(PathBufs& B) {
-  for (DevBuf* b : {&B.ray_o, &B.ray_d, &B.hit, &B.hit_inst, &B.cls, &B.beta, &B.L, &B.flags, &B.q_ray[0],
-                    &B.q_ray[1], &B.sh_o, &B.sh_d, &B.sh_c, &B.sh_inst, &B.sig, &B.dbg_nee, &B.dbg_tail, &B.spread,
+  for (DevBuf* b : {&B.path, &B.hit_inst, &B.cls, &B.L, &B.eta, &B.q_ray[0], &B.q_ray[1], &B.sh_o, &B.sh_d, &B.sh_c, &B.sh_inst, &B.sig, &B.dbg_nee, &B.dbg_tail, &B.spread,
                     &B.nrc_q, &B.q_nrc})
     b->release();
   for (DevBuf& b : B.q_cls) b.release();
@@ -418,7 +420,6 @@ SceneDev scene_dev(pt_scene* s, int grid_trace, int set = 0) {
   S.env = s->env.as<float4>();
   S.env_row_pmf = s->env_row_pmf.as<float>();
   S.env_row_cdf = s->env_row_cdf.as<float>();
-  S.env_col_pmf = s->env_col_pmf.as<float>();
   S.env_col_cdf = s->env_col_cdf.as<float>();
   S.env_row_guide = s->env_row_guide.as<int32_t>();
   S.env_col_guide = s->env_col_guide.as<int32_t>();
@@ -450,15 +451,12 @@ PathsDev paths_dev(pt_scene* s, int x0, int y0, int w, int h, int spp, int set =
   PathBufs& B = s->pb[set];
   PathsDev P;
   std::memset(&P, 0, sizeof(P));
-  P.ray_o = B.ray_o.as<float4>();
-  P.ray_d = B.ray_d.as<float4>();
-  P.hit = B.hit.as<float4>();
+  P.path = B.path.as<PathRec>();
   P.hit_inst = B.hit_inst.as<uint32_t>();
   P.cls = B.cls.as<uint8_t>();
   P.sh_inst = B.sh_inst.as<uint32_t>();
-  P.beta = B.beta.as<float4>();
   P.L = B.L.as<float4>();
-  P.flags = B.flags.as<uint32_t>();
+  P.eta = has_transmission(s) ? B.eta.as<float>() : nullptr;
   for (int i = 0; i < 2; ++i) P.q_ray[i] = B.q_ray[i].as<uint32_t>();
   for (int i = 0; i < kNumClasses; ++i) P.q_cls[i] = B.q_cls[i].as<uint32_t>();
   P.sh_o = B.sh_o.as<float4>();
@@ -1816,7 +1814,7 @@ pt_status pt_set_environment(pt_scene* s, const float* rgb, int32_t w, int32_t h
     s->lights_dirty = true;
     return PT_OK;
   }
-  std::vector<float> col_pmf(n), col_cdf((size_t)h * (w + 1)), row_pmf((size_t)h), row_cdf((size_t)h + 1);
+  std::vector<float> col_cdf((size_t)h * (w + 1)), row_pmf((size_t)h), row_cdf((size_t)h + 1);
   for (int y = 0; y < h; ++y) {
     double rs = roww[(size_t)y];
     double acc = 0.0;
@@ -1825,7 +1823,7 @@ pt_status pt_set_environment(pt_scene* s, const float* rgb, int32_t w, int32_t h
     for (int x = 0; x < w; ++x) {
       size_t i = (size_t)y * w + x;
       acc += colw[i];
-      col_pmf[i] = rs > 0.0 ? (float)(colw[i] / rs) : 0.0f;
+      tex[i].w = rs > 0.0 ? (float)(colw[i] / rs) : 0.0f;
       cdf[x + 1] = rs > 0.0 ? (float)(acc / rs) : 0.0f;
     }
     if (rs > 0.0) cdf[w] = 1.0f;
@@ -1854,7 +1852,6 @@ pt_status pt_set_environment(pt_scene* s, const float* rgb, int32_t w, int32_t h
   PT_HIP(upload(s->env_row_guide, row_guide.data(), row_guide.size() * sizeof(int32_t), s->stream));
   PT_HIP(upload(s->env_col_guide, col_guide.data(), col_guide.size() * sizeof(int32_t), s->stream));
   PT_HIP(upload(s->env, tex.data(), n * sizeof(float4), s->stream));
-  PT_HIP(upload(s->env_col_pmf, col_pmf.data(), n * sizeof(float), s->stream));
   PT_HIP(upload(s->env_col_cdf, col_cdf.data(), col_cdf.size() * sizeof(float), s->stream));
   PT_HIP(upload(s->env_row_pmf, row_pmf.data(), row_pmf.size() * sizeof(float), s->stream));
   PT_HIP(upload(s->env_row_cdf, row_cdf.data(), row_cdf.size() * sizeof(float), s->stream));

@@ -41,10 +41,11 @@ struct SceneDev {
   const float* light_cdf;    // [n_lights + 1]
   int32_t n_lights;
   float p_env;               // probability of sampling the environment
-  const float4* env;         // [h][w] rgb + unused
+  // [h][w] rgb, probability of the texel in its row: light sampling and its pdf need both, and read
+  // random texels of the sky (one 128-byte line each instead of two)
+  const float4* env;
   const float* env_row_pmf;  // [h]
   const float* env_row_cdf;  // [h + 1]
-  const float* env_col_pmf;  // [h][w]
   const float* env_col_cdf;  // [h][w + 1]
   const int32_t* env_row_guide;  // [kEnvRowGuide]: start of the search for u in [g/G, (g+1)/G)
   const int32_t* env_col_guide;  // [h][kEnvColGuide]
@@ -72,16 +73,24 @@ struct CamDev {
   int32_t W, H;
 };
 
-// Wavefront path state, structure-of-arrays, indexed by path slot.
+// What every vertex of a path reads and writes, in one 64-byte record: the
+// shading kernels of the material classes each visit some of the slots, so
+// separate arrays were fetched almost whole by every class (64M lines of 128
+// bytes for the 15M diffuse hits of a first vertex).
+struct alignas(64) PathRec {
+  float4 o;     // ray origin, skip primitive (bits)
+  float4 d;     // ray direction, skip instance (bits)
+  float4 hit;   // t, b1, b2, triangle record index (bits; 0xFFFFFFFF = miss)
+  float4 beta;  // throughput rgb, pdf of the last BSDF sample (0: a delta lobe)
+};
+
+// Wavefront path state, indexed by path slot.
 struct PathsDev {
-  float4* ray_o;       // o.xyz, skip primitive (bits)
-  float4* ray_d;       // d.xyz, skip instance (bits)
-  float4* hit;         // t, b1, b2, triangle record index (bits; 0xFFFFFFFF = miss)
+  PathRec* path;
   uint32_t* hit_inst;  // instance of the hit (two-level scenes)
   uint8_t* cls;        // material class of the hit (binning)
-  float4* beta;        // throughput rgb, pdf of the last BSDF sample
-  float4* L;           // radiance rgb, eta scale (product of eta^2 over refractions)
-  uint32_t* flags;     // bit 0: last bounce was a delta lobe; bits 1..: pixel index (row-major)
+  float4* L;           // radiance rgb, unused
+  float* eta;          // product of eta^2 over refractions (null: no transmissive material)
   uint32_t* q_ray[2];  // extension queues (double-buffered): kShards segments of seg_cap slots
   uint32_t* q_cls[kNumClasses];
   float4* sh_o;        // shadow queue, in segments as the ray queues: o.xyz, tmax
@@ -90,6 +99,7 @@ struct PathsDev {
   uint32_t* sh_inst;   // skip instance
   uint32_t* counts;    // queue lengths, see count_*
   uint32_t seg_cap;    // items a queue segment has room for
+  uint32_t img_w;      // image width
   unsigned long long* stats;  // see kStat*
   uint64_t* sig;       // path signatures (debug)
   uint32_t* dbg_nee;   // pending next-event light id (debug)
