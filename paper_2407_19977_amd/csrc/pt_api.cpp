@@ -133,8 +133,6 @@ struct pt_scene {
   DevBuf stats;
   unsigned long long overflow_seen = 0;  // stack overflows already reported by a failed call
   hipStream_t stream2 = nullptr;       // created on first use (default priority)
-  hipStream_t shade_side[2] = {nullptr, nullptr};  // side streams of the shading kernels (default priority)
-  hipEvent_t shade_fork = nullptr, shade_join[2] = {nullptr, nullptr};
   hipEvent_t ev_bulk[2] = {nullptr, nullptr}, ev_done[2] = {nullptr, nullptr};
   uint32_t* tail_counts = nullptr;     // pinned host copies of the queue counters, kShardWords per set
   // accumulation
@@ -622,29 +620,6 @@ pt_status read_pass_events(pt_scene* s, int set, int wavefront_bounces, int trac
   return PT_OK;
 }
 
-// Run sampling passes over the tile (x0, y0, w, h) of the camera's image.
-// With train (n == 1), the pass also carries the frame's training paths and
-// the cache learns from them afterwards.  Without training, consecutive
-// passes use the two path sets alternately: a pass's tail kernel and its
-// accumulation run on the second stream while the next pass's dense bounces
-// run on the scene's stream; the accumulations stay in pass order.
-#ifndef PT_SHADE_SIDE
-#define PT_SHADE_SIDE 1
-#endif
-// Side streams for the shading kernels of a pass (created once).
-pt_status shade_streams(pt_scene* s, PassArgs& A) {
-  if (!PT_SHADE_SIDE) return PT_OK;
-  for (int k = 0; k < 2; ++k) {
-    if (!s->shade_side[k]) PT_HIP(hipStreamCreateWithFlags(&s->shade_side[k], hipStreamNonBlocking));
-    if (!s->shade_join[k]) PT_HIP(hipEventCreateWithFlags(&s->shade_join[k], hipEventDisableTiming));
-    A.shade_side[k] = s->shade_side[k];
-    A.shade_join[k] = s->shade_join[k];
-  }
-  if (!s->shade_fork) PT_HIP(hipEventCreateWithFlags(&s->shade_fork, hipEventDisableTiming));
-  A.shade_fork = s->shade_fork;
-  return PT_OK;
-}
-
 // Slots of a sampling pass with several samples per pixel.  A pass of few
 // paths is bound by its launches and by each launch's longest ray (the box at
 // 128x128, 16 spp: 16 passes of 16K slots 4.66 ms, one pass of 262K 0.46 ms).
@@ -661,6 +636,12 @@ int pass_samples(int64_t pixels, int n, int64_t slots = kPassSlots) {
   return (int)((n + passes - 1) / passes);
 }
 
+// Run sampling passes over the tile (x0, y0, w, h) of the camera's image.
+// With train (n == 1), the pass also carries the frame's training paths and
+// the cache learns from them afterwards.  Without training, consecutive
+// passes use the two path sets alternately: a pass's tail kernel and its
+// accumulation run on the second stream while the next pass's dense bounces
+// run on the scene's stream; the accumulations stay in pass order.
 pt_status run_passes(pt_scene* s, const CamDev& C, int x0, int y0, int w, int h, int first, int n, int max_depth,
                      uint64_t seed, double* sum, float* per_sample, uint64_t* sigs, int spp_total,
                      bool train = false) {
@@ -743,7 +724,6 @@ pt_status run_passes(pt_scene* s, const CamDev& C, int x0, int y0, int w, int h,
     }
     A.wavefront_bounces = &wavefront[set];
     A.trace_launches = &traces[set];
-    if ((r = shade_streams(s, A))) return r;
     tail_on_2[set] = false;
     if (overlap) {
       A.tail_stream = s->stream2;
@@ -885,7 +865,6 @@ pt_status run_cache_frames(pt_scene* s, const CamDev& C, int first, int n, int m
     }
     A.wavefront_bounces = &wavefront[set];
     A.trace_launches = &traces[set];
-    if ((r = shade_streams(s, A))) return r;
     tail_on_2[set] = false;
     A.tail_stream = s->stream2;
     A.tail_ready = s->ev_bulk[set];
@@ -1660,12 +1639,6 @@ void pt_scene_destroy(pt_scene* s) {
       if (s->ev_train_t[k][j]) (void)hipEventDestroy(s->ev_train_t[k][j]);
   }
   if (s->ev_train) (void)hipEventDestroy(s->ev_train);
-  for (int k = 0; k < 2; ++k) {
-    if (s->shade_side[k]) (void)hipStreamSynchronize(s->shade_side[k]);
-    if (s->shade_join[k]) (void)hipEventDestroy(s->shade_join[k]);
-    if (s->shade_side[k]) (void)hipStreamDestroy(s->shade_side[k]);
-  }
-  if (s->shade_fork) (void)hipEventDestroy(s->shade_fork);
   if (s->stream2) (void)hipStreamDestroy(s->stream2);
   if (s->tail_counts) (void)hipHostFree(s->tail_counts);
   delete s;

@@ -201,10 +201,6 @@ struct PassArgs {
   hipEvent_t query_wait;
   uint32_t tail_bound;
   bool query_beside;  // launch the cache queries on tail_stream at the hand-off, before the tail kernel
-  // two side streams (both or neither) on which shading kernels of different material classes run
-  // beside the pass's stream, with a fork event and one join event per side stream
-  hipStream_t shade_side[2];
-  hipEvent_t shade_fork, shade_join[2];
 };
 
 hipError_t launch_pass(const SceneDev& S, const PathsDev& P, const CamDev& C, const PassArgs& A,

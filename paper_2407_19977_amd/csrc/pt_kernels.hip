@@ -402,11 +402,6 @@ constexpr uint32_t kRefill = PT_REFILL;  // idle lanes that trigger a refill
 // traversal kernels: lanes at a leaf wait until kLeafWait x their number
 // reaches kLeafWaitDen x the number of lanes at inner nodes (0: no waiting)
 constexpr uint32_t kLeafWait = PT_LEAF_WAIT, kLeafWaitDen = PT_LEAF_WAIT_DEN;
-#ifndef PT_SHADE_GRID_DIV
-#define PT_SHADE_GRID_DIV 3
-#endif
-// with side streams each class kernel gets 1/PT_SHADE_GRID_DIV of the grid, so
-// that the concurrent class kernels can be resident together
 #ifndef PT_TAIL_SHADE_WAIT
 #define PT_TAIL_SHADE_WAIT 1
 #endif
@@ -1077,8 +1072,11 @@ __device__ inline void shade_one(const SceneDev& S, const PathsDev& P, uint32_t 
   }
 }
 
+#ifndef PT_SHADE_WAVES
+#define PT_SHADE_WAVES 4  // 3 (uncapped) 89.1 ms a field render, 4 88.4, 5 94.5, 6 99.5 (spills)
+#endif
 template <int CLS, bool DEBUG, bool TWO>
-__global__ __launch_bounds__(kShadeBlock) void k_shade(SceneDev S, PathsDev P, int b, int max_depth, int next,
+__global__ __launch_bounds__(kShadeBlock, PT_SHADE_WAVES) void k_shade(SceneDev S, PathsDev P, int b, int max_depth, int next,
                                                   uint32_t sample, uint32_t k0, uint32_t k1,
                                                   int nrc_bounce) {
   // per queue (next rays, shadow rays, cache queries): wave counts, then the workgroup's base
@@ -1708,33 +1706,21 @@ int traversal_grid(int64_t rays, bool two_level) {
                                                                       : g / kShards * kShards);
 }
 
+// One shading launch per material class, one after the other: each fills the
+// chip, and side by side on three streams they took as long together (33M
+// paths: 3.45 ms either way) plus 20-30 us a vertex for the joins (box 512x512,
+// 64 spp 5.86 ms against 5.32, icosphere field 13.4 / 13.0, material zoo 16.5 /
+// 15.5; the zoo's seven small launches at 524K slots 1.77 / 1.92).
 template <bool DEBUG, bool TWO>
-static hipError_t shade_all(const SceneDev& S, const PathsDev& P, const PassArgs& A, int b, int next,
-                            hipStream_t st) {
-  // The class kernels touch disjoint path slots and append through atomics,
-  // so with side streams they run concurrently (each is bound by the
-  // latency of its own dependent loads): class i of those present goes to
-  // stream i mod 3 (0: the pass's stream), which then waits for the others.
-  hipStream_t lane[3] = {st, A.shade_side[0], A.shade_side[1]};
-  int n_streams = A.shade_side[0] && A.shade_side[1] ? 3 : 1, used = 0;
-  dim3 g(std::max(1, A.grid * kBlock / kShadeBlock / (n_streams > 1 ? PT_SHADE_GRID_DIV : 1))), blk(kShadeBlock);
-  bool forked = false;
+static hipError_t shade_all(const SceneDev& S, const PathsDev& P, const PassArgs& A, int b, int next, hipStream_t st) {
+  dim3 g(std::max(1, A.grid * kBlock / kShadeBlock)), blk(kShadeBlock);
   for (int c = 0; c < kNumClasses; ++c) {
     if (!(A.class_mask & (1u << c))) continue;
-    hipStream_t q = lane[used % n_streams];
-    if (q != st && !forked) {
-      hipError_t e = hipEventRecord(A.shade_fork, st);
-      if (e == hipSuccess) e = hipStreamWaitEvent(A.shade_side[0], A.shade_fork, 0);
-      if (e == hipSuccess) e = hipStreamWaitEvent(A.shade_side[1], A.shade_fork, 0);
-      if (e != hipSuccess) return e;
-      forked = true;
-    }
-    ++used;
     switch (c) {
-#define PT_SHADE(C)                                                                                      \
-  case C:                                                                                                \
-    hipLaunchKernelGGL((k_shade<C, DEBUG, TWO>), g, blk, 0, q, S, P, b, A.max_depth, next, A.sample, A.k0, \
-                       A.k1, A.nrc_bounce);                                                           \
+#define PT_SHADE(C)                                                                                       \
+  case C:                                                                                                 \
+    hipLaunchKernelGGL((k_shade<C, DEBUG, TWO>), g, blk, 0, st, S, P, b, A.max_depth, next, A.sample, A.k0, \
+                       A.k1, A.nrc_bounce);                                                               \
     break;
       PT_SHADE(kClsMiss)
       PT_SHADE(kClsAbsorb)
@@ -1744,13 +1730,6 @@ static hipError_t shade_all(const SceneDev& S, const PathsDev& P, const PassArgs
       PT_SHADE(kClsGlass)
       PT_SHADE(kClsGeneral)
 #undef PT_SHADE
-    }
-  }
-  if (forked) {
-    for (int k = 0; k < 2; ++k) {
-      hipError_t e = hipEventRecord(A.shade_join[k], A.shade_side[k]);
-      if (e == hipSuccess) e = hipStreamWaitEvent(st, A.shade_join[k], 0);
-      if (e != hipSuccess) return e;
     }
   }
   return hipGetLastError();
@@ -1763,6 +1742,14 @@ static hipError_t shade_all(const SceneDev& S, const PathsDev& P, const PassArgs
 // slots: 0.7M 103.8 ms, 1.4M 103.5, 2M 102.9, 3M 106.5, no bound (2^24
 // slots) 121.9; instanced scene 32 spp: 151.7 / 153.7 / 150.8 / 153.7 ms.
 static constexpr int32_t kTailPassSlots = 1 << 21;
+// A pass of few slots runs in the tail kernel from its first vertex: the
+// wavefront's launches, stream joins and count reads take longer than its
+// better lane use saves.  Render in us, wavefront first / whole pass: box 262K
+// slots 538 / 324, 524K 565 / 455, 1M 704 / 740; material zoo 262K 1673 / 1439,
+// 524K 1784 / 2097; icosphere field (1.31M triangles) 16K 1346 / 837, 262K 1532 /
+// 1069, 524K 1716 / 1528, 1M 2027 / 2468; instanced 262K 2689 / 2067, 524K 2998 /
+// 3247.
+static constexpr int32_t kWholePassSlots = 5 << 16;
 
 template <bool DEBUG, bool COUNT, bool TWO>
 static hipError_t bounce_loop(const SceneDev& S, const PathsDev& P, const CamDev& C, const PassArgs& A,
@@ -1792,7 +1779,8 @@ static hipError_t bounce_loop(const SceneDev& S, const PathsDev& P, const CamDev
   const double tail_limit = A.tail_fraction * (double)std::min(P.n, kTailPassSlots);
   for (int b = 0; b <= A.max_depth; ++b) {
     const int next = (b & 1) ^ 1, cur = b == 0 ? kQueueAll : b & 1;
-    if (A.tail_host_count && b >= A.tail_min_bounce) {
+    const bool whole = P.n <= kWholePassSlots;
+    if (A.tail_host_count && (whole || b >= A.tail_min_bounce)) {
       // hand the remaining vertices to one persistent kernel once few paths are left
       uint32_t alive = 0;
       if (A.tail_bound && A.nrc_bounce >= 0 && b > A.nrc_bounce &&
@@ -1807,7 +1795,7 @@ static hipError_t bounce_loop(const SceneDev& S, const PathsDev& P, const CamDev
         if (e0 != hipSuccess) return e0;
         for (uint32_t g = 0; g < kShards; ++g) alive += A.tail_host_count[count_ray(g, cur)];
       }
-      if ((double)alive <= tail_limit) {
+      if (whole || (double)alive <= tail_limit) {
         if (A.wavefront_bounces) *A.wavefront_bounces = b;
         hipStream_t ts = st;
         if (A.tail_stream) {  // continue on the second stream; the caller's stream is free for the next pass
