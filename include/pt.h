@@ -398,7 +398,9 @@ pt_status pt_nrc_training_records(pt_scene* scene, const pt_camera* camera, int3
  * at most 2^21 of them: a pass holds several samples of every pixel) are still
  * alive, one persistent kernel runs all remaining vertices of every path
  * (closest hit, shading, shadow ray, next ray) without a kernel boundary
- * per bounce.  The decision reads one counter back per pass.  Results are
+ * per bounce.  The decision reads one counter back per pass.  A pass of at
+ * most 327,680 slots runs in that kernel from its first vertex, unless the
+ * hand-off is off.  Results are
  * identical either way (same arithmetic, same random numbers).  Defaults:
  * min_bounce 2, max_fraction 0.15; max_fraction 0 (or min_bounce > 64)
  * keeps the wavefront throughout.  Errors: INVALID_ARG for min_bounce < 0

@@ -390,7 +390,7 @@ __global__ void k_reset_counts(uint32_t* counts, int next_queue) {
 // child order), so the closest hit is unchanged bit for bit.
 constexpr uint32_t kNoInst = 0xFFFFFFFFu;
 #ifndef PT_REFILL
-#define PT_REFILL 16
+#define PT_REFILL 20  // 10 / 16 / 20 / 24: field 87.7 / 86.9 / 86.4 / 86.8 ms, instanced 117.4 / 114.3 / 112.9 / 112.6
 #endif
 constexpr uint32_t kRefill = PT_REFILL;  // idle lanes that trigger a refill
 #ifndef PT_LEAF_WAIT
@@ -722,7 +722,11 @@ __device__ inline bool lane_step(const SceneDev& S, LaneRay& L, float tmin, DevS
 }
 
 // The persistent-lane loop shared by the traversal kernels.  Src supplies
-// start(i, L) (load item i into the lane) and finish(i, L, found).
+// start(i, L) (load item i into the lane) and finish(i, L, found).  A lane whose
+// walk has ended keeps its result until the next refill, where all such lanes
+// finish together: one or two lanes end at almost every step, and finishing them
+// at once put two dependent loads into every step of the wave (field of spheres
+// 1920x1080 64 spp 88.4 -> 86.4 ms, instanced 115.4 -> 112.9).
 template <int KIND, bool COUNT, bool TWO, class Src>
 __device__ inline void persistent_trace(const SceneDev& S, Src& src, uint32_t count, unsigned long long* s_stack,
                                         lds_byte* top, uint32_t* s_next, uint32_t& nvis, uint32_t& ntri, bool& overflow) {
@@ -732,12 +736,15 @@ __device__ inline void persistent_trace(const SceneDev& S, Src& src, uint32_t co
   __syncthreads();
   DevStack st = make_stack(s_stack);
   LaneRay L;
-  bool busy = false, drained = false;
+  bool busy = false, ended = false, drained = false;
   uint32_t item = 0;
   while (true) {
     const uint64_t idle = __ballot(!busy);
     const uint32_t n_idle = (uint32_t)__popcll((unsigned long long)idle);
-    if (!drained && (n_idle >= kRefill || n_idle == 64u)) {
+    if ((!drained && n_idle >= kRefill) || n_idle == 64u) {
+      if (ended) src.finish(item, L, L.found());
+      ended = false;
+      if (drained) break;
       uint32_t base = 0;
       if (lane_id() == 0) base = atomicAdd(s_next, n_idle);
       base = __shfl(base, 0);
@@ -763,8 +770,8 @@ __device__ inline void persistent_trace(const SceneDev& S, Src& src, uint32_t co
     }
     uint32_t ninst = 0;
     if (go && lane_step<KIND, COUNT, TWO, true>(S, L, src.tmin, st, top, nvis, ntri, ninst)) {
-      src.finish(item, L, L.found());
       busy = false;
+      ended = true;
     }
   }
   overflow |= st.overflow;
@@ -1200,14 +1207,31 @@ __global__ __launch_bounds__(kBlock, TWO ? kTraceWaves2 : kTraceWaves) void k_tr
   ConnectSrc<DEBUG, TWO> cs{S, P, nonfinite};
   LaneRay L;
   L.any = false;
-  bool busy = false, drained = false, shadow = false;
+  bool busy = false, ended = false, drained = false, shadow = false;
   uint32_t item = 0;
   uint32_t rv = 0, rt = 0, nvis = 0, ntri = 0, svis = 0, stri = 0;  // node visits / triangle tests
   uint32_t ri = 0, ninst = 0;  // instances entered (both walk kinds)
   while (true) {
     const uint64_t idle = __ballot(!busy);
     const uint32_t n_idle = (uint32_t)__popcll((unsigned long long)idle);
-    if (!drained && (n_idle >= kRefill || n_idle == 64u)) {
+    if ((!drained && n_idle >= kRefill) || n_idle == 64u) {
+      if (ended) {  // the lanes whose walks have ended since the last refill
+        const bool found = L.found();
+        if (shadow) cs.finish(item, L, found);
+        else es.finish(item, L, found);
+        if (COUNT) {
+          ninst += ri;
+          if (shadow) {
+            svis += rv;
+            stri += rt;
+          } else {
+            nvis += rv;
+            ntri += rt;
+          }
+        }
+        ended = false;
+      }
+      if (drained) break;
       uint32_t base = 0;
       if (lane_id() == 0) base = atomicAdd(&s_next, n_idle);
       base = __shfl(base, 0);
@@ -1236,20 +1260,8 @@ __global__ __launch_bounds__(kBlock, TWO ? kTraceWaves2 : kTraceWaves) void k_tr
       go = busy && (!at_leaf || kLeafWait * n_leaf >= kLeafWaitDen * n_node);
     }
     if (go && lane_step<kWalkPerLane, COUNT, TWO, true>(S, L, S.tmin, st, top, rv, rt, ri)) {
-      const bool found = L.found();
-      if (shadow) cs.finish(item, L, found);
-      else es.finish(item, L, found);
-      if (COUNT) {
-        ninst += ri;
-        if (shadow) {
-          svis += rv;
-          stri += rt;
-        } else {
-          nvis += rv;
-          ntri += rt;
-        }
-      }
       busy = false;
+      ended = true;
     }
   }
   if (COUNT) {
