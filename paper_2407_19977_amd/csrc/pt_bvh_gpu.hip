@@ -52,6 +52,12 @@ constexpr int kPlocRadius = PT_PLOC_RADIUS;  // clusters searched on either side
 #define PT_MORTON_CUBE 1  // 1: Morton cells are cubes (one scale for the three axes), 0: one scale per axis
 #endif
 constexpr int kPlocMaxRounds = 4096;         // bound on the clustering rounds
+// blocks of a clustering round up to which its merge kernel adds up the counts of the blocks before
+// it itself; above, two scan launches (about 8 us) cost less than reading half of them in every block
+constexpr int kPlocSumBlocks = 8192;
+// blocks of the bounds reduction at most: each ends with six atomics on one line, 11 ns apiece
+// (8192 blocks 123 us for 1.31M triangles)
+constexpr int kBoundsGrid = 1024;
 constexpr int kPlocBatch = 8;                // rounds enqueued between two reads of the cluster count
 constexpr int kCollapseBatch = 8;            // collapse levels enqueued between two reads of the job count
 #ifndef PT_GPU_COLLAPSE_DP
@@ -165,27 +171,82 @@ __global__ __launch_bounds__(kBB) void k_radix_hist(const uint32_t* __restrict__
   hist[(size_t)threadIdx.x * nb + blockIdx.x] = h[threadIdx.x];
 }
 
-// exclusive scan of m counts in place (one workgroup of 1024 threads)
-__global__ __launch_bounds__(1024) void k_scan_excl(uint32_t* __restrict__ a, int64_t m) {
-  __shared__ uint32_t part[1024];
-  const int64_t per = (m + 1023) / 1024;
-  const int64_t k0 = std::min<int64_t>(m, (int64_t)threadIdx.x * per), k1 = std::min<int64_t>(m, k0 + per);
-  uint32_t local = 0;
-  for (int64_t k = k0; k < k1; ++k) local += a[k];
-  part[threadIdx.x] = local;
+// Sum over the block's threads, in every thread (s_w: kBB / 64 words).
+template <class T>
+__device__ inline T block_sum(T v, T* s_w) {
+  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
+  if (threadIdx.x % 64 == 0) s_w[threadIdx.x / 64] = v;
   __syncthreads();
-  for (int off = 1; off < 1024; off <<= 1) {
-    const uint32_t v = threadIdx.x >= (unsigned)off ? part[threadIdx.x - off] : 0u;
-    __syncthreads();
-    part[threadIdx.x] += v;
-    __syncthreads();
+  T t = 0;
+  for (int w = 0; w < kBB / 64; ++w) t += s_w[w];
+  __syncthreads();  // s_w may be reused
+  return t;
+}
+
+// Exclusive scan of m counts in place, tiles of kScanTile counts: the tiles'
+// sums, then every block adds up the sums before its own (at most 4096 of
+// them for the largest build) and scans its tile from registers.  A single
+// workgroup that walked 1024 strided segments took 343 us for the 164K radix
+// counts of 1.31M triangles (uncoalesced, one CU); these two launches take 5.
+constexpr int kScanPer = 16;
+constexpr int kScanTile = kBB * kScanPer;
+
+template <class T>
+__global__ __launch_bounds__(kBB) void k_scan_sums(const T* __restrict__ a, int64_t m, T* __restrict__ sums) {
+  __shared__ T s_w[kBB / 64];
+  const int64_t base = (int64_t)blockIdx.x * kScanTile + threadIdx.x;
+  T v = 0;
+  for (int r = 0; r < kScanPer; ++r) {
+    const int64_t i = base + r * kBB;
+    if (i < m) v += a[i];
   }
-  uint32_t run = part[threadIdx.x] - local;
-  for (int64_t k = k0; k < k1; ++k) {
-    const uint32_t c = a[k];
-    a[k] = run;
-    run += c;
+  v = block_sum(v, s_w);
+  if (threadIdx.x == 0) sums[blockIdx.x] = v;
+}
+
+template <class T>
+__global__ __launch_bounds__(kBB) void k_scan_tiles(T* __restrict__ a, int64_t m, const T* __restrict__ sums) {
+  __shared__ T s_w[kBB / 64], s_t[kScanTile];
+  T before = 0;
+  for (uint32_t k = threadIdx.x; k < blockIdx.x; k += kBB) before += sums[k];
+  before = block_sum(before, s_w);
+  const int64_t base = (int64_t)blockIdx.x * kScanTile;
+  for (int r = 0; r < kScanPer; ++r) {
+    const int64_t i = base + r * kBB + threadIdx.x;
+    s_t[r * kBB + threadIdx.x] = i < m ? a[i] : T(0);
   }
+  __syncthreads();
+  T local[kScanPer], sum = 0;  // thread t: counts [t kScanPer, (t + 1) kScanPer) of the tile
+  for (int r = 0; r < kScanPer; ++r) {
+    local[r] = s_t[threadIdx.x * kScanPer + r];
+    sum += local[r];
+  }
+  T incl = sum;
+  for (int off = 1; off < 64; off <<= 1) {
+    const T v = __shfl_up(incl, off);
+    if ((int)(threadIdx.x % 64) >= off) incl += v;
+  }
+  if (threadIdx.x % 64 == 63) s_w[threadIdx.x / 64] = incl;
+  __syncthreads();
+  T run = before + incl - sum;
+  for (int w = 0; w < (int)(threadIdx.x / 64); ++w) run += s_w[w];
+  for (int r = 0; r < kScanPer; ++r) {
+    s_t[threadIdx.x * kScanPer + r] = run;
+    run += local[r];
+  }
+  __syncthreads();
+  for (int r = 0; r < kScanPer; ++r) {
+    const int64_t i = base + r * kBB + threadIdx.x;
+    if (i < m) a[i] = s_t[r * kBB + threadIdx.x];
+  }
+}
+
+// sums: ceil(m / kScanTile) counts of scratch
+template <class T>
+void launch_scan(T* a, int64_t m, T* sums, hipStream_t st) {
+  const int tiles = (int)((m + kScanTile - 1) / kScanTile);
+  if (tiles > 1) hipLaunchKernelGGL(k_scan_sums<T>, dim3(tiles), dim3(kBB), 0, st, a, m, sums);
+  hipLaunchKernelGGL(k_scan_tiles<T>, dim3(tiles), dim3(kBB), 0, st, a, m, sums);
 }
 
 // Stable scatter: within each round of 256 keys a key's rank among equal
@@ -317,12 +378,11 @@ __device__ inline void dp_of_ref(uint32_t ref, const float* dp, float tri_area, 
   for (int j = 0; j < 4; ++j) D[j] = (ref & kLeafRef) ? tri_area : dp[4 * (size_t)ref + j];
 }
 
-__device__ inline void dp_node(uint32_t o, bool as_leaf, uint32_t c, float area, const float Da[4], const float Db[4],
-                               float* __restrict__ dp, uint32_t* __restrict__ dsp) {
+__device__ inline uint32_t dp_node(bool as_leaf, uint32_t c, float area, const float Da[4], const float Db[4],
+                                   float D[4]) {
   if (as_leaf) {
-    for (int j = 0; j < 4; ++j) dp[4 * (size_t)o + j] = (float)c * area;
-    dsp[o] = 0u;
-    return;
+    for (int j = 0; j < 4; ++j) D[j] = (float)c * area;
+    return 0u;
   }
   float Ds[5];
   uint32_t ks[5] = {0u, 0u, 0u, 0u, 0u};
@@ -338,17 +398,16 @@ __device__ inline void dp_node(uint32_t o, bool as_leaf, uint32_t c, float area,
   }
   float best = kSahNode * area + Ds[4];
   uint32_t dec = 0u, bits = 0u;
-  dp[4 * (size_t)o] = best;
+  D[0] = best;
   for (int j = 2; j <= 4; ++j) {
     if (Ds[j] < best) {
       best = Ds[j];
       dec = ks[j] | ((uint32_t)(j - (int)ks[j]) << 2);
     }
-    dp[4 * (size_t)o + j - 1] = best;
+    D[j - 1] = best;
     bits |= dec << (4 * (j - 1));
   }
-  bits |= (ks[4] | ((4u - ks[4]) << 2)) << 16;
-  dsp[o] = bits;
+  return bits | ((ks[4] | ((4u - ks[4]) << 2)) << 16);
 }
 
 __device__ inline float half_area(const float b[6]) {
@@ -385,342 +444,416 @@ __global__ __launch_bounds__(kBB) void k_boxes_up(int64_t n, const uint32_t* __r
       dp_of_ref(c.x, dp, half_area(a), Da);
       dp_of_ref(c.y, dp, half_area(b), Db);
       const uint32_t cp = cnt[p];
-      dp_node((uint32_t)p, (cp & kLeafBitCnt) != 0u, cp & ~kLeafBitCnt, half_area(u), Da, Db, dp, dsp);
+      float D[4];
+      dsp[p] = dp_node((cp & kLeafBitCnt) != 0u, cp & ~kLeafBitCnt, half_area(u), Da, Db, D);
+      for (int j = 0; j < 4; ++j) dp[4 * (size_t)p + j] = D[j];
       p = parent_int[p];
     }
   }
 }
 
 // ---- 4b. locally-ordered clustering.  Cluster i of a round: a binary-tree
-// reference cid[i] and its box cbox[i][6]; m clusters in Morton order.
+// reference cid[i] and its box cbox[k][i] (six planes of n floats); m clusters in
+// Morton order.
 
 __global__ __launch_bounds__(kBB) void k_ploc_init(const uint32_t* __restrict__ val, const float* __restrict__ tbox,
                                                    int64_t n, uint32_t* __restrict__ cid, float* __restrict__ cbox) {
   for (int64_t i = blockIdx.x * (int64_t)kBB + threadIdx.x; i < n; i += (int64_t)gridDim.x * kBB) {
     cid[i] = kLeafRef | (uint32_t)i;
     const float* b = tbox + 6 * (size_t)val[i];
-    for (int k = 0; k < 6; ++k) cbox[6 * i + k] = b[k];
+    for (int k = 0; k < 6; ++k) cbox[(size_t)k * n + i] = b[k];
   }
 }
 
-// Nearest neighbour of every cluster: the least surface area of the merged
+// Nearest neighbour of cluster i of m: the least surface area of the merged
 // box; among equal areas the nearer place, then an even lower index of the
 // pair, then the lower index (one rank per pair, so mutual nearest neighbours
-// always exist, and equal boxes pair up as (2k, 2k + 1)).  With `forced` the
-// neighbour is the adjacent cluster of the pair (2k, 2k + 1) outright (a
-// round after one that merged too few).  One block per kBB clusters, whose
-// boxes and their neighbours' are staged in LDS; grid >= ceil(m / kBB).  The
-// round's cluster count is mc[0] (set by the round before), and that round's
-// own count mc[1]: a round that kept over 99 % pairs neighbours outright.
-__global__ __launch_bounds__(kBB) void k_ploc_nn(const float* __restrict__ cbox, const uint32_t* __restrict__ mc,
-                                                 int32_t* __restrict__ nn) {
-  constexpr int kSpan = kBB + 2 * kPlocRadius;
-  __shared__ float sb[kSpan * 6];
-  const uint32_t m = mc[0];
-  const bool forced = (uint64_t)m * 100u > (uint64_t)mc[1] * 99u;
-  const int64_t b0 = (int64_t)blockIdx.x * kBB, s0 = b0 - kPlocRadius;
-  if (b0 >= (int64_t)m) return;
-  for (int t = threadIdx.x; t < kSpan * 6; t += kBB) {
-    const int64_t g = s0 * 6 + t;  // float index of the staged window
-    sb[t] = (g >= 0 && g < (int64_t)m * 6) ? cbox[g] : 0.0f;
+// always exist, and equal boxes pair up as (2k, 2k + 1)).  At one distance
+// that is the lower place, unless it is odd and i is even.  G neighbouring
+// lanes share a place: even lanes look below, odd ones above, each at every
+// (G / 2)-th distance; the chain of one thread's comparisons is what a round
+// lasts once few clusters are left.  Place i's box is s.get(at).  All G lanes
+// return the neighbour, i if no area compares.
+struct SharedBoxes {  // in LDS, read as 16 + 8 bytes
+  float4* a;          // lo xyz, hi x
+  float2* b;          // hi yz
+  __device__ void put(int q, const float v[6]) const {
+    a[q] = make_float4(v[0], v[1], v[2], v[3]);
+    b[q] = make_float2(v[4], v[5]);
   }
-  __syncthreads();
-  const int64_t i = b0 + threadIdx.x;
-  if (i >= (int64_t)m) return;
-  if (forced) {
-    const int64_t j = i ^ 1;
-    nn[i] = (int32_t)(j < (int64_t)m ? j : i);
-    return;
+  __device__ void get(int q, float v[6]) const {
+    const float4 x = a[q];
+    const float2 y = b[q];
+    v[0] = x.x;
+    v[1] = x.y;
+    v[2] = x.z;
+    v[3] = x.w;
+    v[4] = y.x;
+    v[5] = y.y;
   }
-  const float* bi = sb + 6 * (threadIdx.x + kPlocRadius);
+};
+
+template <int G>
+__device__ inline uint32_t ploc_nearest(const SharedBoxes& s, int at, uint32_t i, uint32_t m) {
+  constexpr uint32_t kNone = 0xFFFFFFFFu;
+  const uint32_t g = threadIdx.x % G;
+  const bool up = (g & 1u) != 0u;
+  const uint32_t reach = up ? m - 1u - i : i;
+  const int step = up ? 1 : -1;
+  float bi[6];
+  s.get(at, bi);
   float best = INFINITY;
-  uint32_t bd = 0xFFFFFFFFu, blo = 0xFFFFFFFFu;
-  int32_t bj = (int32_t)i;
-  for (int d = -kPlocRadius; d <= kPlocRadius; ++d) {
-    const int64_t j = i + d;
-    if (d == 0 || j < 0 || j >= (int64_t)m) continue;
-    const float* bb = sb + 6 * (threadIdx.x + kPlocRadius + d);
+  uint32_t bd = kNone;
+#pragma unroll
+  for (int r = 0; r < 2 * kPlocRadius / G; ++r) {
+    const uint32_t d = 1u + (g >> 1) + (uint32_t)(G / 2 * r);
     float u[6];
+    s.get(at + step * (int)d, u);
     for (int k = 0; k < 3; ++k) {
-      u[k] = fminf(bi[k], bb[k]);
-      u[3 + k] = fmaxf(bi[3 + k], bb[3 + k]);
+      u[k] = fminf(bi[k], u[k]);
+      u[3 + k] = fmaxf(bi[3 + k], u[3 + k]);
     }
     const float a = half_area(u);
-    const uint32_t ad = (uint32_t)(d < 0 ? -d : d), lo = (uint32_t)(d < 0 ? j : i);
-    const bool better =
-        a < best || (a == best && (ad < bd || (ad == bd && ((lo & 1u) < (blo & 1u) ||
-                                                            ((lo & 1u) == (blo & 1u) && lo < blo)))));
-    if (better) {
+    if (d <= reach && (a < best || (a == best && bd == kNone))) {
       best = a;
-      bd = ad;
-      blo = lo;
-      bj = (int32_t)j;
+      bd = d;
     }
   }
-  nn[i] = bj;
-}
-
-// Mutual nearest neighbours i < j merge: a new node (children cid[i], cid[j])
-// takes place i; place j is dropped (keep[j] = 0).  Only thread i reads place
-// j and writes place i, so the update is in place.  The new node's SAH cost
-// (surface area x (kSahNode + the children's costs), a single triangle costing
-// its area) decides whether its subtree becomes one BVH4 leaf: when it holds
-// at most kMaxLeafTris triangles and testing them all costs no more.
-__global__ __launch_bounds__(kBB) void k_ploc_merge(uint32_t* __restrict__ cid, float* __restrict__ cbox,
-                                                    const uint32_t* __restrict__ mc, const int32_t* __restrict__ nn,
-                                                    uint2* __restrict__ child, float* __restrict__ nbox,
-                                                    uint32_t* __restrict__ cnt, float* __restrict__ ncost,
-                                                    float* __restrict__ dp, uint32_t* __restrict__ dsp,
-                                                    uint32_t* __restrict__ n_int, uint32_t cap,
-                                                    uint32_t* __restrict__ keep, uint32_t* __restrict__ err) {
-  const uint32_t m = mc[0];
-  for (int64_t i = blockIdx.x * (int64_t)kBB + threadIdx.x; i < (int64_t)m; i += (int64_t)gridDim.x * kBB) {
-    const int32_t j = nn[i];
-    const bool mutual = j != (int32_t)i && j >= 0 && j < (int32_t)m && nn[j] == (int32_t)i;
-    if (mutual && j < (int32_t)i) {
-      keep[i] = 0u;
-      continue;
+  // rank of the place among equal areas
+  uint32_t rank = bd == kNone ? kNone : 2u * bd + (uint32_t)(up != ((i & 1u) == 0u && (bd & 1u) != 0u));
+  uint32_t j = bd == kNone ? i : (up ? i + bd : i - bd);
+  for (int off = 1; off < G; off <<= 1) {
+    const float oa = __shfl_xor(best, off);
+    const uint32_t orank = __shfl_xor(rank, off), oj = __shfl_xor(j, off);
+    if (oa < best || (oa == best && orank < rank)) {
+      best = oa;
+      rank = orank;
+      j = oj;
     }
-    keep[i] = 1u;
-    if (!mutual) continue;
-    const uint32_t o = atomicAdd(n_int, 1u);
-    if (o >= cap) {  // more merges than a binary tree of this size has nodes: report
-      atomicOr(err, 4u);
-      continue;
-    }
-    const uint32_t a = cid[i], b = cid[j];
-    float u[6], ba[6], bb[6];
-    for (int k = 0; k < 6; ++k) {
-      ba[k] = cbox[6 * i + k];
-      bb[k] = cbox[6 * (size_t)j + k];
-    }
-    for (int k = 0; k < 3; ++k) {
-      u[k] = fminf(ba[k], bb[k]);
-      u[3 + k] = fmaxf(ba[3 + k], bb[3 + k]);
-    }
-    for (int k = 0; k < 6; ++k) {
-      nbox[6 * (size_t)o + k] = u[k];
-      cbox[6 * i + k] = u[k];
-    }
-    const uint32_t c = ref_count(a, cnt) + ref_count(b, cnt);
-    const float area = half_area(u);
-    const float ca = (a & kLeafRef) ? half_area(ba) : ncost[a], cb = (b & kLeafRef) ? half_area(bb) : ncost[b];
-    const float split = kSahNode * area + ca + cb, leaf = (float)c * area;
-    const bool as_leaf = c <= (uint32_t)kMaxLeafTris && leaf <= split;
-    ncost[o] = as_leaf ? leaf : split;
-    float Da[4], Db[4];
-    dp_of_ref(a, dp, half_area(ba), Da);
-    dp_of_ref(b, dp, half_area(bb), Db);
-    dp_node(o, as_leaf, c, area, Da, Db, dp, dsp);
-    child[o] = make_uint2(a, b);
-    cnt[o] = as_leaf ? (c | kLeafBitCnt) : c;
-    cid[i] = o;
   }
+  return j;
 }
 
-// Kept clusters per block of kBB places (every block of the grid writes its count).
-__global__ __launch_bounds__(kBB) void k_ploc_count(const uint32_t* __restrict__ keep, const uint32_t* __restrict__ mc,
-                                                    uint32_t* __restrict__ bc) {
-  __shared__ uint32_t w[kBB / 64];
+// A round's pairs.  mate[i]: the cluster that merges with i (mutual nearest
+// neighbours), else i.  With over 99 % of the clusters of the round before
+// kept (mc[1]: that round's own count, mc[0]: this round's) the pairs are
+// (2k, 2k + 1) outright.  One block per kBB places; it also finds the
+// neighbours of the kPlocRadius places on either side, so that it knows its
+// pairs without another launch, and counts its kept places (low word) and
+// its merges (high word) in bc (0 past the last cluster).  Two threads a
+// place; bound by LDS reads of the 32 boxes a cluster is compared with.
+constexpr int kNnThreads = 2 * (kBB + 2 * kPlocRadius);
+static_assert(kNnThreads % 64 == 0 && kNnThreads <= 1024, "whole waves");
+__global__ __launch_bounds__(kNnThreads) void k_ploc_nn(const float* __restrict__ cbox, uint32_t n,
+                                                 const uint32_t* __restrict__ mc, int32_t* __restrict__ mate,
+                                                 unsigned long long* __restrict__ bc) {
+  constexpr int kNear = kBB + 2 * kPlocRadius;   // places whose neighbour is found here
+  constexpr int kSpan = kBB + 4 * kPlocRadius;   // places compared
+  __shared__ float4 s_a[kSpan];
+  __shared__ float2 s_b[kSpan];
+  const SharedBoxes boxes{s_a, s_b};
+  __shared__ uint32_t s_nn[kNear];
+  __shared__ unsigned long long s_w[kNnThreads / 64];
   const uint32_t m = mc[0];
-  const int64_t i = (int64_t)blockIdx.x * kBB + threadIdx.x;
-  const uint64_t bal = __ballot(i < (int64_t)m && keep[i] != 0u);
-  if (threadIdx.x % 64 == 0) w[threadIdx.x / 64] = (uint32_t)__popcll(bal);
+  const bool forced = (uint64_t)m * 100u > (uint64_t)mc[1] * 99u;
+  const int64_t b0 = (int64_t)blockIdx.x * kBB;
+  if (b0 >= (int64_t)m) {
+    if (threadIdx.x == 0) bc[blockIdx.x] = 0ull;
+    return;
+  }
+  if (!forced) {
+    for (int t = threadIdx.x; t < kSpan; t += kNnThreads) {
+      const int64_t g = b0 - 2 * kPlocRadius + t;
+      const bool in = g >= 0 && g < (int64_t)m;
+      float v[6];
+      for (int k = 0; k < 6; ++k) v[k] = in ? cbox[(size_t)k * n + g] : 0.0f;
+      boxes.put(t, v);
+    }
+    __syncthreads();
+  }
+  const int t = threadIdx.x / 2;  // a pair of lanes takes the same branches
+  const int64_t p = b0 - kPlocRadius + t;
+  uint32_t near = 0;
+  if (p >= 0 && p < (int64_t)m) {
+    const uint32_t q = (uint32_t)p;
+    near = forced ? ((q ^ 1u) < m ? q ^ 1u : q) : ploc_nearest<2>(boxes, t + kPlocRadius, q, m);
+  }
+  if (threadIdx.x % 2 == 0) s_nn[t] = near;
+  __syncthreads();
+  const uint32_t i = (uint32_t)b0 + threadIdx.x;
+  bool kept = false, merges = false;
+  if (threadIdx.x < kBB && i < m) {
+    const uint32_t j = s_nn[threadIdx.x + kPlocRadius];
+    // j is within kPlocRadius places of i
+    const bool mutual = j != i && s_nn[(int)(j - (uint32_t)b0) + kPlocRadius] == i;
+    mate[i] = (int32_t)(mutual ? j : i);
+    kept = !(mutual && j < i);
+    merges = mutual && i < j;
+  }
+  const unsigned long long w = (unsigned long long)__popcll(__ballot(kept)) |
+                               ((unsigned long long)__popcll(__ballot(merges)) << 32);
+  if (threadIdx.x % 64 == 0) s_w[threadIdx.x / 64] = w;
   __syncthreads();
   if (threadIdx.x == 0) {
-    uint32_t t = 0;
-    for (int k = 0; k < kBB / 64; ++k) t += w[k];
-    bc[blockIdx.x] = t;
+    unsigned long long sum = 0;
+    for (int k = 0; k < kBB / 64; ++k) sum += s_w[k];
+    bc[blockIdx.x] = sum;
   }
 }
 
-// Kept clusters to their places in the next round's arrays, in order (off:
-// exclusive scan of the block counts); the last block writes the new count
-// to mc_out[0] and this round's to mc_out[1] (the next round's mc).
-__global__ __launch_bounds__(kBB) void k_ploc_scatter(const uint32_t* __restrict__ cid, const float* __restrict__ cbox,
-                                                      const uint32_t* __restrict__ keep, const uint32_t* __restrict__ mc,
-                                                      const uint32_t* __restrict__ off, uint32_t* __restrict__ cid2,
-                                                      float* __restrict__ cbox2, uint32_t* __restrict__ mc_out) {
-  __shared__ uint32_t w[kBB / 64];
-  const uint32_t m = mc[0];
-  const int64_t i = (int64_t)blockIdx.x * kBB + threadIdx.x;
-  const bool k = i < (int64_t)m && keep[i] != 0u;
-  const uint64_t bal = __ballot(k);
-  const int wave = threadIdx.x / 64, lane = threadIdx.x % 64;
-  if (lane == 0) w[wave] = (uint32_t)__popcll(bal);
-  __syncthreads();
-  uint32_t pos = off[blockIdx.x];
-  for (int q = 0; q < wave; ++q) pos += w[q];
-  const uint64_t lt = lane == 0 ? 0ull : (~0ull >> (64 - lane));
-  pos += (uint32_t)__popcll(bal & lt);
-  if (k) {
-    cid2[pos] = cid[i];
-    for (int q = 0; q < 6; ++q) cbox2[6 * (size_t)pos + q] = cbox[6 * i + q];
+// What the rounds know of a cluster's subtree: triangles (kLeafBitCnt: one
+// BVH4 leaf), SAH cost and the costs of covering it with 1..4 roots.
+struct SubTree {
+  uint32_t cnt;
+  float cost, D[4];
+};
+
+__device__ inline SubTree sub_tree(uint32_t ref, float area, const uint32_t* cnt, const float* ncost, const float* dp) {
+  SubTree s;
+  if (ref & kLeafRef) {
+    s.cnt = 1u;
+    s.cost = area;
+    for (int j = 0; j < 4; ++j) s.D[j] = area;
+  } else {
+    s.cnt = cnt[ref];
+    s.cost = ncost[ref];
+    const float4 d = reinterpret_cast<const float4*>(dp)[ref];
+    s.D[0] = d.x;
+    s.D[1] = d.y;
+    s.D[2] = d.z;
+    s.D[3] = d.w;
   }
-  if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) {
-    uint32_t t = off[blockIdx.x];
-    for (int q = 0; q < kBB / 64; ++q) t += w[q];
-    mc_out[0] = t;
+  return s;
+}
+
+// Binary node o of the clusters a and b (boxes ba, bb); its box replaces ba,
+// what the next rounds need of it sa.  Its SAH cost (surface area x (kSahNode
+// + the children's costs), a single triangle costing its area) decides whether
+// its subtree becomes one BVH4 leaf: when it holds at most kMaxLeafTris
+// triangles and testing them all costs no more.
+__device__ inline void ploc_node(uint32_t o, uint32_t a, uint32_t b, float ba[6], const float bb[6], SubTree& sa,
+                                 const SubTree& sc, uint2* __restrict__ child, float* __restrict__ nbox,
+                                 uint32_t* __restrict__ cnt, float* __restrict__ dp, uint32_t* __restrict__ dsp) {
+  for (int k = 0; k < 3; ++k) {
+    ba[k] = fminf(ba[k], bb[k]);
+    ba[3 + k] = fmaxf(ba[3 + k], bb[3 + k]);
+  }
+  for (int k = 0; k < 6; ++k) nbox[6 * (size_t)o + k] = ba[k];
+  const uint32_t c = (sa.cnt & ~kLeafBitCnt) + (sc.cnt & ~kLeafBitCnt);
+  const float area = half_area(ba);
+  const float split = kSahNode * area + sa.cost + sc.cost, leaf = (float)c * area;
+  const bool as_leaf = c <= (uint32_t)kMaxLeafTris && leaf <= split;
+  float D[4];
+  dsp[o] = dp_node(as_leaf, c, area, sa.D, sc.D, D);
+  reinterpret_cast<float4*>(dp)[o] = make_float4(D[0], D[1], D[2], D[3]);
+  child[o] = make_uint2(a, b);
+  sa.cnt = as_leaf ? (c | kLeafBitCnt) : c;
+  cnt[o] = sa.cnt;
+  sa.cost = as_leaf ? leaf : split;
+  for (int j = 0; j < 4; ++j) sa.D[j] = D[j];
+}
+
+// A round's merges and the compaction in one pass: pairs i < j become one node
+// at place i, place j is dropped, and the kept clusters go in order to the
+// next round's arrays.  After a tree of n leaves has come down to m clusters
+// it has n - m inner nodes, so a merge's node index is n - m plus the merges
+// before it: no counter is shared (one atomic per wave on one line took most
+// of a 239 us first round; this pass takes 38).  bc: this round's block
+// counts, or with `scanned` their exclusive scan.  The last block writes the
+// new count to mc_out[0] and this round's to mc_out[1].
+__global__ __launch_bounds__(kBB) void k_ploc_merge(
+    const uint32_t* __restrict__ cid, const float* __restrict__ cbox, uint32_t n, const uint32_t* __restrict__ mc,
+    const int32_t* __restrict__ mate, const unsigned long long* __restrict__ bc, bool scanned,
+    uint2* __restrict__ child, float* __restrict__ nbox, uint32_t* __restrict__ cnt, float* __restrict__ ncost,
+    float* __restrict__ dp, uint32_t* __restrict__ dsp, uint32_t* __restrict__ cid2, float* __restrict__ cbox2,
+    uint32_t* __restrict__ mc_out, uint32_t* __restrict__ err) {
+  __shared__ unsigned long long s_w[kBB / 64];
+  const uint32_t m = mc[0];
+  const bool last = blockIdx.x == gridDim.x - 1;
+  if ((int64_t)blockIdx.x * kBB >= (int64_t)m && !last) return;
+  unsigned long long before = 0;
+  if (scanned) {
+    before = bc[blockIdx.x];
+  } else {
+    for (uint32_t k = threadIdx.x; k < blockIdx.x; k += kBB) before += bc[k];
+    before = block_sum(before, s_w);
+  }
+  const uint32_t i = blockIdx.x * (uint32_t)kBB + threadIdx.x;
+  const uint32_t j = i < m ? (uint32_t)mate[i] : i;
+  const bool keep = i < m && j >= i, merge = i < m && j > i;
+  const uint64_t bk = __ballot(keep), bm = __ballot(merge);
+  const int wave = threadIdx.x / 64, lane = threadIdx.x % 64;
+  if (lane == 0)
+    s_w[wave] = (unsigned long long)__popcll(bk) | ((unsigned long long)__popcll(bm) << 32);
+  __syncthreads();
+  unsigned long long at = before, total = before;
+  for (int q = 0; q < kBB / 64; ++q) {
+    if (q < wave) at += s_w[q];
+    total += s_w[q];
+  }
+  if (last && threadIdx.x == 0) {
+    mc_out[0] = (uint32_t)total;
     mc_out[1] = m;
   }
+  if (!keep) return;
+  const uint64_t lt = lane == 0 ? 0ull : (~0ull >> (64 - lane));
+  const uint32_t pos = (uint32_t)at + (uint32_t)__popcll(bk & lt);
+  uint32_t id = cid[i];
+  float ba[6];
+  for (int k = 0; k < 6; ++k) ba[k] = cbox[(size_t)k * n + i];
+  if (merge) {
+    const uint32_t o = n - m + (uint32_t)(at >> 32) + (uint32_t)__popcll(bm & lt);
+    if (o >= n - 1u || j >= m) {  // more merges than a binary tree of this size has nodes: report
+      atomicOr(err, 4u);
+    } else {
+      const uint32_t b = cid[j];
+      float bb[6];
+      for (int k = 0; k < 6; ++k) bb[k] = cbox[(size_t)k * n + j];
+      SubTree sa = sub_tree(id, half_area(ba), cnt, ncost, dp), sc = sub_tree(b, half_area(bb), cnt, ncost, dp);
+      ploc_node(o, id, b, ba, bb, sa, sc, child, nbox, cnt, dp, dsp);
+      ncost[o] = sa.cost;
+      id = o;
+    }
+  }
+  cid2[pos] = id;
+  for (int k = 0; k < 6; ++k) cbox2[(size_t)k * n + pos] = ba[k];
 }
 
 // The last rounds of the clustering in one workgroup, once at most
-// kFinishMax clusters are left: the same rounds as k_ploc_nn .. k_ploc_scatter
-// (same ranks, same merges, same forced rounds) with the clusters in LDS and
-// barriers between the steps instead of launches.  Then the root's job.
+// kFinishMax clusters are left: the same rounds (same ranks, same merges,
+// same forced rounds) with the clusters and what is known of their subtrees in
+// LDS and barriers between the steps instead of launches.  The barriers order
+// LDS only, since no round reads what another stored.  Then the root's job.
+// A chain of about 25 rounds, each as long as one thread's 32 comparisons.
 constexpr int kFinishThreads = 1024;
 constexpr int kFinishMax = 2048;
 constexpr int kFinishPer = kFinishMax / kFinishThreads;
+constexpr int kFinishSpan = kFinishMax + 2 * kPlocRadius;
+
+__device__ inline void lds_barrier() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
 
 __device__ inline uint32_t block_excl_scan_1024(bool flag, uint32_t* s_w, uint32_t& total) {
   const int lane = threadIdx.x % 64, wave = threadIdx.x / 64;
   const uint64_t bal = __ballot(flag);
   const uint64_t lt = lane == 0 ? 0ull : (~0ull >> (64 - lane));
   if (lane == 0) s_w[wave] = (uint32_t)__popcll(bal);
-  __syncthreads();
+  lds_barrier();
   uint32_t before = 0, t = 0;
   for (int w = 0; w < kFinishThreads / 64; ++w) {
     if (w < wave) before += s_w[w];
     t += s_w[w];
   }
-  __syncthreads();  // s_w is reused by the next scan
   total = t;
   return before + (uint32_t)__popcll(bal & lt);
 }
 
-__global__ __launch_bounds__(kFinishThreads) void k_ploc_finish(const uint32_t* __restrict__ cid_in,
-                                                                const float* __restrict__ cbox_in,
-                                                                const uint32_t* __restrict__ mc,
-                                                                uint2* __restrict__ child, float* __restrict__ nbox,
-                                                                uint32_t* __restrict__ cnt, float* __restrict__ ncost,
-                                                                float* __restrict__ dp, uint32_t* __restrict__ dsp,
-                                                                uint32_t* __restrict__ n_int, uint32_t cap,
-                                                                uint4* __restrict__ jobs, uint32_t* __restrict__ err) {
-  __shared__ float sb[kFinishMax * 6];
-  __shared__ uint32_t sid[kFinishMax];
-  __shared__ int32_t snn[kFinishMax];
-  __shared__ uint32_t s_w[kFinishThreads / 64];
+// Nearest neighbours of the m clusters in LDS, G lanes a cluster.  A place's
+// window reaches past the arrays' ends: kPlocRadius boxes before and after.
+template <int G>
+__device__ inline void finish_nearest(const SharedBoxes& boxes, uint32_t* snn, uint32_t m) {
+  for (uint32_t i = threadIdx.x / G; i < m; i += kFinishThreads / G) {
+    const uint32_t j = ploc_nearest<G>(boxes, (int)i + kPlocRadius, i, m);
+    if (threadIdx.x % G == 0) snn[i] = j;
+  }
+}
+
+__global__ __launch_bounds__(kFinishThreads) void k_ploc_finish(
+    const uint32_t* __restrict__ cid_in, const float* __restrict__ cbox_in, uint32_t n,
+    const uint32_t* __restrict__ mc, uint2* __restrict__ child, float* __restrict__ nbox, uint32_t* __restrict__ cnt,
+    const float* __restrict__ ncost, float* __restrict__ dp, uint32_t* __restrict__ dsp, uint4* __restrict__ jobs,
+    uint32_t* __restrict__ err) {
+  constexpr int kSub = 6;  // words of a SubTree
+  __shared__ float4 s_a[kFinishSpan];
+  __shared__ float2 s_b[kFinishSpan];
+  const SharedBoxes boxes{s_a, s_b};
+  __shared__ uint32_t s_sub[kSub * kFinishMax];
+  __shared__ uint32_t sid[kFinishMax], snn[kFinishMax];
+  __shared__ uint32_t s_w[kFinishPer][kFinishThreads / 64], s_nodes;
   uint32_t m = mc[0], prev = mc[1];
-  if (m > (uint32_t)kFinishMax) {  // the host launches this only at or below kFinishMax clusters
+  if (m > (uint32_t)kFinishMax || m == 0u) {  // the host launches this only at or below kFinishMax clusters
     if (threadIdx.x == 0) atomicOr(err, 16u);
     return;
   }
+  const auto load_sub = [&](uint32_t i) {
+    SubTree s;
+    s.cnt = s_sub[i];
+    s.cost = __uint_as_float(s_sub[kFinishMax + i]);
+    for (int k = 0; k < 4; ++k) s.D[k] = __uint_as_float(s_sub[(2 + k) * kFinishMax + i]);
+    return s;
+  };
+  const auto store = [&](uint32_t i, uint32_t id, const float b[6], const SubTree& s) {
+    sid[i] = id;
+    boxes.put((int)i + kPlocRadius, b);
+    s_sub[i] = s.cnt;
+    s_sub[kFinishMax + i] = __float_as_uint(s.cost);
+    for (int k = 0; k < 4; ++k) s_sub[(2 + k) * kFinishMax + i] = __float_as_uint(s.D[k]);
+  };
   for (int e = 0; e < kFinishPer; ++e) {
     const uint32_t i = threadIdx.x + e * kFinishThreads;
     if (i < m) {
-      sid[i] = cid_in[i];
-      for (int k = 0; k < 6; ++k) sb[6 * i + k] = cbox_in[6 * (size_t)i + k];
+      const uint32_t id = cid_in[i];
+      float b[6];
+      for (int k = 0; k < 6; ++k) b[k] = cbox_in[(size_t)k * n + i];
+      store(i, id, b, sub_tree(id, half_area(b), cnt, ncost, dp));
     }
   }
-  __syncthreads();
+  if (threadIdx.x == 0) s_nodes = n - m;  // inner nodes so far
+  lds_barrier();
   for (int round = 0; m > 1; ++round) {
     if (round >= kPlocMaxRounds) {
       if (threadIdx.x == 0) atomicOr(err, 16u);
       return;
     }
     const bool forced = (uint64_t)m * 100u > (uint64_t)prev * 99u;
-    for (int e = 0; e < kFinishPer; ++e) {  // nearest neighbours
-      const int64_t i = threadIdx.x + e * kFinishThreads;
-      if (i >= (int64_t)m) continue;
-      if (forced) {
-        const int64_t j = i ^ 1;
-        snn[i] = (int32_t)(j < (int64_t)m ? j : i);
-        continue;
-      }
-      const float* bi = sb + 6 * i;
-      float best = INFINITY;
-      uint32_t bd = 0xFFFFFFFFu, blo = 0xFFFFFFFFu;
-      int32_t bj = (int32_t)i;
-      for (int d = -kPlocRadius; d <= kPlocRadius; ++d) {
-        const int64_t j = i + d;
-        if (d == 0 || j < 0 || j >= (int64_t)m) continue;
-        const float* bb = sb + 6 * j;
-        float u[6];
-        for (int k = 0; k < 3; ++k) {
-          u[k] = fminf(bi[k], bb[k]);
-          u[3 + k] = fmaxf(bi[3 + k], bb[3 + k]);
-        }
-        const float a = half_area(u);
-        const uint32_t ad = (uint32_t)(d < 0 ? -d : d), lo = (uint32_t)(d < 0 ? j : i);
-        const bool better =
-            a < best || (a == best && (ad < bd || (ad == bd && ((lo & 1u) < (blo & 1u) ||
-                                                                ((lo & 1u) == (blo & 1u) && lo < blo)))));
-        if (better) {
-          best = a;
-          bd = ad;
-          blo = lo;
-          bj = (int32_t)j;
-        }
-      }
-      snn[i] = bj;
+    if (forced) {
+      for (uint32_t i = threadIdx.x; i < m; i += kFinishThreads) snn[i] = (i ^ 1u) < m ? i ^ 1u : i;
+    } else if (m > kFinishThreads / 8) {
+      finish_nearest<2>(boxes, snn, m);
+    } else {
+      finish_nearest<8>(boxes, snn, m);
     }
-    __syncthreads();
+    lds_barrier();
+    // merges into registers, then the compaction in order: places tid (first) then
+    // tid + kFinishThreads (second)
     bool keep[kFinishPer];
-    for (int e = 0; e < kFinishPer; ++e) {  // merges (in place, as in k_ploc_merge)
-      const int64_t i = threadIdx.x + e * kFinishThreads;
+    uint32_t id_r[kFinishPer];
+    float box_r[kFinishPer][6];
+    SubTree sub_r[kFinishPer];
+    uint32_t pos[kFinishPer], tot[kFinishPer];
+    for (int e = 0; e < kFinishPer; ++e) {
+      const uint32_t i = threadIdx.x + e * kFinishThreads;
       keep[e] = false;
-      if (i >= (int64_t)m) continue;
-      const int32_t j = snn[i];
-      const bool mutual = j != (int32_t)i && j >= 0 && j < (int32_t)m && snn[j] == (int32_t)i;
-      keep[e] = !(mutual && j < (int32_t)i);
-      if (!mutual || j < (int32_t)i) continue;
-      const uint32_t o = atomicAdd(n_int, 1u);
-      if (o >= cap) {
+      if (i >= m) continue;
+      const uint32_t j = snn[i];
+      const bool mutual = j != i && snn[j] == i;
+      keep[e] = !(mutual && j < i);
+      if (!keep[e]) continue;
+      id_r[e] = sid[i];
+      boxes.get((int)i + kPlocRadius, box_r[e]);
+      sub_r[e] = load_sub(i);
+      if (!mutual) continue;
+      const uint32_t o = atomicAdd(&s_nodes, 1u);
+      if (o >= n - 1u) {
         atomicOr(err, 4u);
         continue;
       }
-      const uint32_t a = sid[i], b = sid[j];
-      float u[6], ba[6], bb[6];
-      for (int k = 0; k < 6; ++k) {
-        ba[k] = sb[6 * i + k];
-        bb[k] = sb[6 * j + k];
-      }
-      for (int k = 0; k < 3; ++k) {
-        u[k] = fminf(ba[k], bb[k]);
-        u[3 + k] = fmaxf(ba[3 + k], bb[3 + k]);
-      }
-      for (int k = 0; k < 6; ++k) {
-        nbox[6 * (size_t)o + k] = u[k];
-        sb[6 * i + k] = u[k];
-      }
-      const uint32_t c = ref_count(a, cnt) + ref_count(b, cnt);
-      const float area = half_area(u);
-      const float ca = (a & kLeafRef) ? half_area(ba) : ncost[a], cb = (b & kLeafRef) ? half_area(bb) : ncost[b];
-      const float split = kSahNode * area + ca + cb, leaf = (float)c * area;
-      const bool as_leaf = c <= (uint32_t)kMaxLeafTris && leaf <= split;
-      ncost[o] = as_leaf ? leaf : split;
-      float Da[4], Db[4];
-      dp_of_ref(a, dp, half_area(ba), Da);
-      dp_of_ref(b, dp, half_area(bb), Db);
-      dp_node(o, as_leaf, c, area, Da, Db, dp, dsp);
-      child[o] = make_uint2(a, b);
-      cnt[o] = as_leaf ? (c | kLeafBitCnt) : c;
-      sid[i] = o;
+      float bb[6];
+      boxes.get((int)j + kPlocRadius, bb);
+      const SubTree sc = load_sub(j);
+      ploc_node(o, id_r[e], sid[j], box_r[e], bb, sub_r[e], sc, child, nbox, cnt, dp, dsp);
+      id_r[e] = o;
     }
-    __syncthreads();
-    // compaction in order: places tid (first) then tid + kFinishThreads (second)
-    uint32_t pos[kFinishPer], tot[kFinishPer];
-    for (int e = 0; e < kFinishPer; ++e) pos[e] = block_excl_scan_1024(keep[e], s_w, tot[e]);
-    uint32_t id_r[kFinishPer];
-    float box_r[kFinishPer][6];
-    for (int e = 0; e < kFinishPer; ++e) {
-      const uint32_t i = threadIdx.x + e * kFinishThreads;
-      if (!keep[e]) continue;
-      id_r[e] = sid[i];
-      for (int k = 0; k < 6; ++k) box_r[e][k] = sb[6 * i + k];
-    }
-    __syncthreads();
+    for (int e = 0; e < kFinishPer; ++e) pos[e] = block_excl_scan_1024(keep[e], s_w[e], tot[e]);
     uint32_t base = 0;
-    for (int e = 0; e < kFinishPer; ++e) {
-      if (keep[e]) {
-        const uint32_t q = base + pos[e];
-        sid[q] = id_r[e];
-        for (int k = 0; k < 6; ++k) sb[6 * q + k] = box_r[e][k];
-      }
+    for (int e = 0; e < kFinishPer; ++e) {  // every thread has read its places before the scan's barriers
+      if (keep[e]) store(base + pos[e], id_r[e], box_r[e], sub_r[e]);
       base += tot[e];
     }
-    __syncthreads();
+    lds_barrier();
     prev = m;
     m = base;
   }
@@ -945,7 +1078,7 @@ struct Scratch {
 };
 
 // workspace bytes per triangle of one build: boxes, keys, tree, jobs, clusters (an upper bound)
-constexpr size_t kBuildBytesPerTri = 232;
+constexpr size_t kBuildBytesPerTri = 200;
 
 }  // namespace
 
@@ -961,7 +1094,7 @@ hipError_t gpu_build_bvh4(const float* soup, const uint32_t* prim, const uint32_
   if (builder != kGpuBvhPloc && builder != kGpuBvhLbvh) return hipErrorInvalidValue;
   Scratch S((size_t)n * kBuildBytesPerTri + (size_t)256 * 4 * (size_t)((n + kTile - 1) / kTile) + (64u << 10));
   float *tbox = nullptr, *nbox = nullptr;
-  uint32_t *cb = nullptr, *keyA = nullptr, *valA = nullptr, *keyB = nullptr, *valB = nullptr, *hist = nullptr;
+  uint32_t *cb = nullptr, *keyA = nullptr, *valA = nullptr, *keyB = nullptr, *valB = nullptr, *hist = nullptr, *scan_sums = nullptr;
   uint32_t *counters = nullptr, *cnt = nullptr, *order = nullptr;
   uint2* child = nullptr;
   uint4* jobs[2] = {nullptr, nullptr};
@@ -975,8 +1108,8 @@ hipError_t gpu_build_bvh4(const float* soup, const uint32_t* prim, const uint32_
   PT_TRY(S.get(&keyB, (size_t)n));
   PT_TRY(S.get(&valB, (size_t)n));
   PT_TRY(S.get(&hist, (size_t)256 * nb));
-  // [0] BVH4 nodes, [1] jobs of the next level, [2] largest leaf, [3] error bits, [4] binary nodes,
-  // [5] clusters after a round
+  PT_TRY(S.get(&scan_sums, ((size_t)256 * nb + kScanTile - 1) / kScanTile));
+  // [0] BVH4 nodes, [1] jobs of the next level, [2] largest leaf, [3] error bits
   PT_TRY(S.get(&counters, 8));
   PT_TRY(S.get(&child, (size_t)ni));
   PT_TRY(S.get(&cnt, (size_t)ni));
@@ -989,12 +1122,12 @@ hipError_t gpu_build_bvh4(const float* soup, const uint32_t* prim, const uint32_
   PT_TRY(S.get(&jobs[1], (size_t)n));
 
   hipLaunchKernelGGL(k_init_bounds, dim3(1), dim3(64), 0, st, cb);
-  hipLaunchKernelGGL(k_tri_boxes, dim3(grid_of(n)), dim3(kBB), 0, st, soup, n, tbox, cb);
+  hipLaunchKernelGGL(k_tri_boxes, dim3(std::min(grid_of(n), kBoundsGrid)), dim3(kBB), 0, st, soup, n, tbox, cb);
   hipLaunchKernelGGL(k_morton, dim3(grid_of(n)), dim3(kBB), 0, st, tbox, n, cb, keyA, valA);
   for (int pass = 0; pass < 4; ++pass) {  // codes have 30 bits
     const int shift = 8 * pass;
     hipLaunchKernelGGL(k_radix_hist, dim3(nb), dim3(kBB), 0, st, keyA, n, shift, hist, nb);
-    hipLaunchKernelGGL(k_scan_excl, dim3(1), dim3(1024), 0, st, hist, (int64_t)256 * nb);
+    launch_scan(hist, (int64_t)256 * nb, scan_sums, st);
     hipLaunchKernelGGL(k_radix_scatter, dim3(nb), dim3(kBB), 0, st, keyA, valA, keyB, valB, n, shift, hist, nb);
     std::swap(keyA, keyB);
     std::swap(valA, valB);
@@ -1015,18 +1148,18 @@ hipError_t gpu_build_bvh4(const float* soup, const uint32_t* prim, const uint32_
     const uint4 root = make_uint4(0u, 0u, 0u, 0u);
     PT_TRY(hipMemcpyAsync(jobs[0], &root, sizeof(root), hipMemcpyHostToDevice, st));
   } else if (n > 1) {
-    uint32_t *cid[2] = {nullptr, nullptr}, *keep = nullptr, *bc = nullptr, *mc = nullptr;
-    float* cbox[2] = {nullptr, nullptr};
-    float* ncost = nullptr;
-    int32_t* nn = nullptr;
+    uint32_t *cid[2] = {nullptr, nullptr}, *mc = nullptr;
+    float *cbox[2] = {nullptr, nullptr}, *ncost = nullptr;
+    int32_t* mate = nullptr;
+    unsigned long long *bc = nullptr, *bc_sums = nullptr;
     const int64_t nblk = (n + kBB - 1) / kBB;
     for (int k = 0; k < 2; ++k) {
       PT_TRY(S.get(&cid[k], (size_t)n));
       PT_TRY(S.get(&cbox[k], (size_t)n * 6));
     }
-    PT_TRY(S.get(&keep, (size_t)n));
     PT_TRY(S.get(&bc, (size_t)nblk));
-    PT_TRY(S.get(&nn, (size_t)n));
+    PT_TRY(S.get(&bc_sums, (size_t)(nblk + kScanTile - 1) / kScanTile));
+    PT_TRY(S.get(&mate, (size_t)n));
     PT_TRY(S.get(&ncost, (size_t)ni));
     PT_TRY(S.get(&mc, 4));  // cluster counts: [0..1] read by even rounds, [2..3] by odd rounds
     hipLaunchKernelGGL(k_ploc_init, dim3(grid_of(n)), dim3(kBB), 0, st, valA, tbox, n, cid[0], cbox[0]);
@@ -1039,16 +1172,15 @@ hipError_t gpu_build_bvh4(const float* soup, const uint32_t* prim, const uint32_
     while (m > (uint32_t)kFinishMax) {
       if (rounds >= kPlocMaxRounds) return hipErrorUnknown;
       const int blocks = (int)((m + kBB - 1) / kBB);
+      const bool scanned = blocks > kPlocSumBlocks;
       for (int r = 0; r < kPlocBatch; ++r, ++rounds) {
         const uint32_t* mc_in = mc + 2 * (rounds & 1);
         uint32_t* mc_out = mc + 2 * ((rounds & 1) ^ 1);
-        hipLaunchKernelGGL(k_ploc_nn, dim3(blocks), dim3(kBB), 0, st, cbox[cur], mc_in, nn);
-        hipLaunchKernelGGL(k_ploc_merge, dim3(grid_of(m)), dim3(kBB), 0, st, cid[cur], cbox[cur], mc_in, nn, child,
-                           nbox, cnt, ncost, dp, dsp, counters + 4, (uint32_t)ni, keep, counters + 3);
-        hipLaunchKernelGGL(k_ploc_count, dim3(blocks), dim3(kBB), 0, st, keep, mc_in, bc);
-        hipLaunchKernelGGL(k_scan_excl, dim3(1), dim3(1024), 0, st, bc, (int64_t)blocks);
-        hipLaunchKernelGGL(k_ploc_scatter, dim3(blocks), dim3(kBB), 0, st, cid[cur], cbox[cur], keep, mc_in, bc,
-                           cid[cur ^ 1], cbox[cur ^ 1], mc_out);
+        hipLaunchKernelGGL(k_ploc_nn, dim3(blocks), dim3(kNnThreads), 0, st, cbox[cur], (uint32_t)n, mc_in, mate, bc);
+        if (scanned) launch_scan(bc, (int64_t)blocks, bc_sums, st);
+        hipLaunchKernelGGL(k_ploc_merge, dim3(blocks), dim3(kBB), 0, st, cid[cur], cbox[cur], (uint32_t)n, mc_in, mate,
+                           bc, scanned, child, nbox, cnt, ncost, dp, dsp, cid[cur ^ 1], cbox[cur ^ 1], mc_out,
+                           counters + 3);
         cur ^= 1;
       }
       PT_TRY(hipGetLastError());
@@ -1058,9 +1190,8 @@ hipError_t gpu_build_bvh4(const float* soup, const uint32_t* prim, const uint32_
       m = m_host[0];
     }
     // the last rounds (at most kFinishMax clusters) in one workgroup; it also writes the root's job
-    hipLaunchKernelGGL(k_ploc_finish, dim3(1), dim3(kFinishThreads), 0, st, cid[cur], cbox[cur],
-                       mc + 2 * (rounds & 1), child, nbox, cnt, ncost, dp, dsp, counters + 4, (uint32_t)ni, jobs[0],
-                       counters + 3);
+    hipLaunchKernelGGL(k_ploc_finish, dim3(1), dim3(kFinishThreads), 0, st, cid[cur], cbox[cur], (uint32_t)n,
+                       mc + 2 * (rounds & 1), child, nbox, cnt, ncost, dp, dsp, jobs[0], counters + 3);
   } else {
     const uint4 root = make_uint4(kLeafRef, 0u, 0u, 0u);
     PT_TRY(hipMemcpyAsync(jobs[0], &root, sizeof(root), hipMemcpyHostToDevice, st));
