@@ -423,8 +423,8 @@ typedef struct pt_bvh_info {
 /* The scene's mesh-level BVH (either builder): node and triangle counts,
  * depth, largest leaf, SAH cost (host builds; 0 for device builds),
  * build_ms from the triangle soup in host memory to the BVH in the builder's
- * memory (device builds: soup upload included; two-level: summed over the
- * meshes), and the traversal stack capacity.  Errors: STATE without a BVH. */
+ * memory (device builds: from the meshes in host memory, their copy and
+ * checks included; two-level: summed over the meshes), and the traversal stack capacity.  Errors: STATE without a BVH. */
 pt_status pt_scene_bvh_info(pt_scene* scene, pt_bvh_info* info);
 /* Copy the scene's mesh-level BVH to host memory: nodes (n_nodes * 128
  * bytes, root at 0; two-level scenes: the meshes' trees concatenated) and

@@ -106,8 +106,6 @@ struct pt_scene {
   bool bvh_on_device = false;
   float tmin = 0.0f;
   int32_t max_mat_id = -1;
-  std::vector<float> host_tri_verts;  // [n][9] world space, prim order (single level)
-  std::vector<int32_t> host_tri_mat;  // [n], prim order (single level)
   // two-level hierarchy
   bool two_level = false;
   DevBuf insts, tlas_items, light_map, mesh_tri_first, mesh_tri_count;
@@ -237,18 +235,42 @@ void push_light(std::vector<LightTmp>& list, const double* v, const pt_openpbr_m
 pt_status ensure_lights(pt_scene* s) {
   if (!s->lights_dirty) return PT_OK;
   std::vector<LightTmp> list;
-  std::vector<int32_t> tri_light(1, -1), lmap(1, -1);
+  std::vector<int32_t> lmap(1, -1);
+  const int64_t n_tri = s->two_level ? 1 : s->n_tris;
+  PT_HIP(s->tri_light.alloc((size_t)n_tri * sizeof(int32_t)));
   if (!s->two_level) {
-    const int64_t n = s->n_tris;
-    tri_light.assign((size_t)std::max<int64_t>(n, 1), -1);
-    for (int64_t i = 0; i < n; ++i) {
-      const pt_openpbr_material& m = s->host_mats[(size_t)s->host_tri_mat[(size_t)i]];
-      if (!mat_emits(m)) continue;
-      const float* v = &s->host_tri_verts[9 * (size_t)i];
-      double vd[9];
-      for (int k = 0; k < 9; ++k) vd[k] = v[k];
-      tri_light[(size_t)i] = (int32_t)list.size();
-      push_light(list, vd, m);
+    // the emissive triangles come from the device's records, in primitive order
+    std::vector<uint32_t> emits(s->host_mats.size());
+    bool any = false;
+    for (size_t k = 0; k < emits.size(); ++k) any |= (emits[k] = mat_emits(s->host_mats[k]) ? 1u : 0u) != 0u;
+    uint32_t n_list = 0;
+    if (any) {
+      DevBuf demits, doff, dsums, dlist;
+      PT_HIP(upload(demits, emits.data(), emits.size() * sizeof(uint32_t), s->stream));
+      PT_HIP(doff.alloc((size_t)(n_tri + 1) * sizeof(uint32_t)));
+      PT_HIP(dsums.alloc(gpu_count_lights_scratch(n_tri) * sizeof(uint32_t)));
+      PT_HIP(gpu_count_lights(s->tris.as<TriRec>(), n_tri, demits.as<uint32_t>(), (uint32_t)emits.size(),
+                              doff.as<uint32_t>(), dsums.as<uint32_t>(), s->stream));
+      PT_HIP(hipMemcpyAsync(&n_list, doff.as<uint32_t>() + n_tri, sizeof(n_list), hipMemcpyDeviceToHost, s->stream));
+      PT_HIP(hipStreamSynchronize(s->stream));
+      std::vector<uint32_t> words((size_t)n_list * kLightWords);
+      PT_HIP(dlist.alloc(words.size() * sizeof(uint32_t)));
+      PT_HIP(gpu_list_lights(s->tris.as<TriRec>(), n_tri, doff.as<uint32_t>(), s->tri_light.as<int32_t>(),
+                             dlist.as<uint32_t>(), s->stream));
+      if (n_list)
+        PT_HIP(hipMemcpyAsync(words.data(), dlist.p, words.size() * sizeof(uint32_t), hipMemcpyDeviceToHost, s->stream));
+      PT_HIP(hipStreamSynchronize(s->stream));
+      list.reserve(n_list);
+      for (size_t i = 0; i < n_list; ++i) {
+        const uint32_t* w = &words[i * kLightWords];
+        double vd[9];
+        for (int k = 0; k < 9; ++k) {
+          float f;
+          std::memcpy(&f, &w[k], sizeof(f));
+          vd[k] = f;
+        }
+        push_light(list, vd, s->host_mats[w[9]]);
+      }
     }
   } else {
     // lights in instance order, then primitive order; each instance with emitters gets a
@@ -280,6 +302,7 @@ pt_status ensure_lights(pt_scene* s) {
       }
     }
     if (lmap.empty()) lmap.push_back(-1);
+    PT_HIP(gpu_list_lights(nullptr, n_tri, nullptr, s->tri_light.as<int32_t>(), nullptr, s->stream));
   }
   double wsum = 0.0;
   for (auto& t : list) wsum += t.w;
@@ -299,14 +322,13 @@ pt_status ensure_lights(pt_scene* s) {
   if (has_tri) cdf[list.size()] = 1.0f;
   if (!has_tri) {
     lt.clear();
-    std::fill(tri_light.begin(), tri_light.end(), -1);
+    PT_HIP(gpu_list_lights(s->tris.as<TriRec>(), n_tri, nullptr, s->tri_light.as<int32_t>(), nullptr, s->stream));
     std::fill(lmap.begin(), lmap.end(), -1);
   }
   s->n_lights = (int32_t)lt.size();
   s->p_env = (float)p_env;
   PT_HIP(upload(s->lights, lt.data(), lt.size() * sizeof(LightTri), s->stream));
   PT_HIP(upload(s->light_cdf, cdf.data(), cdf.size() * sizeof(float), s->stream));
-  PT_HIP(upload(s->tri_light, tri_light.data(), tri_light.size() * sizeof(int32_t), s->stream));
   PT_HIP(upload(s->light_map, lmap.data(), lmap.size() * sizeof(int32_t), s->stream));
   if (s->two_level)
     PT_HIP(upload(s->insts, s->host_insts.data(), s->host_insts.size() * sizeof(InstRec), s->stream));
@@ -1450,8 +1472,6 @@ pt_status build_two_level(pt_scene* s, const pt_mesh* meshes, int32_t n_meshes, 
   s->bvh_build_ms = T.build_ms;
   s->bvh_on_device = on_device;
   s->max_mat_id = T.max_mat;
-  s->host_tri_verts.clear();
-  s->host_tri_mat.clear();
   s->host_insts.swap(T.insts);
   s->host_mesh_verts.swap(T.mverts);
   s->host_mesh_mat.swap(T.mmat);
@@ -1461,9 +1481,10 @@ pt_status build_two_level(pt_scene* s, const pt_mesh* meshes, int32_t n_meshes, 
   return PT_OK;
 }
 
-// Validation shared by the host and device builds (checked before any state change).
+// Validation shared by the host and device builds (checked before any state change).  contents false:
+// only the sizes and pointers; the caller checks vertices, indices and material ids.
 pt_status check_build_args(const pt_mesh* meshes, int32_t n_meshes, const pt_instance* instances,
-                           int32_t n_instances, int64_t* total_out) {
+                           int32_t n_instances, bool contents, int64_t* total_out) {
   if (!meshes || n_meshes <= 0) return fail(PT_ERR_INVALID_ARG, "meshes must be non-NULL with n_meshes > 0");
   if (n_instances < 0 || (n_instances > 0 && !instances)) return fail(PT_ERR_INVALID_ARG, "bad instances");
   for (int i = 0; i < n_instances; ++i) {
@@ -1481,6 +1502,8 @@ pt_status check_build_args(const pt_mesh* meshes, int32_t n_meshes, const pt_ins
       return fail(PT_ERR_INVALID_ARG, "mesh %d: NULL arrays or empty counts", i);
     if (!m.material_ids && n_instances == 0)
       return fail(PT_ERR_INVALID_ARG, "mesh %d: material_ids is NULL and nothing overrides it", i);
+    total += m.n_triangles;
+    if (!contents) continue;
     if (!finite_all(m.vertices, (size_t)m.n_vertices * 3)) return fail(PT_ERR_INVALID_ARG, "mesh %d: non-finite vertex", i);
     for (int64_t t = 0; t < m.n_triangles * 3; ++t)
       if (m.indices[t] < 0 || m.indices[t] >= m.n_vertices)
@@ -1488,56 +1511,123 @@ pt_status check_build_args(const pt_mesh* meshes, int32_t n_meshes, const pt_ins
     if (m.material_ids)
       for (int64_t t = 0; t < m.n_triangles; ++t)
         if (m.material_ids[t] < 0) return fail(PT_ERR_INVALID_ARG, "mesh %d: negative material id", i);
-    total += m.n_triangles;
   }
   if (n_instances == 0 && total >= (int64_t)kLeafFirstMask) return fail(PT_ERR_INVALID_ARG, "too many triangles");
   *total_out = total;
   return PT_OK;
 }
 
-// pt_build_bvh (on_device false: host binned-SAH builder) and pt_build_bvh_gpu (device linear BVH).
+// Meshes of a build on the device: copied there as they are and gathered into
+// soup by a kernel that also checks them.  On the host the same work (checks,
+// soup, box, page faults of 57 MB of vectors) took 19 ms for 1.31M triangles;
+// the copy is bound by the host link (29 MB, 0.9 ms).  Many small meshes are
+// joined on the host first: three copies and two launches a mesh take as long
+// as its host work at about 2000 triangles.
+struct DeviceSoup {
+  DevBuf mem;
+  float* soup = nullptr;
+  uint32_t* mat = nullptr;
+  uint32_t info[kGatherWords] = {};
+};
+
+hipError_t gather_on_device(pt_scene* s, const pt_mesh* meshes, int32_t n_meshes, int64_t total, DeviceSoup& out) {
+  int64_t nv = 0;
+  for (int i = 0; i < n_meshes; ++i) nv += meshes[i].n_vertices;
+  const bool join = n_meshes > 1 && total < 2000 * (int64_t)n_meshes && nv <= INT32_MAX;
+  const auto up = [](size_t b) { return (b + 255) & ~size_t(255); };
+  const size_t b_soup = up((size_t)total * 9 * sizeof(float)), b_mat = up((size_t)total * sizeof(uint32_t)),
+               b_idx = up((size_t)total * 3 * sizeof(int32_t)), b_vert = up((size_t)nv * 3 * sizeof(float));
+  hipError_t e = out.mem.alloc(b_soup + b_mat + b_idx + b_vert + 256);
+  if (e != hipSuccess) return e;
+  char* base = out.mem.as<char>();
+  out.soup = reinterpret_cast<float*>(base);
+  out.mat = reinterpret_cast<uint32_t*>(base + b_soup);
+  int32_t* idx = reinterpret_cast<int32_t*>(base + b_soup + b_mat);
+  float* vert = reinterpret_cast<float*>(base + b_soup + b_mat + b_idx);
+  uint32_t* info = reinterpret_cast<uint32_t*>(base + b_soup + b_mat + b_idx + b_vert);
+  e = gpu_gather_init(info, s->stream);
+  std::vector<float> jv;
+  std::vector<int32_t> ji, jm;
+  const auto mesh = [&](const float* v, int64_t n_v, const int32_t* ix, const int32_t* m, int64_t n, int64_t v0,
+                        int64_t t0) {
+    if (e == hipSuccess)
+      e = hipMemcpyAsync(vert + 3 * v0, v, (size_t)n_v * 3 * sizeof(float), hipMemcpyHostToDevice, s->stream);
+    if (e == hipSuccess)
+      e = hipMemcpyAsync(idx + 3 * t0, ix, (size_t)n * 3 * sizeof(int32_t), hipMemcpyHostToDevice, s->stream);
+    if (e == hipSuccess)
+      e = hipMemcpyAsync(out.mat + t0, m, (size_t)n * sizeof(int32_t), hipMemcpyHostToDevice, s->stream);
+    if (e == hipSuccess)
+      e = gpu_gather_mesh(vert + 3 * v0, n_v, idx + 3 * t0, out.mat + t0, n, out.soup + 9 * t0, info, s->stream);
+  };
+  if (join) {  // indices outside their own mesh stay outside the joined one
+    jv.reserve((size_t)nv * 3);
+    ji.reserve((size_t)total * 3);
+    jm.reserve((size_t)total);
+    for (int i = 0; i < n_meshes; ++i) {
+      const pt_mesh& m = meshes[i];
+      const int64_t v0 = (int64_t)(jv.size() / 3);
+      jv.insert(jv.end(), m.vertices, m.vertices + 3 * m.n_vertices);
+      for (int64_t k = 0; k < 3 * m.n_triangles; ++k) {
+        const int64_t q = m.indices[k];
+        ji.push_back(q < 0 || q >= m.n_vertices ? -1 : (int32_t)(v0 + q));
+      }
+      jm.insert(jm.end(), m.material_ids, m.material_ids + m.n_triangles);
+    }
+    mesh(jv.data(), nv, ji.data(), jm.data(), total, 0, 0);
+  } else {
+    int64_t v0 = 0, t0 = 0;
+    for (int i = 0; i < n_meshes; ++i) {
+      const pt_mesh& m = meshes[i];
+      mesh(m.vertices, m.n_vertices, m.indices, m.material_ids, m.n_triangles, v0, t0);
+      v0 += m.n_vertices;
+      t0 += m.n_triangles;
+    }
+  }
+  if (e == hipSuccess) e = hipMemcpyAsync(out.info, info, sizeof(out.info), hipMemcpyDeviceToHost, s->stream);
+  const hipError_t e2 = hipStreamSynchronize(s->stream);  // the copies read the caller's and joined arrays
+  return e != hipSuccess ? e : e2;
+}
+
+// pt_build_bvh (on_device false: host binned-SAH builder) and pt_build_bvh_gpu (device builders).
 pt_status build_bvh_any(pt_scene* s, const pt_mesh* meshes, int32_t n_meshes, const pt_instance* instances,
                         int32_t n_instances, bool on_device) {
   pt_status r = check_scene(s);
   if (r) return r;
   int64_t total = 0;
-  if ((r = check_build_args(meshes, n_meshes, instances, n_instances, &total))) return r;
+  const bool gather = on_device && n_instances == 0;
+  // a device build checks the contents where it gathers them; the host's check then names what it found
+  r = check_build_args(meshes, n_meshes, instances, n_instances, !gather, &total);
+  const auto named = [&](pt_status other) {
+    const pt_status c = check_build_args(meshes, n_meshes, instances, n_instances, true, &total);
+    return c ? c : other;
+  };
+  if (r) return gather ? named(r) : r;
   if (n_instances > 0) return build_two_level(s, meshes, n_meshes, instances, n_instances, on_device);
-  std::vector<float> verts((size_t)total * 9);
-  std::vector<int32_t> mat((size_t)total);
-  std::vector<uint32_t> prim((size_t)total), matu((size_t)total);
-  int64_t t = 0;
-  int32_t max_mat = -1;
-  for (int i = 0; i < n_meshes; ++i) {
-    const pt_mesh& m = meshes[i];
-    for (int64_t k = 0; k < m.n_triangles; ++k, ++t) {
-      for (int v = 0; v < 3; ++v) {
-        int32_t vi = m.indices[3 * k + v];
-        for (int c = 0; c < 3; ++c) verts[9 * (size_t)t + 3 * v + c] = m.vertices[3 * (size_t)vi + c];
-      }
-      mat[(size_t)t] = m.material_ids[k];
-      matu[(size_t)t] = (uint32_t)m.material_ids[k];
-      prim[(size_t)t] = (uint32_t)t;
-      max_mat = std::max(max_mat, m.material_ids[k]);
-    }
-  }
-  r = set_device(s);
-  if (r) return r;
   int64_t n_nodes = 0;
   int depth = 0, max_leaf = 0;
+  int32_t max_mat = -1;
   double sah = 0.0, build_ms = 0.0;
+  double lo[3] = {INFINITY, INFINITY, INFINITY}, hi[3] = {-INFINITY, -INFINITY, -INFINITY};
   if (on_device) {
-    // the soup goes up once; nodes and triangle records are written in place
+    r = set_device(s);
+    if (r) return named(r);
     auto t0 = std::chrono::steady_clock::now();
-    DevBuf dsoup, dprim, dmat;
-    PT_HIP(upload(dsoup, verts.data(), verts.size() * sizeof(float), s->stream));
-    PT_HIP(upload(dprim, prim.data(), prim.size() * sizeof(uint32_t), s->stream));
-    PT_HIP(upload(dmat, matu.data(), matu.size() * sizeof(uint32_t), s->stream));
+    DeviceSoup soup;
+    hipError_t e = gather_on_device(s, meshes, n_meshes, total, soup);
+    if (e != hipSuccess)
+      return named(fail(PT_ERR_DEVICE, "copy of the meshes to the device failed: %s", hipGetErrorString(e)));
+    if (soup.info[0]) return named(fail(PT_ERR_DEVICE, "the device's check of the meshes failed"));
+    max_mat = (int32_t)soup.info[1];
+    for (int k = 0; k < 3; ++k) {
+      lo[k] = gpu_ordered_float(soup.info[2 + k]);
+      hi[k] = gpu_ordered_float(soup.info[5 + k]);
+    }
+    // nodes and triangle records are written in place
     PT_HIP(s->nodes.alloc((size_t)std::max<int64_t>(1, total - 1) * sizeof(BVHNode)));
     PT_HIP(s->tris.alloc((size_t)total * sizeof(TriRec)));
     GpuBvhStats st{};
-    hipError_t e = gpu_build_bvh4(dsoup.as<float>(), dprim.as<uint32_t>(), dmat.as<uint32_t>(), total,
-                                  s->nodes.as<BVHNode>(), s->tris.as<TriRec>(), s->stream, &st, s->gpu_bvh_builder);
+    e = gpu_build_bvh4(soup.soup, nullptr, soup.mat, total, s->nodes.as<BVHNode>(), s->tris.as<TriRec>(), s->stream,
+                       &st, s->gpu_bvh_builder);
     if (e != hipSuccess) {
       s->has_bvh = false;  // the scene's buffers were overwritten
       return fail(PT_ERR_DEVICE, "device BVH build failed: %s", hipGetErrorString(e));
@@ -1547,6 +1637,28 @@ pt_status build_bvh_any(pt_scene* s, const pt_mesh* meshes, int32_t n_meshes, co
     max_leaf = st.max_leaf;
     build_ms = std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t0).count();
   } else {
+    std::vector<float> verts((size_t)total * 9);
+    std::vector<uint32_t> prim((size_t)total), matu((size_t)total);
+    int64_t t = 0;
+    for (int i = 0; i < n_meshes; ++i) {
+      const pt_mesh& m = meshes[i];
+      for (int64_t k = 0; k < m.n_triangles; ++k, ++t) {
+        for (int v = 0; v < 3; ++v) {
+          int32_t vi = m.indices[3 * k + v];
+          for (int c = 0; c < 3; ++c) verts[9 * (size_t)t + 3 * v + c] = m.vertices[3 * (size_t)vi + c];
+        }
+        matu[(size_t)t] = (uint32_t)m.material_ids[k];
+        prim[(size_t)t] = (uint32_t)t;
+        max_mat = std::max(max_mat, m.material_ids[k]);
+      }
+    }
+    for (size_t q = 0; q < verts.size(); q += 3)
+      for (int k = 0; k < 3; ++k) {
+        lo[k] = std::min(lo[k], (double)verts[q + k]);
+        hi[k] = std::max(hi[k], (double)verts[q + k]);
+      }
+    r = set_device(s);
+    if (r) return r;
     Bvh4 bvh;
     std::string err;
     if (!build_bvh4(verts.data(), prim.data(), matu.data(), total, bvh, err)) return fail(PT_ERR_INVALID_ARG, "%s", err.c_str());
@@ -1559,12 +1671,6 @@ pt_status build_bvh_any(pt_scene* s, const pt_mesh* meshes, int32_t n_meshes, co
     sah = bvh.sah_cost;
     build_ms = bvh.build_ms;
   }
-  double lo[3] = {INFINITY, INFINITY, INFINITY}, hi[3] = {-INFINITY, -INFINITY, -INFINITY};
-  for (size_t q = 0; q < verts.size(); q += 3)
-    for (int k = 0; k < 3; ++k) {
-      lo[k] = std::min(lo[k], (double)verts[q + k]);
-      hi[k] = std::max(hi[k], (double)verts[q + k]);
-    }
   // t_min from the float box of the triangles (as the host builder reports it)
   double dx = (double)(float)hi[0] - (float)lo[0], dy = (double)(float)hi[1] - (float)lo[1],
          dz = (double)(float)hi[2] - (float)lo[2];
@@ -1581,8 +1687,6 @@ pt_status build_bvh_any(pt_scene* s, const pt_mesh* meshes, int32_t n_meshes, co
   s->bvh_build_ms = build_ms;
   s->bvh_on_device = on_device;
   s->max_mat_id = max_mat;
-  s->host_tri_verts.swap(verts);
-  s->host_tri_mat.swap(mat);
   s->host_insts.clear();
   s->host_mesh_verts.clear();
   s->host_mesh_mat.clear();

@@ -1037,10 +1037,99 @@ __global__ __launch_bounds__(kBB) void k_sorted_tris(const float* __restrict__ s
     const uint32_t t = val[order[i]];
     const float* p = soup + 9 * (size_t)t;
     TriRec r;
-    r.a = make_float4(p[0], p[1], p[2], __uint_as_float(prim[t]));
+    r.a = make_float4(p[0], p[1], p[2], __uint_as_float(prim ? prim[t] : t));
     r.b = make_float4(p[3], p[4], p[5], __uint_as_float(mat[t]));
     r.c = make_float4(p[6], p[7], p[8], 0.0f);
     tris[i] = r;
+  }
+}
+
+// A mesh's triangles as soup, its contents checked on the way: a bad index
+// reads nothing and reports.  12 bytes of indices in and 36 of soup out per
+// triangle (the vertices mostly stay in L2).
+__global__ void k_gather_init(uint32_t* info) {
+  if (threadIdx.x < (unsigned)kGatherWords)
+    info[threadIdx.x] = threadIdx.x >= 2u && threadIdx.x < 5u ? 0xFFFFFFFFu : 0u;
+}
+
+__global__ __launch_bounds__(kBB) void k_check_vertices(const float* __restrict__ v, int64_t n,
+                                                        uint32_t* __restrict__ info) {
+  bool bad = false;
+  for (int64_t i = blockIdx.x * (int64_t)kBB + threadIdx.x; i < n; i += (int64_t)gridDim.x * kBB)
+    bad |= (__float_as_uint(v[i]) & 0x7F800000u) == 0x7F800000u;
+  if (bad) atomicOr(info, 1u);
+}
+
+__global__ __launch_bounds__(kBB) void k_gather_soup(const float* __restrict__ v, int64_t nv,
+                                                     const int32_t* __restrict__ idx, const uint32_t* __restrict__ mat,
+                                                     int64_t n, float* __restrict__ soup, uint32_t* __restrict__ info) {
+  __shared__ uint32_t red[8];
+  if (threadIdx.x < 8) red[threadIdx.x] = threadIdx.x >= 2 && threadIdx.x < 5 ? 0xFFFFFFFFu : 0u;
+  __syncthreads();
+  uint32_t bad = 0u, top = 0u, lo[3] = {0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu}, hi[3] = {0u, 0u, 0u};
+  for (int64_t i = blockIdx.x * (int64_t)kBB + threadIdx.x; i < n; i += (int64_t)gridDim.x * kBB) {
+    const uint32_t m = mat[i];
+    if (m & 0x80000000u) bad = 1u;
+    else top = m > top ? m : top;
+    for (int c = 0; c < 3; ++c) {
+      const int64_t q = idx[3 * i + c];
+      if (q < 0 || q >= nv) {
+        bad = 1u;
+        continue;
+      }
+      for (int k = 0; k < 3; ++k) {
+        const float x = v[3 * q + k];
+        soup[9 * i + 3 * c + k] = x;
+        const uint32_t u = f2ord(x + 0.0f);  // -0 as 0
+        lo[k] = u < lo[k] ? u : lo[k];
+        hi[k] = u > hi[k] ? u : hi[k];
+      }
+    }
+  }
+  if (bad) atomicOr(&red[0], 1u);
+  atomicMax(&red[1], top);
+  for (int k = 0; k < 3; ++k) {
+    atomicMin(&red[2 + k], lo[k]);
+    atomicMax(&red[5 + k], hi[k]);
+  }
+  __syncthreads();
+  if (threadIdx.x == 0 && red[0]) atomicOr(&info[0], 1u);
+  if (threadIdx.x >= 2 && threadIdx.x < 5) atomicMin(&info[threadIdx.x], red[threadIdx.x]);
+  if (threadIdx.x == 1 || (threadIdx.x >= 5 && threadIdx.x < 8)) atomicMax(&info[threadIdx.x], red[threadIdx.x]);
+}
+
+// Emissive triangles: a flag per primitive, scanned by the caller into places.
+__global__ __launch_bounds__(kBB) void k_light_flags(const TriRec* __restrict__ tris, int64_t n,
+                                                     const uint32_t* __restrict__ emits, uint32_t n_mats,
+                                                     uint32_t* __restrict__ off) {
+  for (int64_t i = blockIdx.x * (int64_t)kBB + threadIdx.x; i <= n; i += (int64_t)gridDim.x * kBB) {
+    if (i == n) {
+      off[n] = 0u;
+    } else {
+      const uint32_t prim = __float_as_uint(tris[i].a.w), m = __float_as_uint(tris[i].b.w);
+      if (prim < (uint64_t)n) off[prim] = m < n_mats && emits[m] ? 1u : 0u;
+    }
+  }
+}
+
+__global__ __launch_bounds__(kBB) void k_light_list(const TriRec* __restrict__ tris, int64_t n,
+                                                    const uint32_t* __restrict__ off, int32_t* __restrict__ tri_light,
+                                                    uint32_t* __restrict__ list) {
+  for (int64_t i = blockIdx.x * (int64_t)kBB + threadIdx.x; i < n; i += (int64_t)gridDim.x * kBB) {
+    if (!off) {
+      tri_light[i] = -1;
+      continue;
+    }
+    const TriRec r = tris[i];
+    const uint32_t prim = __float_as_uint(r.a.w);
+    if (prim >= (uint64_t)n) continue;
+    const uint32_t at = off[prim];
+    const bool light = off[prim + 1] != at;
+    tri_light[prim] = light ? (int32_t)at : -1;
+    if (!light) continue;
+    const float v[9] = {r.a.x, r.a.y, r.a.z, r.b.x, r.b.y, r.b.z, r.c.x, r.c.y, r.c.z};
+    for (int k = 0; k < 9; ++k) list[(size_t)kLightWords * at + k] = __float_as_uint(v[k]);
+    list[(size_t)kLightWords * at + 9] = __float_as_uint(r.b.w);
   }
 }
 
@@ -1228,6 +1317,42 @@ hipError_t gpu_build_bvh4(const float* soup, const uint32_t* prim, const uint32_
   stats->n_nodes = fin[0];
   stats->max_leaf = (int)fin[2];
   stats->depth = levels + 1;  // node levels, plus the leaves under the deepest nodes
+  return hipGetLastError();
+}
+
+float gpu_ordered_float(uint32_t u) {
+  u = (u & 0x80000000u) ? (u & 0x7FFFFFFFu) : ~u;
+  float f;
+  __builtin_memcpy(&f, &u, sizeof(f));
+  return f;
+}
+
+hipError_t gpu_gather_init(uint32_t* info, hipStream_t st) {
+  hipLaunchKernelGGL(k_gather_init, dim3(1), dim3(64), 0, st, info);
+  return hipGetLastError();
+}
+
+hipError_t gpu_gather_mesh(const float* vertices, int64_t n_vertices, const int32_t* indices, const uint32_t* mat,
+                           int64_t n, float* soup, uint32_t* info, hipStream_t st) {
+  hipLaunchKernelGGL(k_check_vertices, dim3(std::min(grid_of(3 * n_vertices), kBoundsGrid)), dim3(kBB), 0, st,
+                     vertices, 3 * n_vertices, info);
+  hipLaunchKernelGGL(k_gather_soup, dim3(std::min(grid_of(n), kBoundsGrid)), dim3(kBB), 0, st, vertices, n_vertices,
+                     indices, mat, n, soup, info);
+  return hipGetLastError();
+}
+
+size_t gpu_count_lights_scratch(int64_t n) { return (size_t)((n + 1 + kScanTile - 1) / kScanTile); }
+
+hipError_t gpu_count_lights(const TriRec* tris, int64_t n, const uint32_t* emits, uint32_t n_mats, uint32_t* off,
+                            uint32_t* sums, hipStream_t st) {
+  hipLaunchKernelGGL(k_light_flags, dim3(grid_of(n + 1)), dim3(kBB), 0, st, tris, n, emits, n_mats, off);
+  launch_scan(off, n + 1, sums, st);
+  return hipGetLastError();
+}
+
+hipError_t gpu_list_lights(const TriRec* tris, int64_t n, const uint32_t* off, int32_t* tri_light, uint32_t* list,
+                           hipStream_t st) {
+  hipLaunchKernelGGL(k_light_list, dim3(grid_of(n)), dim3(kBB), 0, st, tris, n, off, tri_light, list);
   return hipGetLastError();
 }
 

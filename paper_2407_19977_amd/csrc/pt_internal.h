@@ -236,12 +236,32 @@ struct GpuBvhStats {
   int depth;        // nodes on the longest root-to-leaf path, counting the leaf level
   int max_leaf;     // largest leaf (triangles)
 };
-// soup [n][9] floats, prim / mat [n] (device); nodes (device, room for max(1, n - 1) nodes; node 0 is
+// soup [n][9] floats, prim (nullable: triangle i is primitive i) / mat [n] (device); nodes (device, room for max(1, n - 1) nodes; node 0 is
 // the root) and tris (device, [n], leaf order) are written; synchronises the stream.
 // builder: kGpuBvhPloc (locally-ordered clustering) or kGpuBvhLbvh (linear BVH)
 constexpr int kGpuBvhPloc = 0, kGpuBvhLbvh = 1;
 hipError_t gpu_build_bvh4(const float* soup, const uint32_t* prim, const uint32_t* mat, int64_t n, BVHNode* nodes,
                           TriRec* tris, hipStream_t st, GpuBvhStats* stats, int builder);
+
+// Triangle soup of a mesh on the device (indices, vertices and materials there too).  Words of info,
+// set by gpu_gather_init and gathered over all meshes of a build: [0] nonzero if an index lies outside
+// [0, n_vertices), a vertex is not finite or a material id is negative (the soup is then incomplete),
+// [1] largest material id, [2..4] / [5..7] box of the triangles (gpu_ordered_float)
+constexpr int kGatherWords = 8;
+float gpu_ordered_float(uint32_t u);
+hipError_t gpu_gather_init(uint32_t* info, hipStream_t st);
+hipError_t gpu_gather_mesh(const float* vertices, int64_t n_vertices, const int32_t* indices, const uint32_t* mat,
+                           int64_t n, float* soup, uint32_t* info, hipStream_t st);
+// Emissive triangles of a single-level scene in primitive order.  emits[m]: material m emits.
+// gpu_count_lights fills off [n + 1] (off[n]: their number; sums: gpu_count_lights_scratch(n) words);
+// gpu_list_lights writes tri_light [n] (place in the list, or -1; all -1 if off is null) and list
+// [off[n]][kLightWords] (nine floats of the triangle, its material).
+constexpr int kLightWords = 10;
+size_t gpu_count_lights_scratch(int64_t n);
+hipError_t gpu_count_lights(const TriRec* tris, int64_t n, const uint32_t* emits, uint32_t n_mats, uint32_t* off,
+                            uint32_t* sums, hipStream_t st);
+hipError_t gpu_list_lights(const TriRec* tris, int64_t n, const uint32_t* off, int32_t* tri_light, uint32_t* list,
+                           hipStream_t st);
 
 // ---- radiance cache (pt_nrc.hip) ----
 // t_step / n_records (nullable): count the applied Adam step on the device unless the batch had no records

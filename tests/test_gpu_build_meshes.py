@@ -1,0 +1,96 @@
+"""Meshes gathered and checked on the device by a device build (GPU).
+
+Large meshes are copied one by one, many small ones joined first; both have to
+give the primitives, materials, lights and box of the host build, so closest
+hits and renders are compared bit for bit.  Inputs that the host build refuses
+are refused with its words, and leave the scene as it was.
+"""
+import os
+import sys
+
+import numpy as np
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+sys.path.insert(0, ROOT)
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+
+
+def _split(mesh, parts):
+    """The mesh as `parts` meshes with their own vertices."""
+    from paper_2407_19977_amd import scenes
+    out = []
+    for ids in np.array_split(np.arange(mesh.n_triangles), parts):
+        used, inv = np.unique(mesh.indices[ids], return_inverse=True)
+        out.append(scenes.Mesh(np.ascontiguousarray(mesh.vertices[used]), inv.reshape(-1, 3).astype(np.int32),
+                               np.ascontiguousarray(mesh.material_ids[ids])))
+    return out
+
+
+@pytest.mark.parametrize("which,parts", [("cornell", 1), ("cornell", 7), ("spheres", 1), ("spheres", 3), ("spheres", 200),
+                                         ("material_zoo", 5)])
+def test_device_gather_equals_host_build(which, parts):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    print(f"[gather] {which} in {parts}", flush=True)
+    from paper_2407_19977_amd import pt, scenes
+    sc = getattr(scenes, which)()
+    assert not sc.instances
+    meshes = [p for m in sc.meshes for p in (_split(m, parts) if parts > 1 else [m])]
+    cam = sc.with_camera(width=96, height=64).camera
+    res = []
+    for dev in (False, True):
+        s = pt.scene_from(sc, device=0)
+        try:
+            s.build_bvh(meshes, on_device=dev)
+            out = torch.empty((64, 96, 3), dtype=torch.float32, device="cuda:0")
+            s.render(cam, 3, 5, 9, out)
+            # another material table: the lights follow it
+            mats = np.asarray(sc.materials, np.float32).reshape(-1, 39).copy()
+            s.upload_materials(mats[::-1].copy())
+            out2 = torch.empty_like(out)
+            s.render(cam, 2, 5, 9, out2)
+            res.append((out.cpu(), out2.cpu()))
+        finally:
+            s.close()
+    assert torch.equal(res[0][0], res[1][0]) and torch.equal(res[0][1], res[1][1])
+
+
+@pytest.mark.parametrize("parts", [1, 6])
+@pytest.mark.parametrize("fault", ["index", "low_index", "nan", "inf_unused", "material"])
+def test_refused_meshes_leave_the_scene(parts, fault):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    print(f"[refuse] {fault} in {parts}", flush=True)
+    from paper_2407_19977_amd import pt, scenes
+    sc = scenes.cornell()
+    s = pt.scene_from(sc, device=0)
+    try:
+        cam = sc.with_camera(width=32, height=32).camera
+        before, after = (torch.empty((32, 32, 3), dtype=torch.float32, device="cuda:0") for _ in range(2))
+        s.render(cam, 2, 4, 1, before)
+        meshes = _split(sc.meshes[0], parts)
+        m = meshes[-1]
+        v, ix, mid = m.vertices.copy(), m.indices.copy(), m.material_ids.copy()
+        if fault == "index":
+            ix[-1, 2] = len(v)
+        elif fault == "low_index":
+            ix[0, 1] = -1
+        elif fault == "nan":
+            v[0, 1] = np.nan
+        elif fault == "inf_unused":
+            v = np.concatenate([v, np.full((1, 3), np.inf, np.float32)])
+        else:
+            mid[0] = -3
+        meshes[-1] = scenes.Mesh(v, ix, mid)
+        said = []
+        for dev in (False, True):
+            with pytest.raises(Exception) as e:
+                s.build_bvh(meshes, on_device=dev)
+            said.append(str(e.value))
+        assert said[0] == said[1]
+        s.render(cam, 2, 4, 1, after)
+        assert torch.equal(before, after)
+    finally:
+        s.close()
