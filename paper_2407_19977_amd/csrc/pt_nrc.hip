@@ -367,9 +367,47 @@ __global__ __launch_bounds__(64 * kInferWaves) void k_nrc_infer(const float* __r
 }
 
 // -------------------------------------------------------- forward+backward
-// a_store[l][f][n] (l = 0..5 layer inputs) and g_store[l][f][n] (l = 0..5
-// gradients of the layer outputs), bf16, n padded to npad.  Samples at
-// n >= N are written as zeros.  loss_part[block] = sum of the block's loss terms.
+// a_store (l = 0..5 layer inputs) and g_store (l = 0..5 gradients of the layer
+// outputs), bf16 in blocks of 32 samples: [l][n / 32][f][n % 32], n padded to
+// npad.  A matrix-core operand of k_nrc_dw (16 features of 32 samples) is then
+// 1 KB in a row; as [l][f][n] its 16 rows lay 2 npad bytes apart, 32 KB for
+// 16,384 samples, all on the same few L2 channels (dW 16.7 us with that layout, 13.6 with this).
+// Samples at n >= N are written as zeros.  loss_part[block] = sum of the
+// block's loss terms.  With 16,384 samples a wave has one group, so the kernel
+// lasts as long as one chain: 80 KB of weights into LDS (all loads at once, the
+// group's rows before them), encoding, twelve dependent layers, 25 MB of stores
+// (20.8 us, with the loads ahead 17.8).
+__device__ inline size_t store_at(int l, int f, int n, int npad) {
+  return ((size_t)l * (npad / 32) + n / 32) * (64 * 32) + f * 32 + n % 32;
+}
+
+// Eight features of one sample a lane (u, feature(j) for j = 0..7), as two
+// stores of four samples of one feature: the lanes of a quad (four samples)
+// exchange halves twice.  44 stores a lane instead of 176 two-byte ones: half
+// of the memory instructions and address arithmetic of a kernel alone on the
+// chip (no more than 0.5 us of 18), less for what runs beside it in a frame.
+// Every lane of the wave takes part.
+template <class F>
+__device__ inline void store_features(uint16_t* __restrict__ store, int l, uint4 u, F feature, int n, int npad) {
+  const uint32_t bit0 = n & 1, bit1 = (n >> 1) & 1;
+  const uint32_t w[4] = {u.x, u.y, u.z, u.w};
+  uint32_t p[4];  // feature 2k + bit0 of samples (n & ~1), + 1
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    const uint32_t o = (uint32_t)__builtin_amdgcn_mov_dpp((int)w[k], 0xB1, 0xF, 0xF, true);  // lane ^ 1
+    p[k] = __builtin_amdgcn_perm(o, w[k], bit0 ? 0x03020706u : 0x05040100u);
+  }
+#pragma unroll
+  for (int k = 0; k < 4; k += 2) {
+    const uint32_t send = bit1 ? p[k] : p[k + 1];
+    const uint32_t got = (uint32_t)__builtin_amdgcn_mov_dpp((int)send, 0x4E, 0xF, 0xF, true);  // lane ^ 2
+    const uint2 v = bit1 ? make_uint2(got, p[k + 1]) : make_uint2(p[k], got);
+    *reinterpret_cast<uint2*>(store + store_at(l, feature(2 * k + (int)(2 * bit1 + bit0)), n & ~3, npad)) = v;
+  }
+}
+
+__device__ inline uint4 as_words(bf16x8 v) { return __builtin_bit_cast(uint4, v); }
+
 __global__ __launch_bounds__(256) void k_nrc_fwd_bwd(const float* __restrict__ X, const float* __restrict__ T,
                                                      int N, int npad, const uint4* __restrict__ fwd,
                                                      const uint4* __restrict__ bwd, uint16_t* __restrict__ a_store,
@@ -377,19 +415,42 @@ __global__ __launch_bounds__(256) void k_nrc_fwd_bwd(const float* __restrict__ X
   __shared__ uint4 sw[kNrcFwdFrags * 64];
   __shared__ uint4 swt[kNrcBwdFrags * 64];
   __shared__ float wave_loss[4];
-  for (int i = threadIdx.x; i < kNrcFwdFrags * 64; i += blockDim.x) sw[i] = fwd[i];
-  for (int i = threadIdx.x; i < kNrcBwdFrags * 64; i += blockDim.x) swt[i] = bwd[i];
-  __syncthreads();
   const int wave = threadIdx.x / 64, lane = threadIdx.x % 64, g = lane / 16, q = lane % 16;
+  // a group's inputs and targets: rows past the last read the last and are not used
+  float x_in[12], t_in[3];
+  const auto load_group = [&](int grp) {
+    const size_t row = (size_t)min(grp * 16 + q, N - 1);
+#pragma unroll
+    for (int k = 0; k < 12; ++k) x_in[k] = X[row * 12 + k];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) t_in[k] = T[row * 3 + k];
+  };
+  load_group(blockIdx.x * 4 + wave);
+  {  // all of a thread's weight fragments in flight at once
+    constexpr int kF = kNrcFwdFrags * 64, kB = kNrcBwdFrags * 64;
+    uint4 f[(kF + 255) / 256], b[(kB + 255) / 256];
+#pragma unroll
+    for (int k = 0; k < (kF + 255) / 256; ++k) f[k] = fwd[min(k * 256 + (int)threadIdx.x, kF - 1)];
+#pragma unroll
+    for (int k = 0; k < (kB + 255) / 256; ++k) b[k] = bwd[min(k * 256 + (int)threadIdx.x, kB - 1)];
+#pragma unroll
+    for (int k = 0; k < (kF + 255) / 256; ++k)
+      if (k * 256 + (int)threadIdx.x < kF) sw[k * 256 + threadIdx.x] = f[k];
+#pragma unroll
+    for (int k = 0; k < (kB + 255) / 256; ++k)
+      if (k * 256 + (int)threadIdx.x < kB) swt[k * 256 + threadIdx.x] = b[k];
+  }
+  __syncthreads();
   const float inv_count = 1.0f / (3.0f * (float)N);
   float my_loss = 0.0f;
-  const size_t L = (size_t)64 * npad;  // one layer of a store
   for (int grp = blockIdx.x * 4 + wave; grp * 16 < npad; grp += gridDim.x * 4) {
     int qi = grp * 16 + q;
     bool valid = qi < N;
     float x[12];
 #pragma unroll
-    for (int k = 0; k < 12; ++k) x[k] = valid ? X[(size_t)qi * 12 + k] : 0.0f;
+    for (int k = 0; k < 12; ++k) x[k] = valid ? x_in[k] : 0.0f;
+    const float target[3] = {t_in[0], t_in[1], t_in[2]};
+    load_group(grp + gridDim.x * 4);
     bf16x8 keep[12];
     bf16x8 B[2];
     encode_operand(x, g, B);
@@ -398,19 +459,17 @@ __global__ __launch_bounds__(256) void k_nrc_fwd_bwd(const float* __restrict__ X
 #pragma unroll
     for (int l = 0; l < 6; ++l)
 #pragma unroll
-      for (int c = 0; c < 2; ++c)
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-          int f = l == 0 ? nrc_k_in(c, g, j) : nrc_k_chained(c, g, j);
-          float v = valid ? bf16x8_get(keep[2 * l + c], j) : 0.0f;
-          a_store[l * L + (size_t)f * npad + qi] = bf16_bits(v);
-        }
+      for (int c = 0; c < 2; ++c) {
+        const uint4 u = valid ? as_words(keep[2 * l + c]) : make_uint4(0u, 0u, 0u, 0u);
+        store_features(a_store, l, u, [&](int j) { return l == 0 ? nrc_k_in(c, g, j) : nrc_k_chained(c, g, j); }, qi,
+                       npad);
+      }
     // loss gradient (lanes g == 0 hold the three outputs of query q)
     float dy[3] = {0.0f, 0.0f, 0.0f};
     if (g == 0 && valid) {
 #pragma unroll
       for (int ch = 0; ch < 3; ++ch) {
-        float t = T[(size_t)qi * 3 + ch];
+        float t = target[ch];
         float d = y[ch] * y[ch] + 0.01f;
         float r = y[ch] - t;
         my_loss += r * r / d;
@@ -425,7 +484,7 @@ __global__ __launch_bounds__(256) void k_nrc_fwd_bwd(const float* __restrict__ X
     bf16x8 G5 = as_bf16x8(gu);
     if (g == 0) {
 #pragma unroll
-      for (int ch = 0; ch < 3; ++ch) g_store[5 * L + (size_t)ch * npad + qi] = bf16_bits(dy[ch]);
+      for (int ch = 0; ch < 3; ++ch) g_store[store_at(5, ch, qi, npad)] = bf16_bits(dy[ch]);
     }
     // g_4 = (W5^T g_5) * [a_5 > 0]
     f32x4 acc[4];
@@ -442,7 +501,6 @@ __global__ __launch_bounds__(256) void k_nrc_fwd_bwd(const float* __restrict__ X
         for (int i = 0; i < 4; ++i) {
           float a = bf16x8_get(keep[2 * (lo + 1) + t / 2], (t % 2) * 4 + i);
           gv[t][i] = a > 0.0f ? acc[t][i] : 0.0f;
-          g_store[lo * L + (size_t)(16 * t + 4 * g + i) * npad + qi] = bf16_bits(valid ? gv[t][i] : 0.0f);
         }
 #pragma unroll
       for (int c = 0; c < 2; ++c) {
@@ -452,6 +510,8 @@ __global__ __launch_bounds__(256) void k_nrc_fwd_bwd(const float* __restrict__ X
         u.z = pack2(gv[2 * c + 1][0], gv[2 * c + 1][1]);
         u.w = pack2(gv[2 * c + 1][2], gv[2 * c + 1][3]);
         Gc[c] = as_bf16x8(u);
+        store_features(g_store, lo, valid ? u : make_uint4(0u, 0u, 0u, 0u),
+                       [&](int j) { return nrc_k_chained(c, g, j); }, qi, npad);
       }
       if (lo == 0) break;
       // g_{lo-1} (pre-mask) = W_lo^T g_lo
@@ -471,40 +531,49 @@ __global__ __launch_bounds__(256) void k_nrc_fwd_bwd(const float* __restrict__ X
 }
 
 // ---------------------------------------------------------- weight grads
-// One wave per (tile, split): dW_l[16 to + .][16 ti + .] over samples of the split.
+// One wave per (tile, split): dW_l[16 to + .][16 ti + .] over the samples of
+// the split, in sample order.  A workgroup's waves are the four ti of one to
+// (one gradient operand); the four workgroups of a (layer, split) follow each
+// other on one XCD (workgroup index mod 8), whose L2 then serves three of the
+// four reads of its layer inputs (16,384 samples: 13.6 us without, 11.8 with; with
+// the loads ahead of the chain 9.8).
+constexpr int kXcds = 8;
 __global__ __launch_bounds__(256) void k_nrc_dw(const uint16_t* __restrict__ a_store,
                                                 const uint16_t* __restrict__ g_store, int npad, int n_split,
                                                 float* __restrict__ dw_part) {
-  const int wave = threadIdx.x / 64, lane = threadIdx.x % 64, g = lane / 16, r = lane % 16;
-  const int wid = blockIdx.x * 4 + wave;
-  if (wid >= 84 * n_split) return;
-  const int tile = wid % 84, split = wid / 84;
-  int l, to, ti;
-  if (tile < 80) {
-    l = tile / 16;
-    to = (tile % 16) / 4;
-    ti = tile % 4;
-  } else {
-    l = 5;
-    to = 0;
-    ti = tile - 80;
-  }
-  const size_t L = (size_t)64 * npad;
+  const int ti = threadIdx.x / 64, lane = threadIdx.x % 64, g = lane / 16, r = lane % 16;
+  const int turn = blockIdx.x / kXcds, to = turn % 4, unit = turn / 4 * kXcds + (int)(blockIdx.x % kXcds);
+  const int l = unit % 6, split = unit / 6;
+  if (split >= n_split || (l == 5 && to > 0)) return;  // layer 5 has three outputs
   const int per = npad / n_split;
-  const int n0 = split * per, n1 = n0 + per;
-  const uint16_t* ga = g_store + l * L + (size_t)(16 * to + r) * npad;
-  const uint16_t* aa = a_store + l * L + (size_t)(16 * ti + r) * npad;
+  const int n0 = split * per;
   const bool row_ok = l < 5 || r < 3;
+  constexpr int kBlk = 64 * 32;  // elements of 32 samples
+  const uint16_t* ga = g_store + store_at(l, 16 * to + r, n0, npad) + 8 * g;
+  const uint16_t* aa = a_store + store_at(l, 16 * ti + r, n0, npad) + 8 * g;
   f32x4 acc = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-  for (int k = n0; k < n1; k += 32) {
-    uint4 au = row_ok ? *reinterpret_cast<const uint4*>(ga + k + 8 * g) : make_uint4(0u, 0u, 0u, 0u);
-    uint4 bu = *reinterpret_cast<const uint4*>(aa + k + 8 * g);
-    acc = mfma(as_bf16x8(au), as_bf16x8(bu), acc);
+  // the chain through acc takes kAhead steps from registers while memory answers the next
+  constexpr int kAhead = 8;
+  const int steps = per / 32;
+  for (int k0 = 0; k0 < steps; k0 += kAhead) {
+    uint4 au[kAhead], bu[kAhead];
+#pragma unroll
+    for (int j = 0; j < kAhead; ++j) {
+      const int k = min(k0 + j, steps - 1);
+      au[j] = *reinterpret_cast<const uint4*>(ga + (size_t)k * kBlk);  // rows past layer 5's three: not used
+      bu[j] = *reinterpret_cast<const uint4*>(aa + (size_t)k * kBlk);
+    }
+#pragma unroll
+    for (int j = 0; j < kAhead; ++j) {
+      if (k0 + j >= steps) break;
+      if (!row_ok) au[j] = make_uint4(0u, 0u, 0u, 0u);
+      acc = mfma(as_bf16x8(au[j]), as_bf16x8(bu[j]), acc);
+    }
   }
   float* dst = dw_part + (size_t)split * kNrcParams;
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
-    int o = 16 * to + 4 * g + i, in = 16 * ti + r;
+    const int o = 16 * to + 4 * g + i, in = 16 * ti + r;
     if (l < 5 || o < 3) dst[nrc_widx(l, o, in)] = acc[i];
   }
 }
@@ -525,6 +594,7 @@ __global__ __launch_bounds__(256) void k_nrc_adam(float* __restrict__ w, float* 
   int p = blockIdx.x * blockDim.x + threadIdx.x;
   if (p >= kNrcParams) return;
   float gsum = 0.0f;
+#pragma unroll 16
   for (int s = 0; s < n_split; ++s) gsum += dw_part[(size_t)s * kNrcParams + p];
   if (grad_out) grad_out[p] = gsum;
   if (!apply || (n_records && *n_records == 0u)) return;
@@ -740,8 +810,8 @@ hipError_t nrc_launch_train(const float* X, const float* T, int N, int npad, int
                             float* dw_part, hipStream_t st) {
   hipLaunchKernelGGL(k_nrc_fwd_bwd, dim3(grid_fb), dim3(256), 0, st, X, T, N, npad, fwd, bwd, a_store, g_store,
                      loss_part);
-  int waves = 84 * n_split;
-  hipLaunchKernelGGL(k_nrc_dw, dim3((waves + 3) / 4), dim3(256), 0, st, a_store, g_store, npad, n_split, dw_part);
+  const int units = (6 * n_split + kXcds - 1) / kXcds * kXcds;
+  hipLaunchKernelGGL(k_nrc_dw, dim3(4 * units), dim3(256), 0, st, a_store, g_store, npad, n_split, dw_part);
   return hipGetLastError();
 }
 
