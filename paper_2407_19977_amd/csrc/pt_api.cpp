@@ -102,7 +102,7 @@ struct pt_scene {
   uint32_t bvh_root = 0;     // node a walk starts at
   int bvh_max_leaf = 0;
   double bvh_sah = 0.0;      // host builds only
-  double bvh_build_ms = 0.0; // triangle soup in host memory -> BVH ready where the builder leaves it
+  double bvh_build_ms = 0.0; // meshes in host memory (host builder: triangle soup) -> BVH ready where the builder leaves it
   bool bvh_on_device = false;
   float tmin = 0.0f;
   int32_t max_mat_id = -1;
