@@ -1623,15 +1623,13 @@ pt_status build_bvh_any(pt_scene* s, const pt_mesh* meshes, int32_t n_meshes, co
       hi[k] = gpu_ordered_float(soup.info[5 + k]);
     }
     // nodes and triangle records are written in place
+    s->has_bvh = false;  // until the new one is whole
     PT_HIP(s->nodes.alloc((size_t)std::max<int64_t>(1, total - 1) * sizeof(BVHNode)));
     PT_HIP(s->tris.alloc((size_t)total * sizeof(TriRec)));
     GpuBvhStats st{};
     e = gpu_build_bvh4(soup.soup, nullptr, soup.mat, total, s->nodes.as<BVHNode>(), s->tris.as<TriRec>(), s->stream,
                        &st, s->gpu_bvh_builder);
-    if (e != hipSuccess) {
-      s->has_bvh = false;  // the scene's buffers were overwritten
-      return fail(PT_ERR_DEVICE, "device BVH build failed: %s", hipGetErrorString(e));
-    }
+    if (e != hipSuccess) return fail(PT_ERR_DEVICE, "device BVH build failed: %s", hipGetErrorString(e));
     n_nodes = st.n_nodes;
     depth = st.depth;
     max_leaf = st.max_leaf;
@@ -1662,6 +1660,7 @@ pt_status build_bvh_any(pt_scene* s, const pt_mesh* meshes, int32_t n_meshes, co
     Bvh4 bvh;
     std::string err;
     if (!build_bvh4(verts.data(), prim.data(), matu.data(), total, bvh, err)) return fail(PT_ERR_INVALID_ARG, "%s", err.c_str());
+    s->has_bvh = false;  // until the new one is whole
     PT_HIP(upload(s->nodes, bvh.nodes.data(), bvh.nodes.size() * sizeof(BVHNode), s->stream));
     PT_HIP(upload(s->tris, bvh.tris.data(), bvh.tris.size() * sizeof(TriRec), s->stream));
     PT_HIP(hipStreamSynchronize(s->stream));
