@@ -477,13 +477,27 @@ __device__ inline float widen_limit(float t) { return fmaf(fabsf(t), 1.907348632
 // at most 4 u |t| + u |o inv| (u = 2^-24); the constants move by 4 u |o inv| to
 // the safe side, the far distance and the pruning limit widen by 64 u and 32 u
 // relative, so every box is at least as wide as one widened by 16 u computed from
-// (p - o) / d.  A component below 2^-100 counts as 2^-100 with a slack of 2^40,
-// 2^-60 in space: finite products instead of 0 x inf, and the axis still prunes.
-__device__ inline void box_axis(float o, float d, float& inv, float& n, float& f) {
-  const float tiny = 7.888609052210118e-31f;  // 2^-100
-  const bool small = fabsf(d) < tiny;
-  inv = __builtin_amdgcn_rcpf(small ? copysignf(tiny, d) : d);
-  const float c = o * inv, e = fmaf(fabsf(c), 2.384185791015625e-07f, small ? 1099511627776.0f : 0.0f);
+// (p - o) / d.  A component smaller than `tiny` counts as tiny with a slack of
+// `reach` in t: finite products instead of 0 x inf, and the axis still prunes.
+// The ray leaves its true line by less than tiny t that way, the slack in space is
+// tiny reach, so no box is lost before t = reach.
+struct BoxSmall {
+  float tiny, reach;
+};
+// Both follow the direction's largest component m, for a ray of any length: tiny is
+// 2^-100 m (2^-126 at least, whose reciprocal is finite) and reach 2^50 / m, about
+// 10^15 units of space; the slack in space is 2^-50 (2^-76 / m below m = 2^-26).
+// Below m = 2^-128 the triangle test's 1 / m is infinite and no hit is possible.
+__device__ inline BoxSmall box_small(float dx, float dy, float dz) {
+  float m = fmaxf(fmaxf(fabsf(dx), fabsf(dy)), fabsf(dz));
+  if (m < 2.938735877055719e-39f) m = 1.0f;  // 2^-128
+  return BoxSmall{fmaxf(m * 7.888609052210118e-31f, 1.1754943508222875e-38f),
+                  __builtin_amdgcn_rcpf(m) * 1125899906842624.0f};
+}
+__device__ inline void box_axis(float o, float d, BoxSmall s, float& inv, float& n, float& f) {
+  const bool small = fabsf(d) < s.tiny;
+  inv = __builtin_amdgcn_rcpf(small ? copysignf(s.tiny, d) : d);
+  const float c = o * inv, e = fmaf(fabsf(c), 2.384185791015625e-07f, small ? s.reach : 0.0f);
   n = -c - e;
   f = -c + e;
 }
@@ -492,9 +506,10 @@ __device__ inline uint32_t near_offset(uint32_t a, float inv) { return (32u * a)
 
 __device__ inline void lane_box(LaneRay& L, float ox, float oy, float oz, float dx, float dy, float dz) {
 #pragma clang fp contract(off)
-  box_axis(ox, dx, L.ix, L.nx, L.fx);
-  box_axis(oy, dy, L.iy, L.ny, L.fy);
-  box_axis(oz, dz, L.iz, L.nz, L.fz);
+  const BoxSmall s = box_small(dx, dy, dz);
+  box_axis(ox, dx, s, L.ix, L.nx, L.fx);
+  box_axis(oy, dy, s, L.iy, L.ny, L.fy);
+  box_axis(oz, dz, s, L.iz, L.nz, L.fz);
 }
 
 // The ray (o, d) of the level whose triangles are tested next.

@@ -88,3 +88,32 @@ def test_hits_equal_brute_force(which, kind):
     assert int(b[:, 5].sum()) > n // 10, "too few rays hit to tell anything"
     bad = torch.nonzero((a != b).any(1)).ravel()
     assert len(bad) == 0, f"{len(bad)} of {n} rays differ, first {bad[:5].tolist()}: {rays[bad[:2]].tolist()}"
+
+
+@pytest.mark.parametrize("kind", ["axis", "plane", "spread", "far"])
+@pytest.mark.parametrize("which", ["box", "field", "instanced"])
+def test_short_directions_equal_brute_force(which, kind):
+    """Directions of any length, down to about 2^-104: the walk's margins have to follow the largest
+    component (t grows as it shrinks), and small components may be far below it or below 2^-100."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2407_19977_amd import pt
+    print(f"[walk] {which} short {kind}", flush=True)
+    sc = _scene(which)
+    n = 3000 if which != "instanced" else 1200
+    rays = _rays(sc, n, "tiny" if kind == "spread" else kind, 23)
+    r = np.random.Generator(np.random.PCG64(29))
+    d = rays[:, 4:7].astype(np.float64)
+    if kind == "spread":  # one component a factor of up to 2^12 below the rest, beside denormal ones
+        d[np.arange(n), r.integers(0, 3, n)] *= 2.0 ** -r.integers(0, 12, n)
+    rays[:, 4:7] = d * 2.0 ** r.choice([-20, -41, -60, -78, -92, -104], (n, 1))
+    rays = torch.from_numpy(rays).to("cuda:0")
+    s = pt.scene_from(sc, device=0)
+    a = torch.empty((n, 6), dtype=torch.int32, device="cuda:0")
+    b = torch.empty_like(a)
+    s.trace_closest(rays, a)
+    s.trace_closest(rays, b, brute_force=True)
+    s.close()
+    assert int(b[:, 5].sum()) > n // 10, "too few rays hit to tell anything"
+    bad = torch.nonzero((a != b).any(1)).ravel()
+    assert len(bad) == 0, f"{len(bad)} of {n} rays differ, first {bad[:5].tolist()}: {rays[bad[:2]].tolist()}"
