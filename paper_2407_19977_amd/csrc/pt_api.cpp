@@ -59,6 +59,7 @@ struct DevBuf {
     release();
     hipError_t e = hipMalloc(&p, n ? n : 16);
     if (e == hipSuccess) bytes = n;
+    else (void)hipGetLastError();  // the caller gets the error; a later call's launch check must not find it
     return e;
   }
   template <class T>
@@ -688,7 +689,6 @@ pt_status run_passes(pt_scene* s, const CamDev& C, int x0, int y0, int w, int h,
     if (e == hipSuccess) break;
     // the device has less memory left than these passes need: smaller passes
     if (e != hipErrorOutOfMemory || spp_max == 1) PT_HIP(e);
-    (void)hipGetLastError();
     for (PathBufs& B : s->pb) release_paths(B);
     spp_max = pass_samples(N, n, N * ((spp_max + 1) / 2));
   }

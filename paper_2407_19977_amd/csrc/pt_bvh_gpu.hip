@@ -1145,8 +1145,12 @@ struct Scratch {
   size_t cap = 0, used = 0;
   std::vector<void*> extra;
   explicit Scratch(size_t bytes) {
-    if (hipMalloc(&arena, bytes) == hipSuccess) cap = bytes;
-    else arena = nullptr;
+    if (hipMalloc(&arena, bytes) == hipSuccess) {
+      cap = bytes;
+    } else {
+      arena = nullptr;
+      (void)hipGetLastError();  // get() allocates piece by piece
+    }
   }
   ~Scratch() {
     for (void* p : extra) (void)hipFree(p);
@@ -1163,6 +1167,7 @@ struct Scratch {
     void* p = nullptr;
     hipError_t e = hipMalloc(&p, b);
     if (e == hipSuccess) extra.push_back(p);
+    else (void)hipGetLastError();
     *out = static_cast<T*>(p);
     return e;
   }

@@ -1,0 +1,75 @@
+"""What the library does when the device runs out of memory (CPU).
+
+libpt.so runs on stand-ins of the HIP calls (hip_host_stub.c) whose memory has a
+budget and whose kernels do nothing, each test in a process of its own.
+"""
+import os
+import subprocess
+import sys
+import textwrap
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+ROOT = os.path.dirname(HERE)
+
+PRELUDE = """
+import ctypes as C, sys
+stub = C.CDLL({stub!r}, mode=C.RTLD_GLOBAL)
+stub.stub_held.restype = stub.stub_peak.restype = C.c_size_t
+stub.stub_budget.argtypes = [C.c_size_t]
+stub.stub_mallocs.restype = stub.stub_launches.restype = C.c_long
+stub.stub_fail_malloc.argtypes = [C.c_long]
+sys.path.insert(0, {root!r})
+import numpy as np
+from paper_2407_19977_amd import pt, scenes
+
+
+class Mem:
+    # a buffer of the stand-in's memory with what the binding asks of a tensor
+    def __init__(self, *shape):
+        self.shape, self.a = shape, np.zeros(shape, np.float64)
+    def data_ptr(self):
+        return self.a.ctypes.data
+    def numel(self):
+        return self.a.size
+
+
+def status(f, *args, **kw):
+    try:
+        f(*args, **kw)
+    except pt.PtError as e:
+        return e.status
+    return 0
+"""
+
+
+@pytest.fixture(scope="module")
+def stub(tmp_path_factory):
+    so = str(tmp_path_factory.mktemp("stub") / "hip_host_stub.so")
+    subprocess.run(["gcc", "-O1", "-shared", "-fPIC", "-o", so, os.path.join(HERE, "hip_host_stub.c")], check=True)
+    return so
+
+
+def _run(stub, body):
+    code = PRELUDE.format(stub=stub, root=ROOT) + textwrap.dedent(body)
+    r = subprocess.run([sys.executable, "-c", code], capture_output=True, text=True, timeout=120)
+    assert r.returncode == 0, r.stdout + r.stderr
+
+
+def test_failed_allocation_is_reported_once(stub):
+    """The call after one that ran out of memory does not report that error again."""
+    _run(stub, """
+    sc = scenes.cornell()
+    rays, hits = Mem(4, 8), Mem(4, 6)
+    s = pt.PtScene(0)
+    stub.stub_fail_malloc(1)
+    assert status(s.build_bvh, sc.meshes) == -3
+    assert status(s.build_bvh, sc.meshes) == 0, pt.last_error()
+    s.upload_materials(sc.materials)
+    out = Mem(16, 16, 3)
+    cam = sc.with_camera(width=16, height=16).camera
+    stub.stub_fail_malloc(3)
+    assert status(s.render, cam, 1, 3, 0, out) == -3
+    assert status(s.trace_closest, rays, hits) == 0, pt.last_error()
+    """)
