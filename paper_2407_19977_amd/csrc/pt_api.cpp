@@ -1445,6 +1445,7 @@ pt_status build_two_level(pt_scene* s, const pt_mesh* meshes, int32_t n_meshes, 
                         std::string& err) { return gpu_mesh_bvh(s, v, prim, mat, n, b, err); };
   r = build_two_level_host(meshes, n_meshes, instances, n_instances, T, on_device ? &gpu : nullptr);
   if (r) return r;
+  s->has_bvh = false;  // until the new one is whole
   // the top level's nodes follow the meshes', so that a walk reads one array
   const uint32_t root = (uint32_t)T.nodes.size();
   for (BVHNode n : T.top.nodes) {

@@ -73,3 +73,34 @@ def test_failed_allocation_is_reported_once(stub):
     assert status(s.render, cam, 1, 3, 0, out) == -3
     assert status(s.trace_closest, rays, hits) == 0, pt.last_error()
     """)
+
+
+def test_failed_two_level_build_leaves_no_bvh(stub):
+    """Whatever allocation fails, a two-level build that replaced part of the old hierarchy leaves none."""
+    _run(stub, """
+    def mesh(level):
+        v, f = scenes.icosphere(level)
+        return scenes.Mesh(v.astype(np.float32), f.astype(np.int32), np.zeros(len(f), np.int32))
+    def placed(n):
+        return [scenes.Instance(np.array([[1, 0, 0, 3 * k], [0, 1, 0, 0], [0, 0, 1, 0]], np.float32), 0, -1) for k in range(n)]
+    rays, hits = Mem(4, 8), Mem(4, 6)
+    failed = 0
+    for k in range(1, 40):
+        s = pt.PtScene(0)
+        s.build_bvh([mesh(1)], placed(3))
+        assert status(s.trace_closest, rays, hits) == 0
+        stub.stub_fail_malloc(k)
+        r = status(s.build_bvh, [mesh(3), mesh(2)], placed(40))
+        stub.stub_fail_malloc(-1)
+        if r == 0:
+            break
+        failed += 1
+        assert r == -3, r
+        launched = stub.stub_launches()
+        assert status(s.trace_closest, rays, hits) == -5, k
+        assert stub.stub_launches() == launched
+        s.build_bvh([mesh(3)], placed(2))
+        assert status(s.trace_closest, rays, hits) == 0, pt.last_error()
+        s.close()
+    assert failed >= 5
+    """)
