@@ -394,16 +394,16 @@ pt_status pt_nrc_training_records(pt_scene* scene, const pt_camera* camera, int3
 
 /* Tail hand-off of the sampling passes.  A pass runs the wavefront kernels
  * (one launch per stage per bounce) while many paths are alive; from bounce
- * min_bounce on, once at most max_fraction of the pass's paths (counted from
- * at most 2^21 of them: a pass holds several samples of every pixel) are still
+ * min_bounce on, once at most max_fraction of the pass's paths are still
  * alive, one persistent kernel runs all remaining vertices of every path
  * (closest hit, shading, shadow ray, next ray) without a kernel boundary
- * per bounce.  The decision reads one counter back per pass.  A pass of at
- * most 327,680 slots runs in that kernel from its first vertex, unless the
- * hand-off is off.  Results are
- * identical either way (same arithmetic, same random numbers).  Defaults:
- * min_bounce 2, max_fraction 0.15; max_fraction 0 (or min_bounce > 64)
- * keeps the wavefront throughout.  Errors: INVALID_ARG for min_bounce < 0
+ * per bounce.  The decision reads the queue counts (2 KB) back once per
+ * bounce from min_bounce on.  Defaults: min_bounce 2, max_fraction 0.15; with
+ * these the fraction counts from at most 2^21 paths (a pass may hold several
+ * samples of every pixel), and a pass of at most 327,680 paths runs in the
+ * persistent kernel from its first vertex.  max_fraction 0 (or min_bounce >
+ * 64) keeps the wavefront throughout.  Results are identical either way (same
+ * arithmetic, same random numbers).  Errors: INVALID_ARG for min_bounce < 0
  * or max_fraction outside [0, 1]. */
 pt_status pt_set_tail(pt_scene* scene, int32_t min_bounce, double max_fraction);
 

@@ -85,6 +85,9 @@ bool finite_all(const float* p, size_t n) {
 
 }  // namespace
 
+constexpr int kTailMinBounce = 2;  // pt_set_tail's defaults
+constexpr double kTailFraction = 0.15;
+
 // Device buffers of one set of path slots (struct-of-arrays).
 struct PathBufs {
   DevBuf path, hit_inst, cls, L, eta, q_ray[2], q_cls[kNumClasses], sh_o, sh_d, sh_c, sh_inst,
@@ -164,8 +167,8 @@ struct pt_scene {
   hipEvent_t ev_train = nullptr;  // the last enqueued training's weights are in place
   hipEvent_t ev_train_t[2][2] = {{nullptr, nullptr}, {nullptr, nullptr}};  // timing around a frame's training
   // tail hand-off
-  int tail_min_bounce = 2;
-  double tail_fraction = 0.15;
+  int tail_min_bounce = kTailMinBounce;
+  double tail_fraction = kTailFraction;
   int gpu_bvh_builder = kGpuBvhPloc;  // builder of pt_build_bvh_gpu
   double ms_tail = 0.0;
   int64_t launches_tail = 0;
@@ -643,6 +646,11 @@ pt_status read_pass_events(pt_scene* s, int set, int wavefront_bounces, int trac
   return PT_OK;
 }
 
+// pt_set_tail has not changed the hand-off (or set its defaults again).
+bool tail_defaults(const pt_scene* s) {
+  return s->tail_min_bounce == kTailMinBounce && s->tail_fraction == kTailFraction;
+}
+
 // Slots of a sampling pass with several samples per pixel.  A pass of few
 // paths is bound by its launches and by each launch's longest ray (the box at
 // 128x128, 16 spp: 16 passes of 16K slots 4.66 ms, one pass of 262K 0.46 ms).
@@ -743,6 +751,7 @@ pt_status run_passes(pt_scene* s, const CamDev& C, int x0, int y0, int w, int h,
       A.tail_host_count = s->tail_counts + set * kShardWords;
       A.tail_min_bounce = s->tail_min_bounce;
       A.tail_fraction = s->tail_fraction;
+      A.tail_sized = tail_defaults(s);
     }
     A.wavefront_bounces = &wavefront[set];
     A.trace_launches = &traces[set];
@@ -883,6 +892,7 @@ pt_status run_cache_frames(pt_scene* s, const CamDev& C, int first, int n, int m
       A.tail_host_count = s->tail_counts + set * kShardWords;
       A.tail_min_bounce = s->tail_min_bounce;
       A.tail_fraction = s->tail_fraction;
+      A.tail_sized = tail_defaults(s);
       A.tail_bound = (uint32_t)s->nrc_cfg.train_paths;
     }
     A.wavefront_bounces = &wavefront[set];

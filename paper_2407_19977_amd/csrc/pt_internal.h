@@ -184,9 +184,10 @@ struct PassArgs {
   int nrc_bounce;          // vertex at which paths end in the radiance cache, -1: no cache
   const uint4* nrc_fwd;    // packed forward weight fragments (when nrc_bounce >= 0)
   hipEvent_t* nrc_events;  // 2 events around the cache-query kernel when timing, else nullptr
-  // tail hand-off: from bounce tail_min_bounce on, when at most tail_fraction of the slots (of
-  // the first 2^21 of a larger pass) are still alive, one persistent kernel finishes the paths (tail_host_count: pinned host word)
+  // tail hand-off: from bounce tail_min_bounce on, when at most tail_fraction of the slots are still
+  // alive, one persistent kernel finishes the paths
   uint32_t* tail_host_count;  // kShardWords pinned words
+  bool tail_sized;            // the defaults: passes of few and of many slots have rules of their own
   int tail_min_bounce;
   double tail_fraction;
   hipEvent_t* tail_events;  // 2 events around the tail kernel when timing, else nullptr

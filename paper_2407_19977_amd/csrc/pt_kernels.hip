@@ -1762,14 +1762,15 @@ static hipError_t shade_all(const SceneDev& S, const PathsDev& P, const PassArgs
   return hipGetLastError();
 }
 
-// The hand-off fraction counts from at most this many slots, so the tail
+// Unless the caller set the hand-off (then what it set holds as it is):
+// the hand-off fraction counts from at most this many slots, so the tail
 // kernel never takes more than max_fraction of them however large the pass:
 // its lanes are 18 % active, the wavefront kernels fill the chip with a few
 // hundred thousand paths.  Icosphere field 1080p 64 spp in passes of 2^25
 // slots: 0.7M 103.8 ms, 1.4M 103.5, 2M 102.9, 3M 106.5, no bound (2^24
 // slots) 121.9; instanced scene 32 spp: 151.7 / 153.7 / 150.8 / 153.7 ms.
 static constexpr int32_t kTailPassSlots = 1 << 21;
-// A pass of few slots runs in the tail kernel from its first vertex: the
+// And a pass of few slots runs in the tail kernel from its first vertex: the
 // wavefront's launches, stream joins and count reads take longer than its
 // better lane use saves.  Render in us, wavefront first / whole pass: box 262K
 // slots 538 / 324, 524K 565 / 455, 1M 704 / 740; material zoo 262K 1673 / 1439,
@@ -1803,10 +1804,10 @@ static hipError_t bounce_loop(const SceneDev& S, const PathsDev& P, const CamDev
     if (A.nrc_events) hipEventRecord(A.nrc_events[1], q);
     return e2;
   };
-  const double tail_limit = A.tail_fraction * (double)std::min(P.n, kTailPassSlots);
+  const double tail_limit = A.tail_fraction * (double)(A.tail_sized ? std::min(P.n, kTailPassSlots) : P.n);
   for (int b = 0; b <= A.max_depth; ++b) {
     const int next = (b & 1) ^ 1, cur = b == 0 ? kQueueAll : b & 1;
-    const bool whole = P.n <= kWholePassSlots;
+    const bool whole = A.tail_sized && P.n <= kWholePassSlots;
     if (A.tail_host_count && (whole || b >= A.tail_min_bounce)) {
       // hand the remaining vertices to one persistent kernel once few paths are left
       uint32_t alive = 0;

@@ -46,3 +46,28 @@ def test_hand_over_rule_keeps_the_bits(scene, w, h, spp):
     finally:
         s.set_tail()
     assert torch.equal(out[0], out[1]) and torch.equal(out[0], out[2])
+
+
+@pytest.mark.parametrize("w,h,spp", [(101, 67, 2), (1024, 1024, 3)])
+@pytest.mark.parametrize("first", [1, 3])
+def test_a_set_hand_over_holds_at_any_size(scene, w, h, spp, first):
+    """min_bounce and max_fraction that a caller set are used as they are, by passes of few slots
+    and of more than 2^21: the persistent kernel takes over every path at vertex `first`."""
+    print(f"[rule] {w}x{h}, {spp} spp, from bounce {first}", flush=True)
+    sc, s = scene
+    cam = sc.with_camera(width=w, height=h).camera
+    out = torch.empty((h, w, 3), dtype=torch.float32, device="cuda:0")
+    rays = []
+    try:
+        for args in ((first, 1.0), (0, 0.0)):
+            s.set_tail(*args)
+            for depth in (first - 1, 6):
+                s.reset_stats()
+                s.render(cam, spp, depth, 5, out)
+                st = s.stats()
+                rays.append((st["extension_rays"], st["tail_extension_rays"]))
+    finally:
+        s.set_tail()
+    # the rays of the vertices before `first`, as a render of that depth traces them
+    assert rays[1][0] == rays[3][0] and rays[3][1] == 0
+    assert rays[1][0] - rays[1][1] == rays[2][0]
