@@ -1777,6 +1777,13 @@ static constexpr int32_t kTailPassSlots = 1 << 21;
 // 524K 1784 / 2097; icosphere field (1.31M triangles) 16K 1346 / 837, 262K 1532 /
 // 1069, 524K 1716 / 1528, 1M 2027 / 2468; instanced 262K 2689 / 2067, 524K 2998 /
 // 3247.
+// Not so a pass beside which the next one runs (the frames of the radiance
+// cache): whole passes would follow each other on the second stream, on the
+// part of the chip that the tail kernel leaves them (tail_grid).  Eight frames
+// of 6 bounces, 65,536 training paths, in us, whole / wavefront first: box
+// 320x240 3735 / 3859, 640x400 4364 / 3986; material zoo 12868 / 13825, 18152 /
+// 14572; icosphere field 10131 / 11086, 14400 / 10839; instanced 18005 / 19916,
+// 26278 / 20856; with 512 training paths the zoo at 160x120 11611 / 9298.
 static constexpr int32_t kWholePassSlots = 5 << 16;
 
 template <bool DEBUG, bool COUNT, bool TWO>
@@ -1807,7 +1814,7 @@ static hipError_t bounce_loop(const SceneDev& S, const PathsDev& P, const CamDev
   const double tail_limit = A.tail_fraction * (double)(A.tail_sized ? std::min(P.n, kTailPassSlots) : P.n);
   for (int b = 0; b <= A.max_depth; ++b) {
     const int next = (b & 1) ^ 1, cur = b == 0 ? kQueueAll : b & 1;
-    const bool whole = A.tail_sized && P.n <= kWholePassSlots;
+    const bool whole = A.tail_sized && !A.tail_stream && P.n <= kWholePassSlots;
     if (A.tail_host_count && (whole || b >= A.tail_min_bounce)) {
       // hand the remaining vertices to one persistent kernel once few paths are left
       uint32_t alive = 0;

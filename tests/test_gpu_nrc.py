@@ -606,6 +606,44 @@ def test_overlapped_frames_equal_frame_by_frame(P, O):
     s.set_radiance_cache(None)
 
 
+@pytest.mark.parametrize("w,h,train", [(96, 64, 512), (704, 512, 65536)])
+def test_overlapped_frames_of_any_size_keep_the_bits(P, O, w, h, train):
+    """Frames below and above the size up to which a pass may run whole in the persistent kernel
+    (327,680 slots; 704x512 with 65,536 training paths has 425,984): overlapped, one call per frame,
+    and with the hand-over off.  Sums, weights, Adam moments and counts must be the same bits."""
+    _say(f"[nrc overlap] box scene {w}x{h}, 4 frames, {train} training paths")
+    sc = scenes.cornell(width=w, height=h)
+    cfg = P.cache_config(train_paths=train, batch_size=2048, steps_per_frame=2)
+    s = P.scene_from(sc, device=0)
+    depth, seed, frames = 5, 3, 4
+    out = torch.empty((h, w, 3), dtype=torch.float32, device="cuda:0")
+    results = []
+    for mode in ("overlapped", "by frame", "wavefront"):
+        s.set_tail(*((0, 0.0) if mode == "wavefront" else ()))
+        s.set_radiance_cache(cfg)
+        s.reset_accumulation()
+        s.reset_stats()
+        if mode == "by frame":
+            for k in range(frames):
+                s.accumulate(sc.camera, k, 1, depth, seed)
+        else:
+            s.accumulate(sc.camera, 0, frames, depth, seed)
+        acc = torch.empty((h, w, 3), dtype=torch.float64, device="cuda:0")
+        s.resolve(out, acc)
+        wts = torch.empty(P.NRC_PARAMS, dtype=torch.float32, device="cuda:0")
+        m, v = torch.empty_like(wts), torch.empty_like(wts)
+        step = s.nrc_get_weights(wts, m, v)
+        st = s.stats()
+        assert (st["tail_extension_rays"] > 0) == (mode != "wavefront")
+        results.append((acc, wts, m, v, step, st["cache_records"], st["cache_queries"]))
+    s.close()
+    assert results[0][4] == frames * 2 and results[0][5] > 0 and results[0][6] > 0
+    for other in results[1:]:
+        assert results[0][4:] == other[4:]
+        for x, y in zip(results[0][:4], other[:4]):
+            assert torch.equal(x, y)
+
+
 def test_cache_api_errors(P, O):
     sc = scenes.cornell(width=8, height=8)
     s = P.scene_from(sc, device=0)
