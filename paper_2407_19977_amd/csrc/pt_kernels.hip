@@ -1094,11 +1094,14 @@ __device__ inline void shade_one(const SceneDev& S, const PathsDev& P, uint32_t 
   }
 }
 
-#ifndef PT_SHADE_WAVES
-#define PT_SHADE_WAVES 4  // 3 (uncapped) 89.1 ms a field render, 4 88.4, 5 94.5, 6 99.5 (spills)
-#endif
+// Waves per SIMD that the shading kernel of a class is compiled for: 4 (128
+// registers), 3 for the general class, which needs 165 and would keep 144 bytes a
+// lane in scratch (material zoo 1024x768, 40 spp, its launches 6.52 ms at 4, 5.99
+// at 3; coated 1.49 / 1.57, glass 0.58 / 0.64; instanced scene glass 3.55 / 3.97).
+// Icosphere field render at 3 / 4 / 5 / 6: 89.1 / 88.4 / 94.5 / 99.5 ms.
+constexpr int shade_waves(int cls) { return cls == kClsGeneral ? 3 : 4; }
 template <int CLS, bool DEBUG, bool TWO>
-__global__ __launch_bounds__(kShadeBlock, PT_SHADE_WAVES) void k_shade(SceneDev S, PathsDev P, int b, int max_depth, int next,
+__global__ __launch_bounds__(kShadeBlock, shade_waves(CLS)) void k_shade(SceneDev S, PathsDev P, int b, int max_depth, int next,
                                                   uint32_t sample, uint32_t k0, uint32_t k1,
                                                   int nrc_bounce) {
   // per queue (next rays, shadow rays, cache queries): wave counts, then the workgroup's base
