@@ -1094,9 +1094,79 @@ __device__ inline void shade_one(const SceneDev& S, const PathsDev& P, uint32_t 
   }
 }
 
+template <bool DEBUG, bool TWO>
+__device__ inline void shade_any(int cls, const SceneDev& S, const PathsDev& P, uint32_t slot, int b, int max_depth,
+                                 uint32_t sample, uint32_t k0, uint32_t k1, int nrc_bounce,
+                                 ShadeOut& o, unsigned long long& nf) {
+  const int q = nrc_bounce;
+  switch (cls) {
+    case kClsMiss: shade_one<kClsMiss, DEBUG, TWO>(S, P, slot, b, max_depth, sample, k0, k1, q, o, nf); break;
+    case kClsAbsorb: shade_one<kClsAbsorb, DEBUG, TWO>(S, P, slot, b, max_depth, sample, k0, k1, q, o, nf); break;
+    case kClsDiffuse: shade_one<kClsDiffuse, DEBUG, TWO>(S, P, slot, b, max_depth, sample, k0, k1, q, o, nf); break;
+    case kClsMetal: shade_one<kClsMetal, DEBUG, TWO>(S, P, slot, b, max_depth, sample, k0, k1, q, o, nf); break;
+    case kClsPlastic: shade_one<kClsPlastic, DEBUG, TWO>(S, P, slot, b, max_depth, sample, k0, k1, q, o, nf); break;
+    case kClsGlass: shade_one<kClsGlass, DEBUG, TWO>(S, P, slot, b, max_depth, sample, k0, k1, q, o, nf); break;
+    default: shade_one<kClsGeneral, DEBUG, TWO>(S, P, slot, b, max_depth, sample, k0, k1, q, o, nf); break;
+  }
+}
+
+using ShadeAppend = uint32_t[3][kShadeBlock / 64 + 1];
+// One workgroup's block of a class queue (items [base, base + kShadeBlock) of `count`): shades its
+// paths and appends what they go on with.  s_app: per queue (next rays, shadow rays, cache queries)
+// the wave counts, then the workgroup's base.
+template <bool TWO, class Shade>
+__device__ inline void shade_tile(const PathsDev& P, const uint32_t* q_cls, uint32_t count, uint32_t base, int next,
+                                  ShadeAppend& s_app, Shade shade) {
+  uint32_t i = base + threadIdx.x;
+  bool active = i < count;
+  uint32_t slot = 0;
+  ShadeOut o;
+  o.cont = o.shadow = o.query = false;
+  if (active) {
+    slot = q_cls[i];
+    shade(slot, o);
+  }
+  // one atomic per queue per workgroup iteration
+  const uint32_t shard = base / kShadeBlock % kShards;
+  const size_t seg = (size_t)shard * P.seg_cap;
+  const uint64_t m_cont = __ballot(o.cont), m_sh = __ballot(o.shadow), m_q = __ballot(o.query);
+  const int w = (int)(threadIdx.x >> 6);
+  if (lane_id() == 0) {
+    s_app[0][w] = (uint32_t)__popcll(m_cont);
+    s_app[1][w] = (uint32_t)__popcll(m_sh);
+    s_app[2][w] = (uint32_t)__popcll(m_q);
+  }
+  __syncthreads();
+  if (threadIdx.x < 3) {
+    uint32_t tot = 0;
+    for (int k = 0; k < kShadeBlock / 64; ++k) tot += s_app[threadIdx.x][k];
+    uint32_t* ctr = threadIdx.x == 0   ? &P.counts[count_ray(shard, next)]
+                    : threadIdx.x == 1 ? &P.counts[count_shadow(shard)]
+                                       : &P.counts[kCountQuery];
+    s_app[threadIdx.x][kShadeBlock / 64] = tot ? atomicAdd(ctr, tot) : 0u;
+  }
+  __syncthreads();
+  uint32_t off[3];
+  for (int q = 0; q < 3; ++q) {
+    uint32_t acc = s_app[q][kShadeBlock / 64];
+    for (int k = 0; k < w; ++k) acc += s_app[q][k];
+    off[q] = acc;
+  }
+  __syncthreads();  // s_app is rewritten by the next iteration
+  if (o.cont) P.q_ray[next][seg + off[0] + lane_prefix(m_cont)] = slot;
+  if (o.query) P.q_nrc[off[2] + lane_prefix(m_q)] = slot;
+  if (o.shadow) {
+    const size_t spos = seg + off[1] + lane_prefix(m_sh);
+    P.sh_o[spos] = o.sh_o;
+    P.sh_d[spos] = o.sh_d;
+    P.sh_c[spos] = o.sh_c;
+    if (TWO) P.sh_inst[spos] = o.sh_inst;
+  }
+}
+
 // Waves per SIMD that the shading kernel of a class is compiled for: 4 (128
-// registers), 3 for the general class, which needs 165 and would keep 144 bytes a
-// lane in scratch (material zoo 1024x768, 40 spp, its launches 6.52 ms at 4, 5.99
+// registers), 3 for the general class, which needs 153 and would keep some in
+// scratch (material zoo 1024x768, 40 spp, its launches 6.52 ms at 4, 5.99
 // at 3; coated 1.49 / 1.57, glass 0.58 / 0.64; instanced scene glass 3.55 / 3.97).
 // Icosphere field render at 3 / 4 / 5 / 6: 89.1 / 88.4 / 94.5 / 99.5 ms.
 constexpr int shade_waves(int cls) { return cls == kClsGeneral ? 3 : 4; }
@@ -1104,56 +1174,35 @@ template <int CLS, bool DEBUG, bool TWO>
 __global__ __launch_bounds__(kShadeBlock, shade_waves(CLS)) void k_shade(SceneDev S, PathsDev P, int b, int max_depth, int next,
                                                   uint32_t sample, uint32_t k0, uint32_t k1,
                                                   int nrc_bounce) {
-  // per queue (next rays, shadow rays, cache queries): wave counts, then the workgroup's base
-  __shared__ uint32_t s_app[3][kShadeBlock / 64 + 1];
+  __shared__ ShadeAppend s_app;
   const uint32_t count = P.counts[count_class(CLS)];
   unsigned long long nonfinite = 0;
-  for (uint32_t base = blockIdx.x * kShadeBlock; base < count; base += gridDim.x * kShadeBlock) {
-    uint32_t i = base + threadIdx.x;
-    bool active = i < count;
-    uint32_t slot = 0;
-    ShadeOut o;
-    o.cont = o.shadow = o.query = false;
-    if (active) {
-      slot = P.q_cls[CLS][i];
+  for (uint32_t base = blockIdx.x * kShadeBlock; base < count; base += gridDim.x * kShadeBlock)
+    shade_tile<TWO>(P, P.q_cls[CLS], count, base, next, s_app, [&](uint32_t slot, ShadeOut& o) {
       shade_one<CLS, DEBUG, TWO>(S, P, slot, b, max_depth, sample, k0, k1, nrc_bounce, o, nonfinite);
-    }
-    // one atomic per queue per workgroup iteration
-    const uint32_t shard = base / kShadeBlock % kShards;
-    const size_t seg = (size_t)shard * P.seg_cap;
-    const uint64_t m_cont = __ballot(o.cont), m_sh = __ballot(o.shadow), m_q = __ballot(o.query);
-    const int w = (int)(threadIdx.x >> 6);
-    if (lane_id() == 0) {
-      s_app[0][w] = (uint32_t)__popcll(m_cont);
-      s_app[1][w] = (uint32_t)__popcll(m_sh);
-      s_app[2][w] = (uint32_t)__popcll(m_q);
-    }
-    __syncthreads();
-    if (threadIdx.x < 3) {
-      uint32_t tot = 0;
-      for (int k = 0; k < kShadeBlock / 64; ++k) tot += s_app[threadIdx.x][k];
-      uint32_t* ctr = threadIdx.x == 0   ? &P.counts[count_ray(shard, next)]
-                      : threadIdx.x == 1 ? &P.counts[count_shadow(shard)]
-                                         : &P.counts[kCountQuery];
-      s_app[threadIdx.x][kShadeBlock / 64] = tot ? atomicAdd(ctr, tot) : 0u;
-    }
-    __syncthreads();
-    uint32_t off[3];
-    for (int q = 0; q < 3; ++q) {
-      uint32_t acc = s_app[q][kShadeBlock / 64];
-      for (int k = 0; k < w; ++k) acc += s_app[q][k];
-      off[q] = acc;
-    }
-    __syncthreads();  // s_app is rewritten by the next iteration
-    if (o.cont) P.q_ray[next][seg + off[0] + lane_prefix(m_cont)] = slot;
-    if (o.query) P.q_nrc[off[2] + lane_prefix(m_q)] = slot;
-    if (o.shadow) {
-      const size_t spos = seg + off[1] + lane_prefix(m_sh);
-      P.sh_o[spos] = o.sh_o;
-      P.sh_d[spos] = o.sh_d;
-      P.sh_c[spos] = o.sh_c;
-      if (TWO) P.sh_inst[spos] = o.sh_inst;
-    }
+    });
+  if (nonfinite) atomicAdd(&P.stats[kStatNonFinite], nonfinite);
+}
+
+// All classes in one launch, for passes of few slots, whose launches last as long as one path's
+// chain of dependent loads: a workgroup takes blocks of the class queues one after the other, each
+// of one class, so that no wave runs the code of two (shade_all says up to which size, with figures).
+template <bool DEBUG, bool TWO>
+__global__ __launch_bounds__(kShadeBlock) void k_shade_classes(SceneDev S, PathsDev P, int b, int max_depth, int next,
+                                                               uint32_t sample, uint32_t k0, uint32_t k1,
+                                                               int nrc_bounce) {
+  __shared__ ShadeAppend s_app;
+  unsigned long long nonfinite = 0;
+  uint32_t first = 0;  // blocks of the classes before
+  for (int cls = 0; cls < kNumClasses; ++cls) {
+    const uint32_t count = P.counts[count_class(cls)], blocks = (count + kShadeBlock - 1) / kShadeBlock;
+    // this workgroup's first block of the class: those it takes are blockIdx.x, + gridDim.x, ... of all classes'
+    uint32_t k = (blockIdx.x + gridDim.x - first % gridDim.x) % gridDim.x;
+    for (; k < blocks; k += gridDim.x)
+      shade_tile<TWO>(P, P.q_cls[cls], count, k * kShadeBlock, next, s_app, [&](uint32_t slot, ShadeOut& o) {
+        shade_any<DEBUG, TWO>(cls, S, P, slot, b, max_depth, sample, k0, k1, nrc_bounce, o, nonfinite);
+      });
+    first += blocks;
   }
   if (nonfinite) atomicAdd(&P.stats[kStatNonFinite], nonfinite);
 }
@@ -1299,22 +1348,6 @@ __global__ __launch_bounds__(kBlock, TWO ? kTraceWaves2 : kTraceWaves) void k_tr
 // shadow ray, next ray) with no kernel boundary between vertices, so short
 // paths do not wait for the slowest ray of every later bounce.  Shading,
 // walks and signatures are the same code as the wavefront kernels'.
-template <bool DEBUG, bool TWO>
-__device__ inline void shade_any(int cls, const SceneDev& S, const PathsDev& P, uint32_t slot, int b, int max_depth,
-                                 uint32_t sample, uint32_t k0, uint32_t k1, int nrc_bounce,
-                                 ShadeOut& o, unsigned long long& nf) {
-  const int q = nrc_bounce;
-  switch (cls) {
-    case kClsMiss: shade_one<kClsMiss, DEBUG, TWO>(S, P, slot, b, max_depth, sample, k0, k1, q, o, nf); break;
-    case kClsAbsorb: shade_one<kClsAbsorb, DEBUG, TWO>(S, P, slot, b, max_depth, sample, k0, k1, q, o, nf); break;
-    case kClsDiffuse: shade_one<kClsDiffuse, DEBUG, TWO>(S, P, slot, b, max_depth, sample, k0, k1, q, o, nf); break;
-    case kClsMetal: shade_one<kClsMetal, DEBUG, TWO>(S, P, slot, b, max_depth, sample, k0, k1, q, o, nf); break;
-    case kClsPlastic: shade_one<kClsPlastic, DEBUG, TWO>(S, P, slot, b, max_depth, sample, k0, k1, q, o, nf); break;
-    case kClsGlass: shade_one<kClsGlass, DEBUG, TWO>(S, P, slot, b, max_depth, sample, k0, k1, q, o, nf); break;
-    default: shade_one<kClsGeneral, DEBUG, TWO>(S, P, slot, b, max_depth, sample, k0, k1, q, o, nf); break;
-  }
-}
-
 template <bool DEBUG, bool COUNT, bool TWO>
 __global__ __launch_bounds__(kBlock) void k_tail(SceneDev S, PathsDev P, int cur, int b_first, int max_depth,
                                                  uint32_t sample, uint32_t k0, uint32_t k1,
@@ -1740,10 +1773,23 @@ int traversal_grid(int64_t rays, bool two_level) {
 // chip, and side by side on three streams they took as long together (33M
 // paths: 3.45 ms either way) plus 20-30 us a vertex for the joins (box 512x512,
 // 64 spp 5.86 ms against 5.32, icosphere field 13.4 / 13.0, material zoo 16.5 /
-// 15.5; the zoo's seven small launches at 524K slots 1.77 / 1.92).
+// 15.5).  In a pass of up to kOneShadeSlots slots no class fills it, and each
+// launch lasts as long as one path's chain; all classes then share one launch.
+// A wavefront render of one sample and 6 bounces in us, one launch each / one in
+// all: zoo 64x64 1488 / 1074, 512x512 1714 / 1188, 1024x1024 2225 / 1786; field
+// (82K triangles) 1206 / 1019, 1645 / 1461, 2173 / 1961; instanced 2973 / 2633, 2769 /
+// 2380, 3628 / 3312; box 304 / 280, 424 / 398, 630 / 611.  From there on a scene
+// of few classes loses to the lower occupancy (164 registers for every class):
+// 2048x1024 with the hand-off, box 696 / 713, field 2475 / 2435.
+static constexpr int32_t kOneShadeSlots = 1 << 20;
 template <bool DEBUG, bool TWO>
 static hipError_t shade_all(const SceneDev& S, const PathsDev& P, const PassArgs& A, int b, int next, hipStream_t st) {
   dim3 g(std::max(1, A.grid * kBlock / kShadeBlock)), blk(kShadeBlock);
+  if (P.n <= kOneShadeSlots && __builtin_popcount(A.class_mask) > 2) {
+    hipLaunchKernelGGL((k_shade_classes<DEBUG, TWO>), g, blk, 0, st, S, P, b, A.max_depth, next, A.sample, A.k0, A.k1,
+                       A.nrc_bounce);
+    return hipGetLastError();
+  }
   for (int c = 0; c < kNumClasses; ++c) {
     if (!(A.class_mask & (1u << c))) continue;
     switch (c) {

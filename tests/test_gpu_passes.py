@@ -60,3 +60,27 @@ def test_sums_do_not_depend_on_the_grouping(scene, w, h, spp):
         sg = torch.empty((h - 2, w - 2, spp), dtype=torch.int64, device="cuda:0")
         s.render_debug(cam, 1, 2, w - 2, h - 2, 3, spp, 4, 11, pc, sg)
         assert torch.equal(pc, per[2:, 1:w - 1]) and torch.equal(sg, sig[2:, 1:w - 1])
+
+
+@pytest.mark.parametrize("which", ["material_zoo", "instanced", "cornell"])
+def test_one_shading_launch_equals_one_per_class(which):
+    """Passes of at most 2^20 slots shade all material classes in one launch, larger ones launch a
+    kernel per class: three samples of 640x640 (1.23M slots) in one pass against one by one."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    print(f"[passes] {which} 640x640, 3 spp, classes", flush=True)
+    from paper_2407_19977_amd import pt, scenes
+    sc = getattr(scenes, which)()
+    cam = sc.with_camera(width=640, height=640).camera
+    s = pt.scene_from(sc, device=0)
+    mean = torch.empty((640, 640, 3), dtype=torch.float32, device="cuda:0")
+    sums = [torch.empty((640, 640, 3), dtype=torch.float64, device="cuda:0") for _ in range(2)]
+    s.set_tail(0, 0.0)  # every vertex in the wavefront kernels
+    s.accumulate(cam, 0, 3, 6, 11)
+    s.resolve(mean, sums[0])
+    s.reset_accumulation()
+    for k in range(3):
+        s.accumulate(cam, k, 1, 6, 11)
+    s.resolve(mean, sums[1])
+    s.close()
+    assert torch.equal(sums[0], sums[1])
