@@ -400,9 +400,9 @@ pt_status pt_nrc_training_records(pt_scene* scene, const pt_camera* camera, int3
  * per bounce.  The decision reads the queue counts (2 KB) back once per
  * bounce from min_bounce on.  Defaults: min_bounce 2, max_fraction 0.15; with
  * these the fraction counts from at most 2^21 paths (a pass may hold several
- * samples of every pixel), and a pass of at most 327,680 paths runs in the
- * persistent kernel from its first vertex, unless the next pass overlaps it
- * (frames of the radiance cache).  max_fraction 0 (or min_bounce > 64) keeps
+ * samples of every pixel), and a pass of at most 327,680 paths may run in the
+ * persistent kernel from its first vertex (where that was measured to be
+ * faster: by depth, materials and training paths).  max_fraction 0 (or min_bounce > 64) keeps
  * the wavefront throughout.  Results are identical either way (same
  * arithmetic, same random numbers).  Errors: INVALID_ARG for min_bounce < 0
  * or max_fraction outside [0, 1]. */

@@ -187,7 +187,7 @@ struct PassArgs {
   // tail hand-off: from bounce tail_min_bounce on, when at most tail_fraction of the slots are still
   // alive, one persistent kernel finishes the paths
   uint32_t* tail_host_count;  // kShardWords pinned words
-  bool tail_sized;            // the defaults: passes of few and of many slots have rules of their own
+  bool tail_sized;            // the defaults: passes of few and of many slots have rules of their own (whole_pass)
   int tail_min_bounce;
   double tail_fraction;
   hipEvent_t* tail_events;  // 2 events around the tail kernel when timing, else nullptr

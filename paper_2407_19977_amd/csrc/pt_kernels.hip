@@ -1820,20 +1820,34 @@ static hipError_t shade_all(const SceneDev& S, const PathsDev& P, const PassArgs
 // slots) 121.9; instanced scene 32 spp: 151.7 / 153.7 / 150.8 / 153.7 ms.
 static constexpr int32_t kTailPassSlots = 1 << 21;
 // And a pass of few slots runs in the tail kernel from its first vertex: the
-// wavefront's launches, stream joins and count reads take longer than its
-// better lane use saves.  Render in us, wavefront first / whole pass: box 262K
-// slots 538 / 324, 524K 565 / 455, 1M 704 / 740; material zoo 262K 1673 / 1439,
-// 524K 1784 / 2097; icosphere field (1.31M triangles) 16K 1346 / 837, 262K 1532 /
-// 1069, 524K 1716 / 1528, 1M 2027 / 2468; instanced 262K 2689 / 2067, 524K 2998 /
-// 3247.
-// Not so a pass beside which the next one runs (the frames of the radiance
-// cache): whole passes would follow each other on the second stream, on the
-// part of the chip that the tail kernel leaves them (tail_grid).  Eight frames
-// of 6 bounces, 65,536 training paths, in us, whole / wavefront first: box
-// 320x240 3735 / 3859, 640x400 4364 / 3986; material zoo 12868 / 13825, 18152 /
-// 14572; icosphere field 10131 / 11086, 14400 / 10839; instanced 18005 / 19916,
-// 26278 / 20856; with 512 training paths the zoo at 160x120 11611 / 9298.
+// wavefront's launches and count reads take longer than its better lane use
+// saves.  Render of 6 bounces in us, hand-off from vertex 2 / whole pass: box 262K
+// slots 437 / 312, 524K 490 / 455; material zoo 1485 / 1410, 1648 / 2097; icosphere
+// field (1.31M triangles) 16K 1236 / 857, 262K 1458 / 1064, 524K 1665 / 1528;
+// instanced 262K 2529 / 2083, 524K 2835 / 3247.
+// Not so short paths where the general class is among the materials: a wave of
+// the tail kernel runs the code of every class its lanes wait for (zoo 640x512,
+// one sample: 2 bounces 599 / 948, 3 777 / 1168, 4 1016 / 1333; at 5 bounces 1444
+// whole, 1459 with three streams and a hand-off).
+// A frame of the radiance cache, beside which the next one runs, is whole where
+// its training paths, which live longest, are a third of it or more, and then on
+// the whole chip: the following frames queue behind it on the second stream.
+// Eight frames, 65,536 training paths, 6 bounces, in us, wavefront first / whole:
+// box 160x120 3437 / 3356, 400x300 3540 / 3655, 640x400 3693 / 4057; zoo 13234 / 11373,
+// 13799 / 11979, 14343 / 14132; field 10463 / 8924, 10037 / 9287, 10026 / 10940;
+// instanced 16166 / 15908, 18828 / 16799, 20019 / 19928.  160x120, 3 bounces: zoo
+// 6184 / 8026, field 7878 / 7623, instanced 10616 / 11257.  64x48, 8,192 training
+// paths: zoo 10151 / 12087, field 8389 / 8487, instanced 12889 / 16630.
 static constexpr int32_t kWholePassSlots = 5 << 16;
+static constexpr int32_t kWholeFrameSlots = 3 << 16;
+static constexpr uint32_t kWholeTrainPaths = 1u << 15;
+static constexpr int kWholeDepth = 5;
+static bool whole_pass(const PathsDev& P, const PassArgs& A) {
+  if (!A.tail_sized) return false;
+  const bool deep = A.max_depth >= kWholeDepth;
+  if (!A.tail_stream) return P.n <= kWholePassSlots && (deep || !(A.class_mask & (1u << kClsGeneral)));
+  return deep && P.n <= kWholeFrameSlots && A.tail_bound >= kWholeTrainPaths && 3u * A.tail_bound >= (uint32_t)P.n;
+}
 
 template <bool DEBUG, bool COUNT, bool TWO>
 static hipError_t bounce_loop(const SceneDev& S, const PathsDev& P, const CamDev& C, const PassArgs& A,
@@ -1861,9 +1875,9 @@ static hipError_t bounce_loop(const SceneDev& S, const PathsDev& P, const CamDev
     return e2;
   };
   const double tail_limit = A.tail_fraction * (double)(A.tail_sized ? std::min(P.n, kTailPassSlots) : P.n);
+  const bool whole = whole_pass(P, A);
   for (int b = 0; b <= A.max_depth; ++b) {
     const int next = (b & 1) ^ 1, cur = b == 0 ? kQueueAll : b & 1;
-    const bool whole = A.tail_sized && !A.tail_stream && P.n <= kWholePassSlots;
     if (A.tail_host_count && (whole || b >= A.tail_min_bounce)) {
       // hand the remaining vertices to one persistent kernel once few paths are left
       uint32_t alive = 0;
@@ -1901,7 +1915,7 @@ static hipError_t bounce_loop(const SceneDev& S, const PathsDev& P, const CamDev
         hipLaunchKernelGGL(k_zero_u32, dim3(1), dim3(1), 0, ts, P.counts + kCountTail);
         if (A.tail_events) hipEventRecord(A.tail_events[0], ts);
         hipLaunchKernelGGL((k_tail<DEBUG, COUNT, TWO>),
-                           dim3(tail_grid(A.grid_trace, alive, A.tail_stream != nullptr)), blk, 0, ts,
+                           dim3(tail_grid(A.grid_trace, alive, A.tail_stream && !whole)), blk, 0, ts,
                            S, P, cur, b, A.max_depth, A.sample, A.k0, A.k1, A.nrc_bounce);
         if (A.tail_events) hipEventRecord(A.tail_events[1], ts);
         if (A.nrc_bounce >= 0 && b <= A.nrc_bounce) {

@@ -606,11 +606,11 @@ def test_overlapped_frames_equal_frame_by_frame(P, O):
     s.set_radiance_cache(None)
 
 
-@pytest.mark.parametrize("w,h,train", [(96, 64, 512), (704, 512, 65536)])
+@pytest.mark.parametrize("w,h,train", [(96, 64, 512), (256, 256, 32768), (256, 257, 32768), (352, 372, 65536), (704, 512, 65536)])
 def test_overlapped_frames_of_any_size_keep_the_bits(P, O, w, h, train):
-    """Frames below and above the size up to which a pass may run whole in the persistent kernel
-    (327,680 slots; 704x512 with 65,536 training paths has 425,984): overlapped, one call per frame,
-    and with the hand-over off.  Sums, weights, Adam moments and counts must be the same bits."""
+    """Frames on either side of the edges up to which they run whole in the persistent kernel (a third
+    of the slots training paths; 196,608 slots) and far above: overlapped, one call per frame, and
+    with the hand-over off.  Sums, weights, Adam moments and counts must be the same bits."""
     _say(f"[nrc overlap] box scene {w}x{h}, 4 frames, {train} training paths")
     sc = scenes.cornell(width=w, height=h)
     cfg = P.cache_config(train_paths=train, batch_size=2048, steps_per_frame=2)
