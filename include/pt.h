@@ -194,9 +194,14 @@ pt_status pt_set_environment(pt_scene* scene, const float* rgb32f, int32_t w, in
 /* Render: reset the FP64 per-pixel sums, accumulate samples [0, spp) of
  * every pixel with paths of at most max_depth scattering events, and write
  * the per-pixel mean to out_rgb32f (device, [height][width][3] float).
- * seed keys the Philox stream.  Errors: INVALID_ARG (camera, spp <= 0,
- * max_depth outside [0, 64], out == NULL), STATE (no BVH or materials,
- * a material id >= the material count), DEVICE. */
+ * seed keys the Philox stream.  A pass holds up to 2^25 paths (5.3 GB on a
+ * scene with one mesh), and a call of several passes two such sets, which the
+ * scene keeps for its next calls.  Passes are smaller where the device would
+ * not be left as much free memory as they hold; a scene's other allocations
+ * get the memory of its idle sets where the device has none left.
+ * Errors: INVALID_ARG (camera, spp <= 0, max_depth outside [0, 64],
+ * out == NULL), STATE (no BVH or materials, a material id >= the material
+ * count), DEVICE. */
 pt_status pt_render(pt_scene* scene, const pt_camera* camera, int32_t spp, int32_t max_depth,
                     uint64_t seed, float* out_rgb32f);
 

@@ -68,13 +68,6 @@ struct DevBuf {
   }
 };
 
-hipError_t upload(DevBuf& b, const void* src, size_t n, hipStream_t st) {
-  hipError_t e = b.alloc(n);
-  if (e != hipSuccess) return e;
-  if (n) e = hipMemcpyAsync(b.p, src, n, hipMemcpyHostToDevice, st);
-  return e;
-}
-
 double lumd(double r, double g, double b) { return 0.2126 * r + 0.7152 * g + 0.0722 * b; }
 
 bool finite_all(const float* p, size_t n) {
@@ -159,7 +152,6 @@ struct pt_scene {
   DevBuf nrc_tail[2];  // per training path: beta * cache at its terminal vertex (self-training), per path set
   DevBuf nrc_rec[2];       // training records, per path set (frames overlap on two sets)
   DevBuf nrc_off, nrc_bsum, nrc_n, nrc_X, nrc_T;  // compaction
-  int64_t nrc_rec_cap = 0;
   DevBuf nrc_Xb, nrc_Tb, nrc_a, nrc_g, nrc_loss, nrc_dw;  // one training step's workspace
   int64_t nrc_ws_npad = 0;
   int nrc_ws_split = 0;
@@ -191,6 +183,42 @@ pt_status check_scene(pt_scene* s) {
 pt_status set_device(pt_scene* s) {
   PT_HIP(hipSetDevice(s->device));
   return PT_OK;
+}
+
+// What of a path set every pass allocates again as it needs it.
+template <class F>
+void for_path_buffers(PathBufs& B, F f) {
+  for (DevBuf* b : {&B.path, &B.hit_inst, &B.cls, &B.L, &B.eta, &B.q_ray[0], &B.q_ray[1], &B.sh_o, &B.sh_d, &B.sh_c,
+                    &B.sh_inst, &B.sig, &B.dbg_nee, &B.dbg_tail, &B.spill, &B.spread, &B.nrc_q, &B.q_nrc})
+    f(*b);
+  for (DevBuf& b : B.q_cls) f(b);
+}
+
+size_t path_bytes(pt_scene* s) {
+  size_t n = 0;
+  for (PathBufs& B : s->pb) for_path_buffers(B, [&](DevBuf& b) { n += b.bytes; });
+  return n;
+}
+
+// Gives the path sets' memory back to the device; true if there was any.  Nothing may be in flight on them.
+bool give_back(pt_scene* s) {
+  if (!path_bytes(s)) return false;
+  for (PathBufs& B : s->pb) for_path_buffers(B, [](DevBuf& b) { b.release(); });
+  return true;
+}
+
+// alloc(), and once more without the idle path sets where the device has no memory left.
+template <class F>
+hipError_t with_memory(pt_scene* s, F alloc) {
+  hipError_t e = alloc();
+  return e == hipErrorOutOfMemory && give_back(s) ? alloc() : e;
+}
+
+// Between calls of the sampling passes only (with_memory).
+hipError_t upload(pt_scene* s, DevBuf& b, const void* src, size_t n) {
+  hipError_t e = with_memory(s, [&] { return b.alloc(n); });
+  if (e == hipSuccess && n) e = hipMemcpyAsync(b.p, src, n, hipMemcpyHostToDevice, s->stream);
+  return e;
 }
 
 // Scene box from exact vertex bounds; an axis of zero extent maps to 0.
@@ -250,7 +278,7 @@ pt_status ensure_lights(pt_scene* s) {
     uint32_t n_list = 0;
     if (any) {
       DevBuf demits, doff, dsums, dlist;
-      PT_HIP(upload(demits, emits.data(), emits.size() * sizeof(uint32_t), s->stream));
+      PT_HIP(upload(s, demits, emits.data(), emits.size() * sizeof(uint32_t)));
       PT_HIP(doff.alloc((size_t)(n_tri + 1) * sizeof(uint32_t)));
       PT_HIP(dsums.alloc(gpu_count_lights_scratch(n_tri) * sizeof(uint32_t)));
       PT_HIP(gpu_count_lights(s->tris.as<TriRec>(), n_tri, demits.as<uint32_t>(), (uint32_t)emits.size(),
@@ -331,11 +359,11 @@ pt_status ensure_lights(pt_scene* s) {
   }
   s->n_lights = (int32_t)lt.size();
   s->p_env = (float)p_env;
-  PT_HIP(upload(s->lights, lt.data(), lt.size() * sizeof(LightTri), s->stream));
-  PT_HIP(upload(s->light_cdf, cdf.data(), cdf.size() * sizeof(float), s->stream));
-  PT_HIP(upload(s->light_map, lmap.data(), lmap.size() * sizeof(int32_t), s->stream));
+  PT_HIP(upload(s, s->lights, lt.data(), lt.size() * sizeof(LightTri)));
+  PT_HIP(upload(s, s->light_cdf, cdf.data(), cdf.size() * sizeof(float)));
+  PT_HIP(upload(s, s->light_map, lmap.data(), lmap.size() * sizeof(int32_t)));
   if (s->two_level)
-    PT_HIP(upload(s->insts, s->host_insts.data(), s->host_insts.size() * sizeof(InstRec), s->stream));
+    PT_HIP(upload(s, s->insts, s->host_insts.data(), s->host_insts.size() * sizeof(InstRec)));
   PT_HIP(hipStreamSynchronize(s->stream));
   s->lights_dirty = false;
   return PT_OK;
@@ -373,18 +401,6 @@ hipError_t alloc_paths(pt_scene* s, int64_t n, int set, bool debug) {
   return e;
 }
 
-void release_paths(PathBufs& B) {
-  for (DevBuf* b : {&B.path, &B.hit_inst, &B.cls, &B.L, &B.eta, &B.q_ray[0], &B.q_ray[1], &B.sh_o, &B.sh_d, &B.sh_c, &B.sh_inst, &B.sig, &B.dbg_nee, &B.dbg_tail, &B.spread,
-                    &B.nrc_q, &B.q_nrc})
-    b->release();
-  for (DevBuf& b : B.q_cls) b.release();
-}
-
-pt_status ensure_paths(pt_scene* s, int64_t n, int set = 0, bool debug = false) {
-  PT_HIP(alloc_paths(s, n, set, debug));
-  return PT_OK;
-}
-
 int bin_grid(int64_t n) {  // 4096 rays per workgroup iteration; whole rounds over the queue segments
   return (int)(std::max<int64_t>(1, std::min<int64_t>((n + 4095) / 4096 + kShards - 1, 2048) / kShards) * kShards);
 }
@@ -414,8 +430,8 @@ hipError_t alloc_spill(pt_scene* s, int grid_trace, int set) {
   return s->pb[set].spill.alloc(bytes);
 }
 
-pt_status ensure_spill(pt_scene* s, int grid_trace, int set = 0) {
-  PT_HIP(alloc_spill(s, grid_trace, set));
+pt_status ensure_spill(pt_scene* s, int grid_trace) {
+  PT_HIP(with_memory(s, [&] { return alloc_spill(s, grid_trace, 0); }));
   return PT_OK;
 }
 
@@ -548,6 +564,18 @@ pt_status ready_to_render(pt_scene* s) {
   return ensure_lights(s);
 }
 
+// Buffers of a frame's training paths and their records (path set `set`).
+hipError_t alloc_training(pt_scene* s, int max_depth, int set) {
+  const size_t n = (size_t)s->nrc_cfg.train_paths, rows = n * (size_t)std::max(1, max_depth);
+  hipError_t e = s->nrc_rec[0].alloc(rows * kNrcRecFloats * sizeof(float));
+  if (e == hipSuccess && (set == 1 || s->nrc_rec[1].p)) e = s->nrc_rec[1].alloc(rows * kNrcRecFloats * sizeof(float));
+  if (e == hipSuccess) e = s->nrc_X.alloc(rows * 12 * sizeof(float));
+  if (e == hipSuccess) e = s->nrc_T.alloc(rows * 3 * sizeof(float));
+  if (e == hipSuccess) e = s->nrc_off.alloc(n * sizeof(uint32_t));
+  if (e == hipSuccess) e = s->nrc_bsum.alloc((n + 255) / 256 * sizeof(uint32_t));
+  return e == hipSuccess ? s->nrc_n.alloc(sizeof(uint32_t)) : e;
+}
+
 // Training paths of a frame appended to a pass as slots [n_render, n_render + paths):
 // path k starts at pixel (k * stride + o_f) mod WH, stride = max(1, floor(WH / paths)),
 // o_f = floor(m * WH / 2^24) with m the top 24 bits of Philox word 0 at counter
@@ -556,18 +584,7 @@ pt_status ready_to_render(pt_scene* s) {
 pt_status setup_training(pt_scene* s, const CamDev& C, PathsDev& P, int64_t n_render, uint32_t frame, int max_depth,
                          uint64_t seed, int set = 0) {
   const int64_t n = s->nrc_cfg.train_paths;
-  const int depth = std::max(1, max_depth);
-  if (n * depth > s->nrc_rec_cap) {
-    PT_HIP(s->nrc_rec[0].alloc((size_t)n * depth * kNrcRecFloats * sizeof(float)));
-    if (s->nrc_rec[1].p) PT_HIP(s->nrc_rec[1].alloc((size_t)n * depth * kNrcRecFloats * sizeof(float)));
-    PT_HIP(s->nrc_X.alloc((size_t)n * depth * 12 * sizeof(float)));
-    PT_HIP(s->nrc_T.alloc((size_t)n * depth * 3 * sizeof(float)));
-    s->nrc_rec_cap = n * depth;
-  }
-  if (set == 1 && !s->nrc_rec[1].p) PT_HIP(s->nrc_rec[1].alloc(s->nrc_rec[0].bytes));
-  PT_HIP(s->nrc_off.alloc((size_t)n * sizeof(uint32_t)));
-  PT_HIP(s->nrc_bsum.alloc((size_t)((n + 255) / 256) * sizeof(uint32_t)));
-  if (!s->nrc_n.p) PT_HIP(s->nrc_n.alloc(sizeof(uint32_t)));
+  PT_HIP(alloc_training(s, max_depth, set));
   const uint64_t WH = (uint64_t)C.W * (uint64_t)C.H;
   P.n = (int32_t)(n_render + n);
   P.n_render = (int32_t)n_render;
@@ -683,7 +700,9 @@ pt_status run_passes(pt_scene* s, const CamDev& C, int x0, int y0, int w, int h,
   int64_t slots = 0;
   int n_passes = 0, nsets = 1;
   bool overlap = false;
+  bool held = path_bytes(s) > 0;  // memory of other calls, which one-sample passes may have back
   while (true) {
+    const size_t had = path_bytes(s);
     n_passes = (n + spp_max - 1) / spp_max;
     slots = N * spp_max + (train ? s->nrc_cfg.train_paths : 0);
     overlap = !train && !use_cache && tail && n_passes > 1;
@@ -693,12 +712,24 @@ pt_status run_passes(pt_scene* s, const CamDev& C, int x0, int y0, int w, int h,
       e = alloc_paths(s, slots, set, per_sample != nullptr);
       if (e == hipSuccess) e = alloc_spill(s, traversal_grid(slots, s->two_level), set);
       if (e == hipSuccess && use_cache) e = alloc_queries(s, N * spp_max, set);
+      if (e == hipSuccess && train) e = alloc_training(s, max_depth, set);
     }
-    if (e == hipSuccess) break;
-    // the device has less memory left than these passes need: smaller passes
-    if (e != hipErrorOutOfMemory || spp_max == 1) PT_HIP(e);
-    for (PathBufs& B : s->pb) release_paths(B);
-    spp_max = pass_samples(N, n, N * ((spp_max + 1) / 2));
+    if (e == hipSuccess) {
+      // passes of several samples leave the device at least as much free memory as they hold
+      const size_t hold = path_bytes(s);
+      size_t avail = 0, total = 0;
+      if (spp_max == 1 || hold <= had || hipMemGetInfo(&avail, &total) != hipSuccess || avail >= hold) break;
+    } else if (e != hipErrorOutOfMemory) {
+      PT_HIP(e);
+    }
+    give_back(s);
+    if (spp_max > 1) {  // smaller passes
+      spp_max = pass_samples(N, n, N * ((spp_max + 1) / 2));
+    } else if (held) {
+      held = false;
+    } else {
+      PT_HIP(e);
+    }
   }
   int grid = grid_for(slots), grid_trace = traversal_grid(slots, s->two_level);
   pt_status r = PT_OK;
@@ -831,11 +862,19 @@ pt_status run_cache_frames(pt_scene* s, const CamDev& C, int first, int n, int m
   int grid = grid_for(slots), grid_trace = traversal_grid(slots, s->two_level);
   pt_status r = PT_OK;
   PathsDev Ps[2];
-  for (int set = 0; set < 2; ++set) {  // every allocation before the first launch
-    if ((r = ensure_paths(s, slots, set))) return r;
+  // every allocation before the first launch
+  PT_HIP(with_memory(s, [&] {
+    hipError_t e = hipSuccess;
+    for (int set = 0; set < 2; ++set) {
+      if (e == hipSuccess) e = alloc_paths(s, slots, set, false);
+      if (e == hipSuccess) e = alloc_spill(s, grid_trace, set);
+      if (e == hipSuccess) e = alloc_queries(s, N, set);
+      if (e == hipSuccess) e = alloc_training(s, max_depth, set);
+    }
+    return e;
+  }));
+  for (int set = 0; set < 2; ++set) {
     if ((r = ensure_counters(s, set))) return r;
-    if ((r = ensure_spill(s, grid_trace, set))) return r;
-    PT_HIP(alloc_queries(s, N, set));
     Ps[set] = paths_dev(s, 0, 0, C.W, C.H, 1, set);
     if ((r = setup_training(s, C, Ps[set], N, (uint32_t)first, max_depth, seed, set))) return r;
   }
@@ -1034,11 +1073,14 @@ pt_status nrc_read_loss(pt_scene* s, int grid, int64_t N, double* loss, hipStrea
 pt_status nrc_trace_training(pt_scene* s, const CamDev& C, uint32_t frame, int max_depth, uint64_t seed,
                              uint32_t* n_records) {
   const int64_t n = s->nrc_cfg.train_paths;
-  pt_status r = ensure_paths(s, n);
-  if (r) return r;
-  if ((r = ensure_counters(s))) return r;
   int grid = grid_for(n), grid_trace = traversal_grid(n, s->two_level);
-  if ((r = ensure_spill(s, grid_trace))) return r;
+  PT_HIP(with_memory(s, [&] {
+    hipError_t e = alloc_paths(s, n, 0, false);
+    if (e == hipSuccess) e = alloc_spill(s, grid_trace, 0);
+    return e == hipSuccess ? alloc_training(s, max_depth, 0) : e;
+  }));
+  pt_status r = ensure_counters(s);
+  if (r) return r;
   SceneDev S = scene_dev(s, grid_trace);
   PathsDev P = paths_dev(s, 0, 0, 1, 0, 1);
   if ((r = setup_training(s, C, P, 0, frame, max_depth, seed))) return r;
@@ -1110,7 +1152,7 @@ pt_status check_render_args(int spp, int max_depth) {
 
 pt_status ensure_accum(pt_scene* s, int W, int H) {
   if (s->acc_w != W || s->acc_h != H || !s->sum.p) {
-    PT_HIP(s->sum.alloc((size_t)W * H * 3 * sizeof(double)));
+    PT_HIP(with_memory(s, [&] { return s->sum.alloc((size_t)W * H * 3 * sizeof(double)); }));
     PT_HIP(launch_zero_f64(s->sum.as<double>(), (int64_t)W * H * 3, s->stream));
     s->acc_w = W;
     s->acc_h = H;
@@ -1417,15 +1459,19 @@ bool gpu_mesh_bvh(pt_scene* s, const float* v, const uint32_t* prim, const uint3
   auto t0 = std::chrono::steady_clock::now();
   DevBuf dsoup, dprim, dmat, dnodes, dtris;
   const int64_t nn = std::max<int64_t>(1, n - 1);
-  hipError_t e = upload(dsoup, v, (size_t)n * 9 * sizeof(float), s->stream);
-  if (e == hipSuccess) e = upload(dprim, prim, (size_t)n * sizeof(uint32_t), s->stream);
-  if (e == hipSuccess) e = upload(dmat, mat, (size_t)n * sizeof(uint32_t), s->stream);
-  if (e == hipSuccess) e = dnodes.alloc((size_t)nn * sizeof(BVHNode));
-  if (e == hipSuccess) e = dtris.alloc((size_t)n * sizeof(TriRec));
+  hipError_t e = upload(s, dsoup, v, (size_t)n * 9 * sizeof(float));
+  if (e == hipSuccess) e = upload(s, dprim, prim, (size_t)n * sizeof(uint32_t));
+  if (e == hipSuccess) e = upload(s, dmat, mat, (size_t)n * sizeof(uint32_t));
   GpuBvhStats st{};
   if (e == hipSuccess)
-    e = gpu_build_bvh4(dsoup.as<float>(), dprim.as<uint32_t>(), dmat.as<uint32_t>(), n, dnodes.as<BVHNode>(),
-                       dtris.as<TriRec>(), s->stream, &st, s->gpu_bvh_builder);
+    e = with_memory(s, [&] {
+      hipError_t e = dnodes.alloc((size_t)nn * sizeof(BVHNode));
+      if (e == hipSuccess) e = dtris.alloc((size_t)n * sizeof(TriRec));
+      return e == hipSuccess ? gpu_build_bvh4(dsoup.as<float>(), dprim.as<uint32_t>(), dmat.as<uint32_t>(), n,
+                                              dnodes.as<BVHNode>(), dtris.as<TriRec>(), s->stream, &st,
+                                              s->gpu_bvh_builder)
+                             : e;
+    });
   if (e == hipSuccess) {
     b.nodes.resize((size_t)st.n_nodes);
     b.tris.resize((size_t)n);
@@ -1463,12 +1509,12 @@ pt_status build_two_level(pt_scene* s, const pt_mesh* meshes, int32_t n_meshes, 
       if (!ref_is_leaf(c)) c += root;
     T.nodes.push_back(n);
   }
-  PT_HIP(upload(s->nodes, T.nodes.data(), T.nodes.size() * sizeof(BVHNode), s->stream));
-  PT_HIP(upload(s->tris, T.tris.data(), T.tris.size() * sizeof(TriRec), s->stream));
-  PT_HIP(upload(s->tlas_items, T.items.data(), T.items.size() * sizeof(uint32_t), s->stream));
-  PT_HIP(upload(s->insts, T.insts.data(), T.insts.size() * sizeof(InstRec), s->stream));
-  PT_HIP(upload(s->mesh_tri_first, T.tfirst.data(), T.tfirst.size() * sizeof(uint32_t), s->stream));
-  PT_HIP(upload(s->mesh_tri_count, T.tcount.data(), T.tcount.size() * sizeof(uint32_t), s->stream));
+  PT_HIP(upload(s, s->nodes, T.nodes.data(), T.nodes.size() * sizeof(BVHNode)));
+  PT_HIP(upload(s, s->tris, T.tris.data(), T.tris.size() * sizeof(TriRec)));
+  PT_HIP(upload(s, s->tlas_items, T.items.data(), T.items.size() * sizeof(uint32_t)));
+  PT_HIP(upload(s, s->insts, T.insts.data(), T.insts.size() * sizeof(InstRec)));
+  PT_HIP(upload(s, s->mesh_tri_first, T.tfirst.data(), T.tfirst.size() * sizeof(uint32_t)));
+  PT_HIP(upload(s, s->mesh_tri_count, T.tcount.data(), T.tcount.size() * sizeof(uint32_t)));
   PT_HIP(hipStreamSynchronize(s->stream));
   s->tmin = T.tmin;
   set_box(s, T.box_lo, T.box_hi);
@@ -1624,7 +1670,7 @@ pt_status build_bvh_any(pt_scene* s, const pt_mesh* meshes, int32_t n_meshes, co
     if (r) return named(r);
     auto t0 = std::chrono::steady_clock::now();
     DeviceSoup soup;
-    hipError_t e = gather_on_device(s, meshes, n_meshes, total, soup);
+    hipError_t e = with_memory(s, [&] { return gather_on_device(s, meshes, n_meshes, total, soup); });
     if (e != hipSuccess)
       return named(fail(PT_ERR_DEVICE, "copy of the meshes to the device failed: %s", hipGetErrorString(e)));
     if (soup.info[0]) return named(fail(PT_ERR_DEVICE, "the device's check of the meshes failed"));
@@ -1635,11 +1681,14 @@ pt_status build_bvh_any(pt_scene* s, const pt_mesh* meshes, int32_t n_meshes, co
     }
     // nodes and triangle records are written in place
     s->has_bvh = false;  // until the new one is whole
-    PT_HIP(s->nodes.alloc((size_t)std::max<int64_t>(1, total - 1) * sizeof(BVHNode)));
-    PT_HIP(s->tris.alloc((size_t)total * sizeof(TriRec)));
     GpuBvhStats st{};
-    e = gpu_build_bvh4(soup.soup, nullptr, soup.mat, total, s->nodes.as<BVHNode>(), s->tris.as<TriRec>(), s->stream,
-                       &st, s->gpu_bvh_builder);
+    e = with_memory(s, [&] {
+      hipError_t e = s->nodes.alloc((size_t)std::max<int64_t>(1, total - 1) * sizeof(BVHNode));
+      if (e == hipSuccess) e = s->tris.alloc((size_t)total * sizeof(TriRec));
+      return e == hipSuccess ? gpu_build_bvh4(soup.soup, nullptr, soup.mat, total, s->nodes.as<BVHNode>(),
+                                              s->tris.as<TriRec>(), s->stream, &st, s->gpu_bvh_builder)
+                             : e;
+    });
     if (e != hipSuccess) return fail(PT_ERR_DEVICE, "device BVH build failed: %s", hipGetErrorString(e));
     n_nodes = st.n_nodes;
     depth = st.depth;
@@ -1672,8 +1721,8 @@ pt_status build_bvh_any(pt_scene* s, const pt_mesh* meshes, int32_t n_meshes, co
     std::string err;
     if (!build_bvh4(verts.data(), prim.data(), matu.data(), total, bvh, err)) return fail(PT_ERR_INVALID_ARG, "%s", err.c_str());
     s->has_bvh = false;  // until the new one is whole
-    PT_HIP(upload(s->nodes, bvh.nodes.data(), bvh.nodes.size() * sizeof(BVHNode), s->stream));
-    PT_HIP(upload(s->tris, bvh.tris.data(), bvh.tris.size() * sizeof(TriRec), s->stream));
+    PT_HIP(upload(s, s->nodes, bvh.nodes.data(), bvh.nodes.size() * sizeof(BVHNode)));
+    PT_HIP(upload(s, s->tris, bvh.tris.data(), bvh.tris.size() * sizeof(TriRec)));
     PT_HIP(hipStreamSynchronize(s->stream));
     n_nodes = (int64_t)bvh.nodes.size();
     depth = bvh.depth;
@@ -1851,11 +1900,11 @@ pt_status pt_upload_materials(pt_scene* s, const pt_openpbr_material* m, int32_t
     tab_of[(size_t)i] = t;
   }
   if (!fuzz.empty()) {
-    PT_HIP(upload(s->fuzz_tabs, fuzz.data(), fuzz.size() * sizeof(float), s->stream));
+    PT_HIP(upload(s, s->fuzz_tabs, fuzz.data(), fuzz.size() * sizeof(float)));
     for (int i = 0; i < n; ++i)
       if (tab_of[(size_t)i] >= 0) recs[(size_t)i].fuzz_E = s->fuzz_tabs.as<float>() + 65 * (size_t)tab_of[(size_t)i];
   }
-  PT_HIP(upload(s->mats, recs.data(), recs.size() * sizeof(MatRec), s->stream));
+  PT_HIP(upload(s, s->mats, recs.data(), recs.size() * sizeof(MatRec)));
   PT_HIP(hipStreamSynchronize(s->stream));
   s->host_mats.assign(m, m + n);
   s->class_mask = mask;
@@ -1936,12 +1985,12 @@ pt_status pt_set_environment(pt_scene* s, const float* rgb, int32_t w, int32_t h
   guide(row_cdf.data(), h, kEnvRowGuide, row_guide.data());
   for (int y = 0; y < h; ++y)
     guide(&col_cdf[(size_t)y * (w + 1)], w, kEnvColGuide, &col_guide[(size_t)y * kEnvColGuide]);
-  PT_HIP(upload(s->env_row_guide, row_guide.data(), row_guide.size() * sizeof(int32_t), s->stream));
-  PT_HIP(upload(s->env_col_guide, col_guide.data(), col_guide.size() * sizeof(int32_t), s->stream));
-  PT_HIP(upload(s->env, tex.data(), n * sizeof(float4), s->stream));
-  PT_HIP(upload(s->env_col_cdf, col_cdf.data(), col_cdf.size() * sizeof(float), s->stream));
-  PT_HIP(upload(s->env_row_pmf, row_pmf.data(), row_pmf.size() * sizeof(float), s->stream));
-  PT_HIP(upload(s->env_row_cdf, row_cdf.data(), row_cdf.size() * sizeof(float), s->stream));
+  PT_HIP(upload(s, s->env_row_guide, row_guide.data(), row_guide.size() * sizeof(int32_t)));
+  PT_HIP(upload(s, s->env_col_guide, col_guide.data(), col_guide.size() * sizeof(int32_t)));
+  PT_HIP(upload(s, s->env, tex.data(), n * sizeof(float4)));
+  PT_HIP(upload(s, s->env_col_cdf, col_cdf.data(), col_cdf.size() * sizeof(float)));
+  PT_HIP(upload(s, s->env_row_pmf, row_pmf.data(), row_pmf.size() * sizeof(float)));
+  PT_HIP(upload(s, s->env_row_cdf, row_cdf.data(), row_cdf.size() * sizeof(float)));
   PT_HIP(hipStreamSynchronize(s->stream));
   s->env_w = w;
   s->env_h = h;
@@ -2089,12 +2138,12 @@ pt_status pt_set_radiance_cache(pt_scene* s, const pt_radiance_cache_config* cfg
   std::vector<float> w;
   nrc_init_weights(c.init_seed, w);
   const size_t bytes = kNrcParams * sizeof(float);
-  PT_HIP(upload(s->nrc_w, w.data(), bytes, s->stream));
-  PT_HIP(upload(s->nrc_wi, w.data(), bytes, s->stream));
+  PT_HIP(upload(s, s->nrc_w, w.data(), bytes));
+  PT_HIP(upload(s, s->nrc_wi, w.data(), bytes));
   std::vector<float> zero(kNrcParams, 0.0f);
-  PT_HIP(upload(s->nrc_m, zero.data(), bytes, s->stream));
-  PT_HIP(upload(s->nrc_v, zero.data(), bytes, s->stream));
-  PT_HIP(upload(s->nrc_e, zero.data(), bytes, s->stream));
+  PT_HIP(upload(s, s->nrc_m, zero.data(), bytes));
+  PT_HIP(upload(s, s->nrc_v, zero.data(), bytes));
+  PT_HIP(upload(s, s->nrc_e, zero.data(), bytes));
   if (!s->nrc_fwd.p) PT_HIP(s->nrc_fwd.alloc(kNrcFwdFrags * 64 * sizeof(uint4)));
   if (!s->nrc_bwd.p) PT_HIP(s->nrc_bwd.alloc(kNrcBwdFrags * 64 * sizeof(uint4)));
   if (!s->nrc_inf.p) PT_HIP(s->nrc_inf.alloc(kNrcFwdFrags * 64 * sizeof(uint4)));

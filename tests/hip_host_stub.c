@@ -11,10 +11,10 @@
 enum { kOk = 0, kOutOfMemory = 2 };
 static const size_t kTotal = (size_t)1 << 36; /* 64 GiB of address space at most */
 static size_t budget = (size_t)1 << 36, held, peak;
-static long fail_in = -1, mallocs, launches;
+static long fail_in, mallocs, launches;
 static int last_error;
 
-/* the n-th hipMalloc from now fails (n >= 1; -1: none) */
+/* the n-th hipMalloc from now and all after it fail (n >= 1; 0: none) */
 void stub_fail_malloc(long n) { fail_in = n; }
 void stub_budget(size_t bytes) { budget = bytes; }
 size_t stub_held(void) { return held; }
@@ -26,7 +26,9 @@ static size_t span(size_t n) { return (n + sizeof(size_t) + 4095) / 4096 * 4096 
 int hipMalloc(void** p, size_t n) {
   *p = NULL;
   ++mallocs;
-  if ((fail_in > 0 && --fail_in == 0) || held + n > budget || n > kTotal) return last_error = kOutOfMemory;
+  if (fail_in > 1) --fail_in;
+  else if (fail_in == 1) return last_error = kOutOfMemory;
+  if (held + n > budget || n > kTotal) return last_error = kOutOfMemory;
   char* m = mmap(NULL, span(n), PROT_READ | PROT_WRITE, MAP_PRIVATE | MAP_ANONYMOUS | MAP_NORESERVE, -1, 0);
   if (m == MAP_FAILED) return last_error = kOutOfMemory;
   *(size_t*)m = n;

@@ -65,12 +65,14 @@ def test_failed_allocation_is_reported_once(stub):
     s = pt.PtScene(0)
     stub.stub_fail_malloc(1)
     assert status(s.build_bvh, sc.meshes) == -3
+    stub.stub_fail_malloc(0)
     assert status(s.build_bvh, sc.meshes) == 0, pt.last_error()
     s.upload_materials(sc.materials)
     out = Mem(16, 16, 3)
     cam = sc.with_camera(width=16, height=16).camera
     stub.stub_fail_malloc(3)
     assert status(s.render, cam, 1, 3, 0, out) == -3
+    stub.stub_fail_malloc(0)
     assert status(s.trace_closest, rays, hits) == 0, pt.last_error()
     """)
 
@@ -91,7 +93,7 @@ def test_failed_two_level_build_leaves_no_bvh(stub):
         assert status(s.trace_closest, rays, hits) == 0
         stub.stub_fail_malloc(k)
         r = status(s.build_bvh, [mesh(3), mesh(2)], placed(40))
-        stub.stub_fail_malloc(-1)
+        stub.stub_fail_malloc(0)
         if r == 0:
             break
         failed += 1
@@ -103,4 +105,94 @@ def test_failed_two_level_build_leaves_no_bvh(stub):
         assert status(s.trace_closest, rays, hits) == 0, pt.last_error()
         s.close()
     assert failed >= 5
+    """)
+
+
+def test_long_passes_leave_room_and_shrink(stub):
+    """Passes of many samples leave the device as much free memory as they hold, down to one sample."""
+    _run(stub, """
+    sc = scenes.cornell()
+    s = pt.scene_from(sc, device=0)
+    cam = sc.with_camera(width=512, height=512).camera
+    out, base = Mem(512, 512, 3), stub.stub_held()
+    one = None
+    for gib in (64.0, 16.0, 4.0, 1.0, 0.25):
+        stub.stub_budget(base + int(gib * 2 ** 30))
+        assert status(s.render, cam, 400, 5, 0, out) == 0, (gib, pt.last_error())
+        held = stub.stub_held() - base
+        assert held <= 0.5 * gib * 2 ** 30 + 2 ** 24, (gib, held)  # (the sums and counters beside the paths)
+        s.close()
+        s = pt.scene_from(sc, device=0)
+    # one sample of every pixel, and no more, fits
+    stub.stub_budget(1 << 40)
+    s.render(cam, 1, 5, 0, out)
+    one = stub.stub_held()
+    s.close()
+    s = pt.scene_from(sc, device=0)
+    stub.stub_budget(one)
+    assert status(s.render, cam, 400, 5, 0, out) in (0, -3)
+    assert status(s.render, cam, 1, 5, 0, out) == 0, pt.last_error()
+    """)
+
+
+def test_idle_path_sets_are_given_back(stub):
+    """What a long render holds is there again for the scene's other calls when the device is full."""
+    _run(stub, """
+    sc = scenes.cornell()
+    cam = sc.with_camera(width=512, height=512).camera
+    big = sc.with_camera(width=1024, height=1024).camera
+    out = Mem(1024, 1024, 3)
+    v, f = scenes.icosphere(5)
+    mesh = scenes.Mesh(v.astype(np.float32), f.astype(np.int32), np.zeros(len(f), np.int32))
+
+    def frames(s):
+        s.set_radiance_cache(pt.cache_config())
+        s.render(big, 3, 5, 0, out)
+
+    def records(s):
+        s.set_radiance_cache(pt.cache_config(train_paths=1 << 20))
+        x, t = Mem(64, 12), Mem(64, 3)
+        s.nrc_training_records(cam, 0, 5, 0, x, t)
+
+    calls = dict(
+        one_sample=lambda s: s.render(big, 1, 5, 0, out),
+        tail_off=lambda s: (s.set_tail(0, 0.0), s.render(big, 1, 5, 0, out)),
+        frames=frames, records=records,
+        host_build=lambda s: s.build_bvh([mesh]),
+        sums=lambda s: s.set_accumulation(Mem(4096, 4096, 3), 1),
+        environment=lambda s: s.set_environment(np.ones((512, 1024, 3), np.float32)),
+        rays=lambda s: s.trace_closest(Mem(1 << 20, 8), Mem(1 << 20, 6)),
+    )
+    for name, call in calls.items():
+        s = pt.scene_from(sc, device=0)
+        stub.stub_budget(1 << 36)
+        s.render(cam, 400, 5, 0, out)   # two path sets
+        held = stub.stub_held()
+        assert held > 4 << 30
+        stub.stub_budget(held)          # others took the rest
+        assert status(call, s) == 0, (name, pt.last_error())
+        s.render(cam, 4, 5, 0, out)     # and the path sets are there again
+        s.close()
+        stub.stub_budget(1 << 36)
+        assert stub.stub_held() == 0, name
+    """)
+
+
+def test_device_build_gets_idle_path_sets(stub):
+    """As above for a build on the device.  Its kernels do nothing here, so it ends in their error: what
+    it must not report is the lack of memory."""
+    _run(stub, """
+    sc = scenes.cornell()
+    cam = sc.with_camera(width=512, height=512).camera
+    v, f = scenes.icosphere(5)
+    mesh = scenes.Mesh(v.astype(np.float32), f.astype(np.int32), np.zeros(len(f), np.int32))
+    place = [scenes.Instance(np.eye(3, 4, dtype=np.float32), 0, -1)]
+    for instances in ((), place):
+        s = pt.scene_from(sc, device=0)
+        s.render(cam, 400, 5, 0, Mem(512, 512, 3))
+        stub.stub_budget(stub.stub_held())
+        assert status(s.build_bvh, [mesh], instances, on_device=True) != 0
+        assert "build failed" in pt.last_error() and "memory" not in pt.last_error(), pt.last_error()
+        s.close()
+        stub.stub_budget(1 << 36)
     """)
