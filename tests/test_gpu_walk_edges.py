@@ -117,3 +117,32 @@ def test_short_directions_equal_brute_force(which, kind):
     assert int(b[:, 5].sum()) > n // 10, "too few rays hit to tell anything"
     bad = torch.nonzero((a != b).any(1)).ravel()
     assert len(bad) == 0, f"{len(bad)} of {n} rays differ, first {bad[:5].tolist()}: {rays[bad[:2]].tolist()}"
+
+
+def test_walk_with_64_bit_node_addresses():
+    """Node arrays of 4 GiB and more (here 33.6M triangles, whose device build reserves a node each) are
+    walked with 64-bit addresses: hits equal the ones of testing every triangle."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2407_19977_amd import pt, scenes
+    n = 4098  # grid of n x n vertices, two triangles a cell
+    print(f"[walk] height field of {2 * (n - 1) ** 2} triangles", flush=True)
+    x, z = np.meshgrid(np.linspace(-1, 1, n, dtype=np.float32), np.linspace(-1, 1, n, dtype=np.float32))
+    v = np.stack([x, np.float32(0.1) * np.sin(9 * x) * np.cos(7 * z), z], -1).reshape(-1, 3)
+    c = (np.arange(n - 1, dtype=np.int32)[:, None] * n + np.arange(n - 1, dtype=np.int32)[None, :]).reshape(-1)
+    f = np.concatenate([np.stack([c, c + n, c + 1], 1), np.stack([c + 1, c + n, c + n + 1], 1)])
+    assert 128 * (len(f) - 1) > 2 ** 32
+    s = pt.PtScene(0)
+    s.build_bvh([scenes.Mesh(v, f, np.zeros(len(f), np.int32))], on_device=True)
+    r = np.random.Generator(np.random.PCG64(3))
+    rays = np.zeros((256, 8), np.float32)
+    rays[:, 0:3] = r.uniform([-1, 0.2, -1], [1, 0.5, 1], (256, 3))
+    rays[:, 4:7] = r.uniform([-1, -1, -1], [1, 0, 1], (256, 3))
+    rays[:, 3], rays[:, 7] = 1e-4, np.inf
+    rays = torch.from_numpy(rays).to("cuda:0")
+    a = torch.empty((256, 6), dtype=torch.int32, device="cuda:0")
+    b = torch.empty_like(a)
+    s.trace_closest(rays, a)
+    s.trace_closest(rays, b, brute_force=True)
+    s.close()
+    assert int(b[:, 5].sum()) > 100 and torch.equal(a, b)
