@@ -1021,6 +1021,7 @@ pt_status nrc_ensure_ws(pt_scene* s, int64_t N) {
   int64_t npad;
   nrc_split(N, split, npad);
   if (npad > s->nrc_ws_npad) {
+    s->nrc_ws_npad = 0;
     size_t store = (size_t)6 * 64 * (size_t)npad * sizeof(uint16_t);
     PT_HIP(s->nrc_a.alloc(store));
     PT_HIP(s->nrc_g.alloc(store));
@@ -1029,6 +1030,7 @@ pt_status nrc_ensure_ws(pt_scene* s, int64_t N) {
     s->nrc_ws_npad = npad;
   }
   if (split > s->nrc_ws_split) {
+    s->nrc_ws_split = 0;
     PT_HIP(s->nrc_dw.alloc((size_t)split * kNrcParams * sizeof(float)));
     s->nrc_ws_split = split;
   }
@@ -1152,6 +1154,8 @@ pt_status check_render_args(int spp, int max_depth) {
 
 pt_status ensure_accum(pt_scene* s, int W, int H) {
   if (s->acc_w != W || s->acc_h != H || !s->sum.p) {
+    s->acc_w = s->acc_h = 0;
+    s->acc_samples = 0;
     PT_HIP(with_memory(s, [&] { return s->sum.alloc((size_t)W * H * 3 * sizeof(double)); }));
     PT_HIP(launch_zero_f64(s->sum.as<double>(), (int64_t)W * H * 3, s->stream));
     s->acc_w = W;
@@ -1899,6 +1903,7 @@ pt_status pt_upload_materials(pt_scene* s, const pt_openpbr_material* m, int32_t
     }
     tab_of[(size_t)i] = t;
   }
+  s->has_mats = false;  // until the new ones are whole
   if (!fuzz.empty()) {
     PT_HIP(upload(s, s->fuzz_tabs, fuzz.data(), fuzz.size() * sizeof(float)));
     for (int i = 0; i < n; ++i)
@@ -1985,6 +1990,8 @@ pt_status pt_set_environment(pt_scene* s, const float* rgb, int32_t w, int32_t h
   guide(row_cdf.data(), h, kEnvRowGuide, row_guide.data());
   for (int y = 0; y < h; ++y)
     guide(&col_cdf[(size_t)y * (w + 1)], w, kEnvColGuide, &col_guide[(size_t)y * kEnvColGuide]);
+  s->env_w = s->env_h = 0;  // none until the new one is whole
+  s->lights_dirty = true;
   PT_HIP(upload(s, s->env_row_guide, row_guide.data(), row_guide.size() * sizeof(int32_t)));
   PT_HIP(upload(s, s->env_col_guide, col_guide.data(), col_guide.size() * sizeof(int32_t)));
   PT_HIP(upload(s, s->env, tex.data(), n * sizeof(float4)));
@@ -2138,6 +2145,7 @@ pt_status pt_set_radiance_cache(pt_scene* s, const pt_radiance_cache_config* cfg
   std::vector<float> w;
   nrc_init_weights(c.init_seed, w);
   const size_t bytes = kNrcParams * sizeof(float);
+  s->nrc_on = s->nrc_ready = false;  // until the new one is whole
   PT_HIP(upload(s, s->nrc_w, w.data(), bytes));
   PT_HIP(upload(s, s->nrc_wi, w.data(), bytes));
   std::vector<float> zero(kNrcParams, 0.0f);

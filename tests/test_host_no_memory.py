@@ -196,3 +196,44 @@ def test_device_build_gets_idle_path_sets(stub):
         s.close()
         stub.stub_budget(1 << 36)
     """)
+
+
+def test_failed_replacements_do_not_count_as_there(stub):
+    """Materials, sums, the cache's workspace and its configuration: a call that ran out of memory after
+    it gave up the old buffer leaves none, and later calls refuse or allocate again."""
+    _run(stub, """
+    sc = scenes.cornell()
+    cam, big = (sc.with_camera(width=w, height=w).camera for w in (16, 512))
+    out = Mem(512, 512, 3)
+
+    def full(f, *args, **kw):
+        stub.stub_fail_malloc(1)
+        r = status(f, *args, **kw)
+        stub.stub_fail_malloc(0)
+        return r
+
+    # materials (more of them than before)
+    s = pt.scene_from(sc, device=0)
+    assert full(s.upload_materials, np.tile(np.asarray(sc.materials, np.float32).reshape(-1, 39), (50, 1))) == -3
+    assert status(s.render, cam, 1, 3, 0, out) == -5
+    s.upload_materials(sc.materials)
+    assert status(s.render, cam, 1, 3, 0, out) == 0
+    # sums (a larger image)
+    s.accumulate(cam, 0, 1, 3, 0)
+    assert full(s.accumulate, big, 0, 1, 3, 0) == -3
+    launched = stub.stub_launches()
+    assert status(s.resolve, out) == -5 and status(s.display, Mem(512, 512)) == -5
+    assert stub.stub_launches() == launched
+    # the cache's workspace: a gradient of more samples, then one of fewer
+    s.set_radiance_cache(pt.cache_config())
+    g = Mem(pt.NRC_PARAMS)
+    assert status(s.nrc_gradient, Mem(64, 12), Mem(64, 3), g) == 0
+    assert full(s.nrc_gradient, Mem(1 << 16, 12), Mem(1 << 16, 3), g) == -3
+    allocated = stub.stub_mallocs()
+    assert status(s.nrc_gradient, Mem(64, 12), Mem(64, 3), g) == 0
+    assert stub.stub_mallocs() > allocated
+    # its configuration: self-training needs a buffer per training path
+    s.set_radiance_cache(pt.cache_config(train_end_bounce=3))
+    assert full(s.set_radiance_cache, pt.cache_config(train_end_bounce=3, train_paths=1 << 20)) == -3
+    assert status(s.nrc_gradient, Mem(64, 12), Mem(64, 3), g) == -5
+    """)
