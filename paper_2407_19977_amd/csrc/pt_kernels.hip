@@ -431,7 +431,7 @@ constexpr int kTraceWaves2 = PT_TRACE_WAVES_2;  // two-level scenes: the world-s
 struct LaneRay {
   float ox, oy, oz;
   float Sx, Sy, Sz;
-  uint32_t k;  // kx, ky, kz, two bits each
+  uint32_t k;  // kx, ky, kz, two bits each (never 0; two-level scenes: 0 while the box test's constants are the world ray's)
   // Box test of a plane p of axis a: t = fma(p, i_a, c) with c = -(o_a i_a) moved
   // by slack to the safe side, n_a for the plane the ray meets first and f_a for
   // the other.
@@ -536,6 +536,7 @@ __device__ inline void lane_start(LaneRay& L, float ox, float oy, float oz, floa
     L.wdy = dy;
     L.wdz = dz;
     lane_box(L, ox, oy, oz, dx, dy, dz);
+    L.k = 0u;
   } else {
     lane_ray(L, ox, oy, oz, dx, dy, dz);
   }
@@ -721,16 +722,19 @@ __device__ inline bool lane_step(const SceneDev& S, LaneRay& L, float tmin, DevS
     L.cur = kEmpty;
   }
   while (true) {
-    if (TWO && L.inst != kNoInst && st.top == L.base) {  // mesh walk over: back to the top level
-      L.inst = kNoInst;
-      lane_box(L, L.wox, L.woy, L.woz, L.wdx, L.wdy, L.wdz);
-    }
+    if (TWO && L.inst != kNoInst && st.top == L.base) L.inst = kNoInst;  // mesh walk over: back to the top level
     if (st.empty()) return true;
     const unsigned long long e = st.pop(S);
     const float k = u2f((uint32_t)(e >> 32));
     if (k <= widen_limit(L.t)) {
       L.cur = (uint32_t)e;
       if (TWO) L.cur_key = k;
+      if (TWO && L.inst == kNoInst && L.k != 0u && !ref_is_leaf(L.cur)) {
+        // a top-level node after a mesh walk: its boxes need the world ray's constants (most entries
+        // here are instances, which do not)
+        lane_box(L, L.wox, L.woy, L.woz, L.wdx, L.wdy, L.wdz);
+        L.k = 0u;
+      }
       return false;
     }
   }
