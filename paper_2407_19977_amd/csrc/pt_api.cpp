@@ -1583,7 +1583,9 @@ pt_status check_build_args(const pt_mesh* meshes, int32_t n_meshes, const pt_ins
 // soup, box, page faults of 57 MB of vectors) took 19 ms for 1.31M triangles;
 // the copy is bound by the host link (29 MB, 0.9 ms).  Many small meshes are
 // joined on the host first: three copies and two launches a mesh take as long
-// as its host work at about 2000 triangles.
+// as its host work at about 2000 triangles, and builds below that many are
+// checked and made into soup on the host altogether.
+constexpr int64_t kGatherTris = 2000;
 struct DeviceSoup {
   DevBuf mem;
   float* soup = nullptr;
@@ -1594,7 +1596,7 @@ struct DeviceSoup {
 hipError_t gather_on_device(pt_scene* s, const pt_mesh* meshes, int32_t n_meshes, int64_t total, DeviceSoup& out) {
   int64_t nv = 0;
   for (int i = 0; i < n_meshes; ++i) nv += meshes[i].n_vertices;
-  const bool join = n_meshes > 1 && total < 2000 * (int64_t)n_meshes && nv <= INT32_MAX;
+  const bool join = n_meshes > 1 && total < kGatherTris * (int64_t)n_meshes && nv <= INT32_MAX;
   const auto up = [](size_t b) { return (b + 255) & ~size_t(255); };
   const size_t b_soup = up((size_t)total * 9 * sizeof(float)), b_mat = up((size_t)total * sizeof(uint32_t)),
                b_idx = up((size_t)total * 3 * sizeof(int32_t)), b_vert = up((size_t)nv * 3 * sizeof(float));
@@ -1655,33 +1657,64 @@ pt_status build_bvh_any(pt_scene* s, const pt_mesh* meshes, int32_t n_meshes, co
   pt_status r = check_scene(s);
   if (r) return r;
   int64_t total = 0;
-  const bool gather = on_device && n_instances == 0;
-  // a device build checks the contents where it gathers them; the host's check then names what it found
-  r = check_build_args(meshes, n_meshes, instances, n_instances, !gather, &total);
+  r = check_build_args(meshes, n_meshes, instances, n_instances, false, &total);
   const auto named = [&](pt_status other) {
     const pt_status c = check_build_args(meshes, n_meshes, instances, n_instances, true, &total);
     return c ? c : other;
   };
-  if (r) return gather ? named(r) : r;
+  if (r) return named(r);
+  // a large build on the device checks the contents where it gathers them; the host's check then names what it found
+  const bool gather = on_device && n_instances == 0 && total >= kGatherTris;
+  if (!gather && (r = named(PT_OK))) return r;
   if (n_instances > 0) return build_two_level(s, meshes, n_meshes, instances, n_instances, on_device);
   int64_t n_nodes = 0;
   int depth = 0, max_leaf = 0;
   int32_t max_mat = -1;
   double sah = 0.0, build_ms = 0.0;
   double lo[3] = {INFINITY, INFINITY, INFINITY}, hi[3] = {-INFINITY, -INFINITY, -INFINITY};
+  const auto host_soup = [&](float* verts, uint32_t* mat) {  // and largest material, box
+    int64_t t = 0;
+    for (int i = 0; i < n_meshes; ++i) {
+      const pt_mesh& m = meshes[i];
+      for (int64_t k = 0; k < m.n_triangles; ++k, ++t) {
+        for (int v = 0; v < 3; ++v) {
+          int32_t vi = m.indices[3 * k + v];
+          for (int c = 0; c < 3; ++c) verts[9 * (size_t)t + 3 * v + c] = m.vertices[3 * (size_t)vi + c];
+        }
+        mat[t] = (uint32_t)m.material_ids[k];
+        max_mat = std::max(max_mat, m.material_ids[k]);
+      }
+    }
+    for (size_t q = 0; q < (size_t)total * 9; q += 3)
+      for (int k = 0; k < 3; ++k) {
+        lo[k] = std::min(lo[k], (double)verts[q + k]);
+        hi[k] = std::max(hi[k], (double)verts[q + k]);
+      }
+  };
   if (on_device) {
     r = set_device(s);
     if (r) return named(r);
     auto t0 = std::chrono::steady_clock::now();
     DeviceSoup soup;
-    hipError_t e = with_memory(s, [&] { return gather_on_device(s, meshes, n_meshes, total, soup); });
-    if (e != hipSuccess)
-      return named(fail(PT_ERR_DEVICE, "copy of the meshes to the device failed: %s", hipGetErrorString(e)));
-    if (soup.info[0]) return named(fail(PT_ERR_DEVICE, "the device's check of the meshes failed"));
-    max_mat = (int32_t)soup.info[1];
-    for (int k = 0; k < 3; ++k) {
-      lo[k] = gpu_ordered_float(soup.info[2 + k]);
-      hi[k] = gpu_ordered_float(soup.info[5 + k]);
+    hipError_t e = hipSuccess;
+    if (gather) {
+      e = with_memory(s, [&] { return gather_on_device(s, meshes, n_meshes, total, soup); });
+      if (e != hipSuccess)
+        return named(fail(PT_ERR_DEVICE, "copy of the meshes to the device failed: %s", hipGetErrorString(e)));
+      if (soup.info[0]) return named(fail(PT_ERR_DEVICE, "the device's check of the meshes failed"));
+      max_mat = (int32_t)soup.info[1];
+      for (int k = 0; k < 3; ++k) {
+        lo[k] = gpu_ordered_float(soup.info[2 + k]);
+        hi[k] = gpu_ordered_float(soup.info[5 + k]);
+      }
+    } else {  // vertices, then materials, in one copy
+      std::vector<float> words((size_t)total * 10);
+      std::vector<uint32_t> mat((size_t)total);
+      host_soup(words.data(), mat.data());
+      std::memcpy(&words[(size_t)total * 9], mat.data(), mat.size() * sizeof(uint32_t));
+      PT_HIP(upload(s, soup.mem, words.data(), words.size() * sizeof(float)));
+      soup.soup = soup.mem.as<float>();
+      soup.mat = soup.mem.as<uint32_t>() + total * 9;
     }
     // nodes and triangle records are written in place
     s->has_bvh = false;  // until the new one is whole
@@ -1701,24 +1734,8 @@ pt_status build_bvh_any(pt_scene* s, const pt_mesh* meshes, int32_t n_meshes, co
   } else {
     std::vector<float> verts((size_t)total * 9);
     std::vector<uint32_t> prim((size_t)total), matu((size_t)total);
-    int64_t t = 0;
-    for (int i = 0; i < n_meshes; ++i) {
-      const pt_mesh& m = meshes[i];
-      for (int64_t k = 0; k < m.n_triangles; ++k, ++t) {
-        for (int v = 0; v < 3; ++v) {
-          int32_t vi = m.indices[3 * k + v];
-          for (int c = 0; c < 3; ++c) verts[9 * (size_t)t + 3 * v + c] = m.vertices[3 * (size_t)vi + c];
-        }
-        matu[(size_t)t] = (uint32_t)m.material_ids[k];
-        prim[(size_t)t] = (uint32_t)t;
-        max_mat = std::max(max_mat, m.material_ids[k]);
-      }
-    }
-    for (size_t q = 0; q < verts.size(); q += 3)
-      for (int k = 0; k < 3; ++k) {
-        lo[k] = std::min(lo[k], (double)verts[q + k]);
-        hi[k] = std::max(hi[k], (double)verts[q + k]);
-      }
+    for (int64_t t = 0; t < total; ++t) prim[(size_t)t] = (uint32_t)t;
+    host_soup(verts.data(), matu.data());
     r = set_device(s);
     if (r) return r;
     Bvh4 bvh;

@@ -94,3 +94,52 @@ def test_refused_meshes_leave_the_scene(parts, fault):
         assert torch.equal(before, after)
     finally:
         s.close()
+
+
+@pytest.mark.parametrize("parts", [1, 3, 40])
+@pytest.mark.parametrize("fault", ["index", "low_index", "nan", "inf_unused", "material"])
+def test_refused_large_meshes(parts, fault):
+    """Builds of 2000 triangles and more are checked on the device: refused with the host build's words,
+    and a mesh of 1999 or 2000 triangles gives the host build's hits."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    print(f"[refuse] {fault} in {parts}, large", flush=True)
+    from paper_2407_19977_amd import pt, scenes
+    sc = scenes.spheres(level=2, env_size=(64, 32))
+    meshes = _split(sc.meshes[0], parts)
+    assert sum(m.n_triangles for m in meshes) > 2000
+    s = pt.PtScene(0)
+    try:
+        m = meshes[-1]
+        v, ix, mid = m.vertices.copy(), m.indices.copy(), m.material_ids.copy()
+        if fault == "index":
+            ix[-1, 2] = len(v)
+        elif fault == "low_index":
+            ix[0, 1] = -1
+        elif fault == "nan":
+            v[0, 1] = np.nan
+        elif fault == "inf_unused":
+            v = np.concatenate([v, np.full((1, 3), np.inf, np.float32)])
+        else:
+            mid[0] = -3
+        said = []
+        for dev in (False, True):
+            with pytest.raises(Exception) as e:
+                s.build_bvh(meshes[:-1] + [scenes.Mesh(v, ix, mid)], on_device=dev)
+            said.append(str(e.value))
+        assert said[0] == said[1] and f"mesh {parts - 1}" in said[0]
+        r = np.random.default_rng(1)
+        rays = np.zeros((2000, 8), np.float32)
+        rays[:, 0:3], rays[:, 4:7] = r.uniform(-8, 8, (2000, 3)), r.normal(size=(2000, 3))
+        rays[:, 3], rays[:, 7] = 1e-4, np.inf
+        rays = torch.from_numpy(rays).to("cuda:0")
+        m = sc.meshes[0]
+        for n in (1999, 2000):
+            part = [scenes.Mesh(m.vertices, m.indices[:n], m.material_ids[:n])]
+            hits = []
+            for dev in (False, True):
+                s.build_bvh(part, on_device=dev)
+                hits.append(s.trace_closest(rays, torch.empty((2000, 6), dtype=torch.int32, device="cuda:0")).clone())
+            assert torch.equal(hits[0], hits[1]) and int(hits[0][:, 5].sum()) > 10
+    finally:
+        s.close()
