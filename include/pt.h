@@ -255,7 +255,7 @@ pt_status pt_render_debug(pt_scene* scene, const pt_camera* camera, int32_t x0, 
                           uint64_t* signature);
 
 /* Closest hit of n rays (device, [n][8] float: ox, oy, oz, tmin, dx, dy, dz,
- * tmax) written to hits (device, [n][6] uint32: t bits, instance, primitive,
+ * tmax; directions of any length) written to hits (device, [n][6] uint32: t bits, instance, primitive,
  * b1 bits, b2 bits, 1 if hit; a miss is +inf, 0xFFFFFFFF, 0xFFFFFFFF, 0, 0, 0).
  * brute_force != 0 tests every triangle instead of walking the BVH.  Ties
  * in t resolve to the smallest (instance, primitive). */

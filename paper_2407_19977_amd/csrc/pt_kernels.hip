@@ -381,13 +381,15 @@ __global__ void k_reset_counts(uint32_t* counts, int next_queue) {
 }
 
 // ------------------------------------------------------------------ extend
-// Persistent lanes: each workgroup owns a contiguous share of the ray queue
-// and its lanes take rays from that share through an LDS counter.  A lane
-// advances its own walk one node or one leaf per loop iteration; when half
-// the wave is idle, the idle lanes take new rays, so the wave's SIMD lanes
-// stay busy instead of waiting for the longest ray of a fixed batch.  The
-// walk visits exactly what the recursive definition would (same culling and
-// child order), so the closest hit is unchanged bit for bit.
+// Persistent lanes: a workgroup takes its items of the ray queues (chunks of
+// kShareChunk dealt round-robin; ray queries: one run of the array) through an
+// LDS counter.  A lane advances its own walk one node or one leaf per loop
+// iteration; once kRefill lanes of a wave are idle they take new rays, so the
+// wave's SIMD lanes stay busy instead of waiting for the longest ray of a
+// fixed batch.  Boxes are visited in the order of the recursive walk (entry
+// distance, then reference); their test is wider than that walk's, never
+// narrower, and the triangle test is the same, so the closest hit is unchanged
+// bit for bit.
 constexpr uint32_t kNoInst = 0xFFFFFFFFu;
 #ifndef PT_REFILL
 #define PT_REFILL 20  // 10 / 16 / 20 / 24: field 87.7 / 86.9 / 86.4 / 86.8 ms, instanced 117.4 / 114.3 / 112.9 / 112.6
@@ -1169,10 +1171,11 @@ __device__ inline void shade_tile(const PathsDev& P, const uint32_t* q_cls, uint
 }
 
 // Waves per SIMD that the shading kernel of a class is compiled for: 4 (128
-// registers), 3 for the general class, which needs 153 and would keep some in
-// scratch (material zoo 1024x768, 40 spp, its launches 6.52 ms at 4, 5.99
-// at 3; coated 1.49 / 1.57, glass 0.58 / 0.64; instanced scene glass 3.55 / 3.97).
-// Icosphere field render at 3 / 4 / 5 / 6: 89.1 / 88.4 / 94.5 / 99.5 ms.
+// registers), 3 for the general class, which needs 153.  Material zoo 1024x768, 40
+// spp, its launches at 4 / 3: 5.99 / 5.94 ms a render (6.52 / 5.99 while it needed 165
+// and kept 144 bytes a lane in scratch at 4); coated 1.44 / 1.57, glass 0.58 / 0.64;
+// instanced scene, glass 3.53 / 3.97.  Icosphere field render at 3 / 4 / 5 / 6: 89.1 /
+// 88.4 / 94.5 / 99.5 ms.
 constexpr int shade_waves(int cls) { return cls == kClsGeneral ? 3 : 4; }
 template <int CLS, bool DEBUG, bool TWO>
 __global__ __launch_bounds__(kShadeBlock, shade_waves(CLS)) void k_shade(SceneDev S, PathsDev P, int b, int max_depth, int next,
