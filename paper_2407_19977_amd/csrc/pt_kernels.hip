@@ -121,12 +121,12 @@ struct DevStack {
       push_lds(e);
       return;
     }
-    const uint32_t i = (uint32_t)(top - lds_end()) / kBlock;  // entries in the spill area
-    if (i >= (uint32_t)(S.stack_cap - kLdsStack)) {
+    const int i = (int)((uint32_t)(top - lds_end()) / kBlock);  // entries in the spill area
+    if (i >= S.stack_cap - kLdsStack) {  // (a capacity below kLdsStack: none)
       overflow = true;
       return;
     }
-    *spill_entry(S, i) = e;
+    *spill_entry(S, (uint32_t)i) = e;
     top += kBlock;
   }
   __device__ inline unsigned long long pop(const SceneDev& S) {
