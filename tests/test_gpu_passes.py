@@ -84,3 +84,30 @@ def test_one_shading_launch_equals_one_per_class(which):
     s.resolve(mean, sums[1])
     s.close()
     assert torch.equal(sums[0], sums[1])
+
+
+@pytest.mark.parametrize("w,h,spp", [(1, 1, 2100), (5, 3, 300), (17, 9, 9), (3, 2, 2048)])
+def test_sums_of_many_samples(scene, w, h, spp):
+    """Accumulation stages 2048 slots at a time: fewer pixels a tile for more than 8 samples, and parts
+    of one pixel's samples for more than 2048."""
+    print(f"[passes] {w}x{h}, {spp} spp", flush=True)
+    sc, s = scene
+    cam = sc.with_camera(width=w, height=h).camera
+    mean = torch.empty((h, w, 3), dtype=torch.float32, device="cuda:0")
+    sums = torch.empty((h, w, 3), dtype=torch.float64, device="cuda:0")
+    s.reset_accumulation()
+    s.accumulate(cam, 1, spp, 3, 7)
+    s.resolve(mean, sums)
+    per = torch.empty((h, w, spp, 3), dtype=torch.float32, device="cuda:0")
+    sig = torch.empty((h, w, spp), dtype=torch.int64, device="cuda:0")
+    s.render_debug(cam, 0, 0, w, h, 1, spp, 3, 7, per, sig)
+    acc = np.zeros((h, w, 3))
+    for k in range(spp):
+        acc += per[:, :, k].cpu().numpy().astype(np.float64)
+    assert np.array_equal(acc, sums.cpu().numpy())
+    # the debug output's samples are the ones of passes of their own
+    one = torch.empty((h, w, 1, 3), dtype=torch.float32, device="cuda:0")
+    sg = torch.empty((h, w, 1), dtype=torch.int64, device="cuda:0")
+    for k in (0, 1, spp // 2, spp - 1):
+        s.render_debug(cam, 0, 0, w, h, 1 + k, 1, 3, 7, one, sg)
+        assert torch.equal(one[:, :, 0], per[:, :, k]) and torch.equal(sg[:, :, 0], sig[:, :, k])
