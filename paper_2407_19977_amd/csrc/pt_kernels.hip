@@ -479,39 +479,47 @@ __device__ inline float widen_limit(float t) { return fmaf(fabsf(t), 1.907348632
 // at most 4 u |t| + u |o inv| (u = 2^-24); the constants move by 4 u |o inv| to
 // the safe side, the far distance and the pruning limit widen by 64 u and 32 u
 // relative, so every box is at least as wide as one widened by 16 u computed from
-// (p - o) / d.  A component smaller than `tiny` counts as tiny with a slack of
-// `reach` in t: finite products instead of 0 x inf, and the axis still prunes.
+// (p - o) / d.  A component smaller than tiny counts as tiny with a slack of
+// reach in t: finite products instead of 0 x inf, and the axis still prunes.
 // The ray leaves its true line by less than tiny t that way, the slack in space is
 // tiny reach, so no box is lost before t = reach.
-struct BoxSmall {
-  float tiny, reach;
-};
-// Both follow the direction's largest component m, for a ray of any length: tiny is
-// 2^-100 m (2^-126 at least, whose reciprocal is finite) and reach 2^50 / m, about
-// 10^15 units of space; the slack in space is 2^-50 (2^-76 / m below m = 2^-26).
-// Below m = 2^-128 the triangle test's 1 / m is infinite and no hit is possible.
-__device__ inline BoxSmall box_small(float dx, float dy, float dz) {
-  float m = fmaxf(fmaxf(fabsf(dx), fabsf(dy)), fabsf(dz));
-  if (m < 2.938735877055719e-39f) m = 1.0f;  // 2^-128
-  return BoxSmall{fmaxf(m * 7.888609052210118e-31f, 1.1754943508222875e-38f),
-                  __builtin_amdgcn_rcpf(m) * 1125899906842624.0f};
-}
-__device__ inline void box_axis(float o, float d, BoxSmall s, float& inv, float& n, float& f) {
-  const bool small = fabsf(d) < s.tiny;
-  inv = __builtin_amdgcn_rcpf(small ? copysignf(s.tiny, d) : d);
-  const float c = o * inv, e = fmaf(fabsf(c), 2.384185791015625e-07f, small ? s.reach : 0.0f);
+__device__ inline void box_axis(float o, float d, float reach, float& inv, float& n, float& f) {
+  inv = __builtin_amdgcn_rcpf(d);
+  const float c = o * inv, e = fmaf(fabsf(c), 2.384185791015625e-07f, reach);
   n = -c - e;
   f = -c + e;
 }
 // Byte offset in a node of the planes that a ray with inverse direction inv meets first on axis a (the others' is this ^ 16).
 __device__ inline uint32_t near_offset(uint32_t a, float inv) { return (32u * a) | ((f2u(inv) >> 27) & 16u); }
 
+// Both follow the direction's largest component m, for a ray of any length: tiny is
+// 2^-100 m (2^-126 at least, whose reciprocal is finite) and reach 2^50 / m, about
+// 10^15 units of space; the slack in space is 2^-50 (2^-76 / m below m = 2^-26).
+// Below m = 2^-128 the triangle test's 1 / m is infinite and no hit is possible.
 __device__ inline void lane_box(LaneRay& L, float ox, float oy, float oz, float dx, float dy, float dz) {
 #pragma clang fp contract(off)
-  const BoxSmall s = box_small(dx, dy, dz);
-  box_axis(ox, dx, s, L.ix, L.nx, L.fx);
-  box_axis(oy, dy, s, L.iy, L.ny, L.fy);
-  box_axis(oz, dz, s, L.iz, L.nz, L.fz);
+  const float ax = fabsf(dx), ay = fabsf(dy), az = fabsf(dz);
+  float m = fmaxf(fmaxf(ax, ay), az), rx = 0.0f, ry = 0.0f, rz = 0.0f;
+  const float kTiny = 7.888609052210118e-31f, kLeast = 1.1754943508222875e-38f;  // 2^-100, 2^-126
+  if (fminf(fminf(ax, ay), az) < fmaxf(m * kTiny, kLeast)) {  // rare: most rays have no small component
+    if (m < 2.938735877055719e-39f) m = 1.0f;  // 2^-128
+    const float tiny = fmaxf(m * kTiny, kLeast), reach = __builtin_amdgcn_rcpf(m) * 1125899906842624.0f;  // 2^50
+    if (ax < tiny) {
+      dx = copysignf(tiny, dx);
+      rx = reach;
+    }
+    if (ay < tiny) {
+      dy = copysignf(tiny, dy);
+      ry = reach;
+    }
+    if (az < tiny) {
+      dz = copysignf(tiny, dz);
+      rz = reach;
+    }
+  }
+  box_axis(ox, dx, rx, L.ix, L.nx, L.fx);
+  box_axis(oy, dy, ry, L.iy, L.ny, L.fy);
+  box_axis(oz, dz, rz, L.iz, L.nz, L.fz);
 }
 
 // The ray (o, d) of the level whose triangles are tested next.
