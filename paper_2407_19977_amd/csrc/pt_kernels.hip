@@ -1851,16 +1851,21 @@ static constexpr int32_t kTailPassSlots = 1 << 21;
 // box 160x120 3437 / 3356, 400x300 3540 / 3655, 640x400 3693 / 4057; zoo 13234 / 11373,
 // 13799 / 11979, 14343 / 14132; field 10463 / 8924, 10037 / 9287, 10026 / 10940;
 // instanced 16166 / 15908, 18828 / 16799, 20019 / 19928.  160x120, 3 bounces: zoo
-// 6184 / 8026, field 7878 / 7623, instanced 10616 / 11257.  64x48, 8,192 training
-// paths: zoo 10151 / 12087, field 8389 / 8487, instanced 12889 / 16630.
+// 6184 / 8026, field 7878 / 7623, instanced 10616 / 11257; 4 bounces: zoo 8495 / 9501,
+// instanced 12328 / 13056, field 9123 / 8231, box 3101 / 3008 (so 4 bounces are enough in
+// single-level scenes without the general class).  64x48, 8,192 training paths:
+// zoo 10151 / 12087, field 8389 / 8487, instanced 12889 / 16630.  A grid of one
+// workgroup per CU instead of all that fit: field 400x300 10933 / 9321, zoo 14181 /
+// 12118, 1000x60 7817 / 7978.
 static constexpr int32_t kWholePassSlots = 5 << 16;
 static constexpr int32_t kWholeFrameSlots = 3 << 16;
 static constexpr uint32_t kWholeTrainPaths = 1u << 15;
 static constexpr int kWholeDepth = 5;
 static bool whole_pass(const PathsDev& P, const PassArgs& A) {
   if (!A.tail_sized) return false;
-  const bool deep = A.max_depth >= kWholeDepth;
-  if (!A.tail_stream) return P.n <= kWholePassSlots && (deep || !(A.class_mask & (1u << kClsGeneral)));
+  const bool general = (A.class_mask & (1u << kClsGeneral)) != 0u;
+  const bool deep = A.max_depth >= kWholeDepth - (general || A.two_level ? 0 : 1);
+  if (!A.tail_stream) return P.n <= kWholePassSlots && (deep || !general);
   return deep && P.n <= kWholeFrameSlots && A.tail_bound >= kWholeTrainPaths && 3u * A.tail_bound >= (uint32_t)P.n;
 }
 
